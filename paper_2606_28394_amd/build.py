@@ -1,5 +1,5 @@
-"""Build the gfx950 shared library ``libjenga.so`` in-tree with hipcc (one object per source,
-compiled side by side, then linked)."""
+"""Build the gfx950 shared library ``libjenga.so`` in-tree with hipcc (one object per source, and per
+part of the step kernel's variants, compiled side by side, then linked)."""
 from __future__ import annotations
 
 import os
@@ -10,7 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjenga.so")
-SOURCES = ["jenga_step.hip", "jenga_world.hip", "jenga_mlp.hip"]
+# (source, object, flags): the step kernel's instantiations take minutes in one object
+SOURCES = [("jenga_step.hip", f"jenga_step{k}", [f"-DJG_STEP_PART={k}"]) for k in range(7)] + \
+    [("jenga_world.hip", "jenga_world", []), ("jenga_mlp.hip", "jenga_mlp", [])]
 ARCH = os.environ.get("JENGA_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
@@ -26,12 +28,12 @@ def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     inc = ["-I", os.path.join(HERE, "..", "include")]
     objs, procs = [], []
-    for s in SOURCES:
-        o = os.path.join(OBJ, os.path.splitext(s)[0] + ".o")
-        cmd = [hipcc, *FLAGS, *inc, "-c", "-o", o, os.path.join(CSRC, s)]
+    for s, name, defs in SOURCES:
+        o = os.path.join(OBJ, name + ".o")
+        cmd = [hipcc, *FLAGS, *defs, *inc, "-c", "-o", o, os.path.join(CSRC, s)]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((s, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        procs.append((name, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(o)
     failed = []
     for s, p in procs:

@@ -174,6 +174,15 @@ inline int64_t lds_words(int nbp, int pc, int tpc, int ppc, int mode) {
   return w;
 }
 
+// the step kernel's variants (each defined by the build part that compiles it): packs on chip, small
+// batches, islands in device memory (hot: the walks' body arrays in LDS), and with the network
+const void* step_variant_pack(bool ext);
+const void* step_variant_lat(bool ext);
+const void* step_variant_island(bool hot, bool ext);
+const void* step_variant_learned_pack();
+const void* step_variant_learned_island();
+const void* step_variant_learned_island_hot();
+
 // queues one launch of the step kernel; returns the hipError_t of the launch (0 = success)
 int launch_step(const StepArgs& a, size_t lds_bytes, void* stream);
 

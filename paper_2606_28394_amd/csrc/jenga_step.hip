@@ -41,13 +41,16 @@
 #include "jenga_device.h"
 #include "mlp_device.h"
 
+#ifndef JG_STEP_PART
+#error "JG_STEP_PART: 0 (launches, grid-wide islands) or the part of the step kernel's variants to compile (1 to 6)"
+#endif
+
 namespace jg {
 namespace {
 
 constexpr uint32_t kGround = 0xffffu;
 constexpr int kIslandWaves = 8;   // waves of a workgroup that steps an island in device memory
 constexpr int kLatencyWaves = 4;  // waves of a workgroup that steps one tower of a small batch
-constexpr int kMaxDevices = 64;
 
 // A barrier among the lanes of one wave.  Every phase runs on one wave (the workgroup's first),
 // so this is all its steps need: LDS and device-memory accesses of one wave are performed in
@@ -3012,6 +3015,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
   if (a.phase_cycles && lane < kPhases) atomicAdd(&a.phase_cycles[lane], L.cyc[lane]);
 }
 
+#if JG_STEP_PART == 0
 // ------------------------------------------------------------------------------------------------
 // Islands stepped by the whole GPU (Sec. "Discussion and Implications for Anastylosis": site-scale
 // walls).  One cooperative launch runs every step; its phases are separated by grid-wide barriers
@@ -3862,13 +3866,43 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
   }
 }
 
+#endif  // JG_STEP_PART == 0
+
 }  // namespace
 
+// The step kernel's variants, by part of the build (this file is compiled once per part, side by side)
+#if JG_STEP_PART == 1
+const void* step_variant_pack(bool ext) {
+  return ext ? (const void*)step_kernel<false, false, false, true> : (const void*)step_kernel<false, false, false, false>;
+}
+#elif JG_STEP_PART == 2
+const void* step_variant_lat(bool ext) {
+  return ext ? (const void*)step_kernel<false, false, false, true, true>
+             : (const void*)step_kernel<false, false, false, false, true>;
+}
+#elif JG_STEP_PART == 3
+const void* step_variant_island(bool hot, bool ext) {
+  return hot ? (ext ? (const void*)step_kernel<false, true, true, true> : (const void*)step_kernel<false, true, true, false>)
+             : (ext ? (const void*)step_kernel<false, true, false, true> : (const void*)step_kernel<false, true, false, false>);
+}
+#elif JG_STEP_PART == 4
+const void* step_variant_learned_pack() { return (const void*)step_kernel<true, false, false, true>; }
+#elif JG_STEP_PART == 5
+const void* step_variant_learned_island() { return (const void*)step_kernel<true, true, false, true>; }
+#elif JG_STEP_PART == 6
+const void* step_variant_learned_island_hot() { return (const void*)step_kernel<true, true, true, true>; }
+#endif
+
+}  // namespace jg
+
+#if JG_STEP_PART == 0
+namespace jg {
 namespace {
 
 // The dynamic-LDS limit of every variant, once per device (the current one), under a lock so
 // that worlds stepped from several host threads agree.
 int ensure_lds_limit() {
+  constexpr int kMaxDevices = 64;
   static std::mutex attr_mutex;
   static bool attr_set[kMaxDevices] = {};
   int dev = 0;
@@ -3876,14 +3910,12 @@ int ensure_lds_limit() {
   if (dev < 0 || dev >= kMaxDevices) return (int)hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(attr_mutex);
   if (!attr_set[dev]) {
-    const void* variants[11] = {
-        (const void*)step_kernel<false, false, false, false>, (const void*)step_kernel<false, false, false, true>,
-        (const void*)step_kernel<true, false, false, true>,   (const void*)step_kernel<false, true, false, false>,
-        (const void*)step_kernel<false, true, false, true>,   (const void*)step_kernel<true, true, false, true>,
-        (const void*)step_kernel<false, true, true, false>,   (const void*)step_kernel<false, true, true, true>,
-        (const void*)step_kernel<true, true, true, true>,
-        (const void*)step_kernel<false, false, false, false, true>,
-        (const void*)step_kernel<false, false, false, true, true>};
+    const void* variants[11] = {step_variant_pack(false),          step_variant_pack(true),
+                                step_variant_lat(false),           step_variant_lat(true),
+                                step_variant_island(false, false), step_variant_island(false, true),
+                                step_variant_island(true, false),  step_variant_island(true, true),
+                                step_variant_learned_pack(),       step_variant_learned_island(),
+                                step_variant_learned_island_hot()};
     for (const void* f : variants)
       if (hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024))
         return (int)e;
@@ -3900,24 +3932,20 @@ int step_launch_config(const StepArgs& a, const void** func, unsigned* block_thr
   // the variants and the episode criteria run in their own instantiations (the network's kernel
   // always carries them)
   const bool ext = a.friction_cone || a.restitution_bias || a.manifold_mode || a.ep_state;
-  const void* f;
   unsigned threads = kWave;
-  if (a.in_gmem) {
-    if (a.hot_bodies)
-      f = learned ? (const void*)step_kernel<true, true, true, true>
-                  : (ext ? (const void*)step_kernel<false, true, true, true> : (const void*)step_kernel<false, true, true, false>);
-    else
-      f = learned ? (const void*)step_kernel<true, true, false, true>
-                  : (ext ? (const void*)step_kernel<false, true, false, true> : (const void*)step_kernel<false, true, false, false>);
-    threads = learned ? step_threads<true, true>() : step_threads<false, true>();
-  } else if (a.lat && !learned) {
-    f = ext ? (const void*)step_kernel<false, false, false, true, true> : (const void*)step_kernel<false, false, false, false, true>;
+  if (learned) {
+    *func = !a.in_gmem ? step_variant_learned_pack()
+                       : (a.hot_bodies ? step_variant_learned_island_hot() : step_variant_learned_island());
+    if (a.in_gmem) threads = step_threads<true, true>();
+  } else if (a.in_gmem) {
+    *func = step_variant_island(a.hot_bodies != 0, ext);
+    threads = step_threads<false, true>();
+  } else if (a.lat) {
+    *func = step_variant_lat(ext);
     threads = step_threads<false, false, true>();
   } else {
-    f = learned ? (const void*)step_kernel<true, false, false, true>
-                : (ext ? (const void*)step_kernel<false, false, false, true> : (const void*)step_kernel<false, false, false, false>);
+    *func = step_variant_pack(ext);
   }
-  *func = f;
   *block_threads = threads;
   return 0;
 }
@@ -3956,3 +3984,4 @@ int launch_mega(const MegaArgs& a, int blocks, void* stream) {
 }
 
 }  // namespace jg
+#endif  // JG_STEP_PART == 0
