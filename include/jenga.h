@@ -405,6 +405,12 @@ int32_t jg_mlp_grad_noalloc(const float* params, const void* packed, const float
 int32_t jg_mlp_adamw(float* params, const float* grad, float* m, float* v, int32_t step, float lr, float beta1,
                      float beta2, float eps, float weight_decay, void* stream);
 
+/* A whole training step: jg_mlp_grad, jg_mlp_adamw on its gradient and jg_mlp_pack of the new
+ * parameters, with their arguments and results, in two launches. */
+int32_t jg_mlp_train_step(float* params, void* packed, const float* feats, const float* targets, int32_t n, float* grad,
+                          float* loss, void* workspace, size_t workspace_bytes, float* m, float* v, int32_t step,
+                          float lr, float beta1, float beta2, float eps, float weight_decay, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -1966,7 +1966,7 @@ __device__ __forceinline__ void learned_chunks(const Lds& L, const StepArgs& a, 
       for (int k = 0; k < 3; ++k) prevd[3 * lane + k] = f[12 + k];
       wave_sync();
       mlp::f32x4 y[4];
-      mlp::infer_chunk(net, xs, lane, y);
+      mlp::infer_chunk<4>(net, xs, lane, y);
       if (lane < 16) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {

@@ -115,22 +115,23 @@ __device__ inline void stage_row(const uint4* pk, const float f[kFeat], uint32_t
   for (int k = 13; k < kRowWords; ++k) row[k] = 0u;
 }
 
-// Network outputs for 64 staged rows (xs: 64 rows x 16 words in LDS).  On return, lanes 0..15
+// Network outputs for 16 kTiles staged rows (xs: rows x 16 words in LDS).  On return, lanes 0..15
 // hold in y[t][0..2] the outputs of row 16t + lane; other lanes hold padding.
-__device__ inline void infer_chunk(const uint4* __restrict__ pk, const uint32_t* xs, int lane, f32x4 y[4]) {
+template <int kTiles>
+__device__ inline void infer_chunk(const uint4* __restrict__ pk, const uint32_t* xs, int lane, f32x4 y[kTiles]) {
   const int g = lane >> 4, r = lane & 15;
-  bf16x8 xb[4];
+  bf16x8 xb[kTiles];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < kTiles; ++t) {
     const uint4 u = *reinterpret_cast<const uint4*>(xs + (16 * t + r) * kRowWords + 4 * g);
     xb[t] = as_bf16x8(u);
   }
-  uint32_t h1[4][4][4];   // [kb][t][word]: K block kb of layer 2's B operand, column tile t
+  uint32_t h1[4][kTiles][4];   // [kb][t][word]: K block kb of layer 2's B operand, column tile t
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     const bf16x8 a = as_bf16x8(pk[kPkW1 + m * 64 + lane]);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < kTiles; ++t) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
       acc = mfma(a, xb[t], acc);
       h1[m >> 1][t][2 * (m & 1)] = pack2(gelu(acc[0]), gelu(acc[1]));
@@ -140,32 +141,32 @@ __device__ inline void infer_chunk(const uint4* __restrict__ pk, const uint32_t*
   const float* b3 = reinterpret_cast<const float*>(pk + kPkB3);
   const f32x4 y0 = g == 0 ? f32x4{b3[0], b3[1], b3[2], 0.f} : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 4; ++t) y[t] = y0;
-  uint32_t h2[4][4];      // [t][word]: current K block of layer 3's B operand
+  for (int t = 0; t < kTiles; ++t) y[t] = y0;
+  uint32_t h2[kTiles][4]; // [t][word]: current K block of layer 3's B operand
 #pragma unroll
   for (int mo = 0; mo < 8; ++mo) {
     const float4 bb = reinterpret_cast<const float4*>(pk + kPkB2)[mo * 4 + g];
-    f32x4 acc[4];
+    f32x4 acc[kTiles];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = f32x4{bb.x, bb.y, bb.z, bb.w};
+    for (int t = 0; t < kTiles; ++t) acc[t] = f32x4{bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       const bf16x8 a = as_bf16x8(pk[kPkW2 + (mo * 4 + kb) * 64 + lane]);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < kTiles; ++t) {
         const uint4 u = {h1[kb][t][0], h1[kb][t][1], h1[kb][t][2], h1[kb][t][3]};
         acc[t] = mfma(a, as_bf16x8(u), acc[t]);
       }
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < kTiles; ++t) {
       h2[t][2 * (mo & 1)] = pack2(gelu(acc[t][0]), gelu(acc[t][1]));
       h2[t][2 * (mo & 1) + 1] = pack2(gelu(acc[t][2]), gelu(acc[t][3]));
     }
     if (mo & 1) {
       const bf16x8 a = as_bf16x8(pk[kPkW3 + (mo >> 1) * 64 + lane]);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < kTiles; ++t) {
         const uint4 u = {h2[t][0], h2[t][1], h2[t][2], h2[t][3]};
         y[t] = mfma(a, as_bf16x8(u), y[t]);
       }

@@ -28,7 +28,7 @@ EXPORTS = ["jg_default_params", "jg_create_world", "jg_destroy_world", "jg_add_b
            "jg_world_size", "jg_sync", "jg_device_views", "jg_body_slots", "jg_begin_episodes",
            "jg_query_episode",
            "jg_last_error", "jg_mlp_packed_bytes", "jg_mlp_pack", "jg_mlp_forward", "jg_mlp_grad_workspace_bytes",
-           "jg_mlp_grad", "jg_mlp_grad_noalloc", "jg_mlp_adamw"]
+           "jg_mlp_grad", "jg_mlp_grad_noalloc", "jg_mlp_adamw", "jg_mlp_train_step"]
 MLP_PARAMS, MLP_TRAINABLE, MLP_FEATURES, FEAT_RECORD = 20147, 20099, 24, 30
 PHASES = ["load/store", "forces+frames", "broad+narrow", "colouring", "manifolds", "pgs", "outputs",
           "residual", "integrate", "baumgarte"]
@@ -128,6 +128,8 @@ def load_library(path: str = LIB_PATH):
     L.jg_mlp_grad.argtypes = [vp, vp, vp, vp, C.c_int32, vp, vp, vp, sz, vp]
     L.jg_mlp_grad_noalloc.argtypes = [vp, vp, vp, vp, C.c_int32, vp, vp, vp]
     L.jg_mlp_adamw.argtypes = [vp, vp, vp, vp, C.c_int32, C.c_float, C.c_float, C.c_float, C.c_float, C.c_float, vp]
+    L.jg_mlp_train_step.argtypes = [vp, vp, vp, vp, C.c_int32, vp, vp, vp, sz, vp, vp, C.c_int32, C.c_float, C.c_float,
+                                    C.c_float, C.c_float, C.c_float, vp]
     for name in EXPORTS:
         if name not in ("jg_default_params", "jg_last_error"):
             getattr(L, name).restype = C.c_int32
@@ -364,6 +366,13 @@ def jg_mlp_adamw(params_ptr, grad_ptr, m_ptr, v_ptr, step, lr, beta1, beta2, eps
                                        float(beta2), float(eps), float(weight_decay), stream))
 
 
+def jg_mlp_train_step(params_ptr, packed_ptr, feats_ptr, targets_ptr, n, grad_ptr, loss_ptr, ws_ptr, ws_bytes, m_ptr,
+                      v_ptr, step, lr, beta1, beta2, eps, weight_decay, stream=None):
+    _check(load_library().jg_mlp_train_step(params_ptr, packed_ptr, feats_ptr, targets_ptr, int(n), grad_ptr, loss_ptr,
+                                            ws_ptr, int(ws_bytes), m_ptr, v_ptr, int(step), float(lr), float(beta1),
+                                            float(beta2), float(eps), float(weight_decay), stream))
+
+
 # ------------------------------------------------------------------------------------------------
 # convenience handles
 # ------------------------------------------------------------------------------------------------
@@ -398,14 +407,17 @@ class Mlp:
         jg_mlp_forward(self.packed.data_ptr(), f.data_ptr(), f.shape[0], y.data_ptr(), self._stream())
         return y
 
+    def _workspace(self, rows, device):
+        need = jg_mlp_grad_workspace_bytes(rows)
+        if self.ws.numel() < need:
+            self.ws = self.torch.zeros(need, dtype=self.torch.uint8, device=device)
+        return self.ws.data_ptr(), self.ws.numel()
+
     def compute_grad(self, feats, targets):
         """Gradient (JG_MLP_TRAINABLE) and loss of the mean squared error on one batch."""
         f, t = feats.contiguous(), targets.contiguous()
-        need = jg_mlp_grad_workspace_bytes(f.shape[0])
-        if self.ws.numel() < need:
-            self.ws = self.torch.zeros(need, dtype=self.torch.uint8, device=f.device)
         jg_mlp_grad(self.params.data_ptr(), self.packed.data_ptr(), f.data_ptr(), t.data_ptr(), f.shape[0],
-                    self.grad.data_ptr(), self.loss.data_ptr(), self.ws.data_ptr(), self.ws.numel(), self._stream())
+                    self.grad.data_ptr(), self.loss.data_ptr(), *self._workspace(f.shape[0], f.device), self._stream())
         return self.grad, self.loss
 
     def adamw(self, lr=3e-4, betas=(0.9, 0.999), eps=1e-8, weight_decay=1e-4):
@@ -414,10 +426,15 @@ class Mlp:
                      self.step_count, lr, betas[0], betas[1], eps, weight_decay, self._stream())
         self.pack()
 
-    def train_step(self, feats, targets, **opt):
-        _, loss = self.compute_grad(feats, targets)
-        self.adamw(**opt)
-        return loss
+    def train_step(self, feats, targets, lr=3e-4, betas=(0.9, 0.999), eps=1e-8, weight_decay=1e-4):
+        """compute_grad and adamw in one call; returns the loss."""
+        f, t = feats.contiguous(), targets.contiguous()
+        ws = self._workspace(f.shape[0], f.device)
+        jg_mlp_train_step(self.params.data_ptr(), self.packed.data_ptr(), f.data_ptr(), t.data_ptr(), f.shape[0],
+                          self.grad.data_ptr(), self.loss.data_ptr(), *ws, self.m.data_ptr(), self.v.data_ptr(),
+                          self.step_count + 1, lr, betas[0], betas[1], eps, weight_decay, self._stream())
+        self.step_count += 1
+        return self.loss
 
 
 def current_stream_handle():

@@ -143,3 +143,31 @@ def test_training_reduces_loss(J):
         first = loss if first is None else first
     _say(f"training: loss {first:.4f} -> {loss:.4f}")
     assert loss < 0.2 * first
+
+
+@pytest.mark.parametrize("n", [31, 32, 33, 16385, 131105])
+def test_forward_rows_do_not_depend_on_the_batch(J, n):
+    """A row's outputs are the same bits wherever it falls: in a partial chunk, another wave or
+    workgroup, or a workgroup's second round."""
+    import torch
+    net = J.Mlp(_params(6))
+    F = _dev(torch, _features(n, 6))
+    y = net.forward(F)
+    for first, count in ((0, 1), (n - 1, 1), (n // 2, 17), (max(0, n - 40), min(n, 40))):
+        assert torch.equal(y[first:first + count], net.forward(F[first:first + count]))
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 16385])
+def test_train_step_is_grad_adamw_and_pack(J, n):
+    """The two-launch training step gives the bits of the separate calls, packed copies included."""
+    import torch
+    F, T = _dev(torch, _features(n, 8)), _dev(torch, np.random.default_rng(9).standard_normal((n, 3)))
+    a, b = J.Mlp(_params(7)), J.Mlp(_params(7))
+    for _ in range(2):
+        loss = a.train_step(F, T, lr=1e-3, weight_decay=1e-2)
+        b.compute_grad(F, T)
+        b.adamw(lr=1e-3, weight_decay=1e-2)
+        for name in ("params", "packed", "m", "v", "grad"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), name
+        assert torch.equal(loss, b.loss)
+    assert a.step_count == b.step_count == 2
