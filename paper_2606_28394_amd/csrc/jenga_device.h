@@ -183,6 +183,11 @@ const void* step_variant_learned_pack();
 const void* step_variant_learned_island();
 const void* step_variant_learned_island_hot();
 
+// a small batch's workgroups also hold their bodies' velocities for the sweeps, from the next multiple
+// of four words on
+constexpr int kLatBodyWords = 8;
+inline int64_t lat_words(int nbp) { return 3 + (int64_t)kLatBodyWords * nbp; }
+
 // queues one launch of the step kernel; returns the hipError_t of the launch (0 = success)
 int launch_step(const StepArgs& a, size_t lds_bytes, void* stream);
 

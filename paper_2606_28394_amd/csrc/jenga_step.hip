@@ -106,6 +106,7 @@ struct Lds {
   uint32_t *tfb, *tfc;
   float* wbox;        // global packs: per 64-body window, AABB lo[3], hi[3] (broadphase)
   uint32_t* cand;     // global packs: the broadphase candidates of a step, canonical order
+  float* vw;          // small batches: the bodies' velocities during the sweeps, eight words each
   uint32_t* cslot;    // global packs: kCandPerBody candidate slots per body (the walk's output)
   int nbp, pc;
 };
@@ -167,6 +168,11 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
   } else {
     L.vsave = L.rpart = nullptr;
     L.tfb = L.tfc = nullptr;
+  }
+  L.vw = nullptr;
+  if (a.lat) {
+    p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses
+    L.vw = take(kLatBodyWords * nb);
   }
   L.wbox = a.in_gmem ? take((int)window_words(nb)) : nullptr;
   L.cand = a.in_gmem ? (uint32_t*)take(kCandPerBody * nb) : nullptr;
@@ -901,7 +907,7 @@ __device__ __forceinline__ float row_lambda_rk(float lam, float u, float rk, flo
     if (o.bias) return fmaxf(__builtin_fmaf(target - u, rk, lam), 0.f);
     return fmaxf(__builtin_fmaf(-((1.f + o.e) * u), rk, lam), 0.f);
   } else {
-    return fminf(fmaxf(__builtin_fmaf(-u, rk, lam), -bound), bound);
+    return __builtin_amdgcn_fmed3f(__builtin_fmaf(-u, rk, lam), -bound, bound);   // bound >= 0
   }
 }
 template <bool kNormal>
@@ -939,9 +945,10 @@ __device__ __forceinline__ void row_single(LBody& A, LBody& B, const float rA[3]
   lam = nl;
 }
 
-// the partner lane's value (lanes 2p and 2p + 1 swap; both must be active)
+// the partner lane's value (lanes 2p and 2p + 1 swap; both must be active: with that, bound_ctrl
+// changes nothing but lets the swap fold into the instruction that uses it)
 __device__ __forceinline__ float pair_swap(float x) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, false));
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));
 }
 
 // one row on a lane pair: this lane holds body S (sg = -1: A, +1: B), its partner the other.
@@ -1195,120 +1202,191 @@ __device__ __forceinline__ void pgs_sweeps(const Lds& L, int sweeps, int ncol, i
   else pgs_sweeps_impl<false>(L, sweeps, ncol, tid, nthr, o);
 }
 
-// One row of a visit by a lane pair from the cached share of the row (r x e_K, I^-1 (r x e_K) in
-// t, the reciprocal rk of the pair's k): what row_pair computes, with the terms that do not change
-// during the sweeps taken from registers.
+// The sum of a value over a lane pair, the same bits on both lanes.
+__device__ __forceinline__ float pair_sum(float x) { return x + pair_swap(x); }
+
+// One row of a visit by a lane pair with everything that does not change during the sweeps in
+// registers: the lane's lever arm r, i = I^-1 (r x e_K), and the reciprocal rk of the pair's k.  The
+// lane of body A holds its velocities negated (S = -S_A), so that the relative velocity is the pair's
+// plain sum and both lanes apply +dl; negation is exact, so the bits are those of row_pair.
 template <int K>
-__device__ __forceinline__ void row_pair_cached(LBody& S, const SideRow<K>& t, float rk, float& lam, float bound,
-                                                const SolveOpts& o, float target, float sg) {
+__device__ __forceinline__ void row_pair_cached(LBody& S, const float r[3], const float i[3], float rk, float& lam,
+                                                float bound, const SolveOpts& o, float target) {
 #pragma clang fp contract(off)
-  const float vp = t.vpart(S);
-  const float u = sg * (vp - pair_swap(vp));
+  SideRow<K> t;
+  axis_cross<K>(r, t.c1, t.c2);
+  const float u = pair_sum(t.vpart(S));
   const float nl = row_lambda_rk<K == 0>(lam, u, rk, bound, o, target);
   const float dl = nl - lam;
-  t.apply(S, sg * dl);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) t.i[q] = i[q];
+  t.apply(S, dl);
   lam = nl;
 }
 
+// One manifold owned by a lane pair for a whole solve: this lane's side of it.
+struct OwnedManifold {
+  float f[9];            // the contact frame, negated on the lane of body A
+  float r[12], i[36];    // lever arms [j * 3 + k], and I^-1 (r x e_K) [(j * 3 + K) * 3 + q]
+  float rk[12], lam[12]; // 1 / k and impulses [j * 3 + K]
+  float tb[4];           // restitution targets (with the bias option)
+  float im, mu;
+  int body, col;         // body -1: the ground; col -1: no manifold
+};
+
+// Registers of colour-sorted manifold m (none when m >= nkept): the terms of a visit's own arithmetic.
+__device__ __forceinline__ void own_manifold(const Lds& L, int m, int nkept, bool is_b, bool bias, OwnedManifold& w) {
+  w.col = -1;
+  if (m >= nkept) return;
+  ManPoints d;
+  fetch_points(L, m, d, bias);
+  const int a_ = (int)(d.ab >> 16), b_ = (int)(d.ab & 0xffffu);
+  const bool ground = b_ == (int)kGround;
+  Frame F;
+  make_frame(d.n, F);
+  const int me = is_b ? b_ : a_;
+  LBody S;
+  load_local_g(L, me, is_b && ground, F, S);
+  float dAB[3] = {0.f, 0.f, 0.f};
+  if (!ground) {
+    float dx[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dx[k] = L.x[k * L.nbp + a_] - L.x[k * L.nbp + b_];
+    to_local(F, dx, dAB);
+  }
+  const float sg = is_b ? 1.f : -1.f;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) w.f[k] = sg * F.f[k / 3][k % 3];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float r[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      r[k] = is_b ? d.r[3 * j + k] + dAB[k] : d.r[3 * j + k];
+      w.r[3 * j + k] = r[k];
+    }
+    SideRow<0> t0;
+    SideRow<1> t1;
+    SideRow<2> t2;
+    t0.build(S, r);
+    t1.build(S, r);
+    t2.build(S, r);
+    const float k0 = t0.kpart(S), k1 = t1.kpart(S), k2 = t2.kpart(S);
+    w.rk[3 * j] = __builtin_amdgcn_rcpf(k0 + pair_swap(k0));
+    w.rk[3 * j + 1] = __builtin_amdgcn_rcpf(k1 + pair_swap(k1));
+    w.rk[3 * j + 2] = __builtin_amdgcn_rcpf(k2 + pair_swap(k2));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      w.i[9 * j + q] = t0.i[q];
+      w.i[9 * j + 3 + q] = t1.i[q];
+      w.i[9 * j + 6 + q] = t2.i[q];
+    }
+    w.tb[j] = d.tb[j];
+    // a slot past the points is worked like the others, to no effect: its row has no lever arm, no
+    // response and no step (a branch per point would cost every visit its masks and register copies)
+    const bool point = j < d.np;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) w.i[9 * j + k] = point ? w.i[9 * j + k] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      w.r[3 * j + k] = point ? w.r[3 * j + k] : 0.f;
+      w.rk[3 * j + k] = point ? w.rk[3 * j + k] : 0.f;
+      w.lam[3 * j + k] = point ? d.l[3 * j + k] : 0.f;
+    }
+  }
+  w.im = S.im;
+  w.mu = d.mu;
+  w.body = is_b && ground ? -1 : me;
+  int col = 0;
+  while (L.coloff[col + 1] <= m) ++col;
+  w.col = col;
+}
+
+// A visit of an owned manifold.  vw: the bodies' velocities, eight words each (v, w, two unused).
+__device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const SolveOpts& o) {
+  float4 p = make_float4(0.f, 0.f, 0.f, 0.f), q = p;
+  if (w.body >= 0) {
+    p = vw[2 * w.body];
+    q = vw[2 * w.body + 1];
+  }
+  const float v[3] = {p.x, p.y, p.z}, om[3] = {p.w, q.x, q.y};
+  Frame F;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) F.f[k / 3][k % 3] = w.f[k];
+  LBody S;
+  to_local(F, v, S.v);
+  to_local(F, om, S.w);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { S.v0[k] = S.v[k]; S.w0[k] = S.w[k]; }
+  S.im = w.im;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    row_pair_cached<0>(S, w.r + 3 * j, w.i + 9 * j, w.rk[3 * j], w.lam[3 * j], 0.f, o, w.tb[j]);
+    const float bound = w.mu * w.lam[3 * j];
+    row_pair_cached<1>(S, w.r + 3 * j, w.i + 9 * j + 3, w.rk[3 * j + 1], w.lam[3 * j + 1], bound, o, 0.f);
+    row_pair_cached<2>(S, w.r + 3 * j, w.i + 9 * j + 6, w.rk[3 * j + 2], w.lam[3 * j + 2], bound, o, 0.f);
+  }
+  if (w.im > 0.f) {
+    float dv[3], dw[3], gv[3], gw[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { dv[k] = S.v[k] - S.v0[k]; dw[k] = S.w[k] - S.w0[k]; }
+    to_world(F, dv, gv);
+    to_world(F, dw, gw);
+    vw[2 * w.body] = make_float4(v[0] + gv[0], v[1] + gv[1], v[2] + gv[2], om[0] + gw[0]);
+    vw[2 * w.body + 1] = make_float4(om[1] + gw[1], om[2] + gw[2], 0.f, 0.f);
+  }
+}
+
 // The sweeps of a tower stepped by a workgroup of kNthr threads (small batches).  Lane pair
-// p = tid / 2 owns colour-sorted manifold p for the whole solve: its body's share of every row
-// (r x e_K, I^-1 (r x e_K)) and the rows' 1 / k are computed once, by the arithmetic of a visit,
-// and kept in registers, so a visit only reads and writes its body's velocities.  The bits are
-// those of pgs_sweeps (the pair mode, which single lanes match bit for bit).  A tower with more
-// manifolds than lane pairs, or the disc friction variant, takes pgs_sweeps.  Every thread
-// passes the same sweeps x ncol barriers.
+// p = tid / 2 owns colour-sorted manifolds p and p + kNthr / 2 for the whole solve, in registers (about
+// 90 each), so a visit only reads and writes its body's velocities, two 16-byte LDS accesses each way.
+// A step's sweeps are a chain of visits (20 sweeps of 7 to 9 colours), so the instructions of one visit
+// and its LDS round trip are what counts: about 210 instead of 546.  Two manifolds to a pair cover
+// towers of up to 256 manifolds (28 levels) at the two waves per SIMD that let a CU hold two towers;
+// with one to a pair the 156 manifolds of 18 levels had fallen back to pgs_sweeps.  The bits are those
+// of pgs_sweeps (the pair mode, which single lanes match bit for bit).  A tower with more
+// manifolds, or the disc friction variant, takes pgs_sweeps.  Every thread passes the same barriers.
 template <int kNthr>
-__device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int ncol, int tid, const SolveOpts& o) {
+__device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int ncol, int tid, int nb, const SolveOpts& o) {
   const int nkept = L.coloff[ncol];
-  if (nkept > kNthr / 2 || o.cone) {
+  if (nkept > kNthr || o.cone) {
     pgs_sweeps(L, sweeps, ncol, tid, kNthr, o);
     return;
   }
-  const int p = tid >> 1;
+  const int p = tid >> 1, NB = L.nbp;
   const bool is_b = (tid & 1) != 0;
-  const bool mine = p < nkept;   // the same for both lanes of a pair
-  SideRow<0> t0[4];
-  SideRow<1> t1[4];
-  SideRow<2> t2[4];
-  float rk[4][3], lam[12], tb[4];
-  Frame F;
-  LBody S;
-  int me = 0, np = 0, col = -1;
-  float mu = 0.f, sg = 0.f;
-  bool ground_me = false;
-  if (mine) {
-    ManPoints d;
-    fetch_points(L, p, d, o.bias);
-    np = d.np;
-    mu = d.mu;
-    const int a_ = (int)(d.ab >> 16), b_ = (int)(d.ab & 0xffffu);
-    make_frame(d.n, F);
-    me = is_b ? b_ : a_;
-    ground_me = is_b && b_ == (int)kGround;
-    load_local_g(L, me, ground_me, F, S);
-    float dAB[3] = {0.f, 0.f, 0.f};
-    if (b_ != (int)kGround) {
-      float dx[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) dx[k] = L.x[k * L.nbp + a_] - L.x[k * L.nbp + b_];
-      to_local(F, dx, dAB);
-    }
-    sg = is_b ? 1.f : -1.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float r[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) r[k] = is_b ? d.r[3 * j + k] + dAB[k] : d.r[3 * j + k];
-      t0[j].build(S, r);
-      t1[j].build(S, r);
-      t2[j].build(S, r);
-      if (j < np) {
-        const float k0 = t0[j].kpart(S), k1 = t1[j].kpart(S), k2 = t2[j].kpart(S);
-        rk[j][0] = __builtin_amdgcn_rcpf(k0 + pair_swap(k0));
-        rk[j][1] = __builtin_amdgcn_rcpf(k1 + pair_swap(k1));
-        rk[j][2] = __builtin_amdgcn_rcpf(k2 + pair_swap(k2));
-      } else {
-        rk[j][0] = rk[j][1] = rk[j][2] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 12; ++k) lam[k] = d.l[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) tb[k] = d.tb[k];
-    col = 0;
-    while (L.coloff[col + 1] <= p) ++col;
+  float4* const vw = reinterpret_cast<float4*>(L.vw);
+  for (int i = tid; i < nb; i += kNthr) {
+    vw[2 * i] = make_float4(L.v[i], L.v[NB + i], L.v[2 * NB + i], L.w[i]);
+    vw[2 * i + 1] = make_float4(L.w[NB + i], L.w[2 * NB + i], 0.f, 0.f);
   }
+  OwnedManifold m0, m1;   // (both lanes of a pair have a manifold, or neither)
+  own_manifold(L, p, nkept, is_b, o.bias, m0);
+  own_manifold(L, p + kNthr / 2, nkept, is_b, o.bias, m1);
+  __syncthreads();
   for (int it = 0; it < sweeps; ++it) {
     for (int c = 0; c < ncol; ++c) {
-      if (mine && c == col) {
-        // the body's velocities in the frame, as load_local_g reads them
-        float v[3] = {0.f, 0.f, 0.f}, w[3] = {0.f, 0.f, 0.f};
-        if (!ground_me) {
-          load3(L.v, L.nbp, me, v);
-          load3(L.w, L.nbp, me, w);
-        }
-        to_local(F, v, S.v);
-        to_local(F, w, S.w);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) { S.v0[k] = S.v[k]; S.w0[k] = S.w[k]; }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (j < np) {
-            row_pair_cached<0>(S, t0[j], rk[j][0], lam[3 * j], 0.f, o, tb[j], sg);
-            const float bound = mu * lam[3 * j];
-            row_pair_cached<1>(S, t1[j], rk[j][1], lam[3 * j + 1], bound, o, 0.f, sg);
-            row_pair_cached<2>(S, t2[j], rk[j][2], lam[3 * j + 2], bound, o, 0.f, sg);
-          }
-        }
-        store_local(L, me, F, S);
-      }
+      if (c == m0.col) visit_owned(vw, m0, o);
+      if (c == m1.col) visit_owned(vw, m1, o);
       __syncthreads();
     }
   }
-  if (mine && !is_b) {
-    float4* rec = reinterpret_cast<float4*>(mdev(L, p));
+  for (int i = tid; i < nb; i += kNthr) {
+    const float4 a = vw[2 * i], b = vw[2 * i + 1];
+    L.v[i] = a.x; L.v[NB + i] = a.y; L.v[2 * NB + i] = a.z;
+    L.w[i] = a.w; L.w[NB + i] = b.x; L.w[2 * NB + i] = b.y;
+  }
+  if (!is_b) {
+    if (m0.col >= 0) {
+      float4* rec = reinterpret_cast<float4*>(mdev(L, p));
 #pragma unroll
-    for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(lam[4 * c], lam[4 * c + 1], lam[4 * c + 2], lam[4 * c + 3]);
+      for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(m0.lam[4 * c], m0.lam[4 * c + 1], m0.lam[4 * c + 2], m0.lam[4 * c + 3]);
+    }
+    if (m1.col >= 0) {
+      float4* rec = reinterpret_cast<float4*>(mdev(L, p + kNthr / 2));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(m1.lam[4 * c], m1.lam[4 * c + 1], m1.lam[4 * c + 2], m1.lam[4 * c + 3]);
+    }
   }
 }
 
@@ -2237,7 +2315,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
             }
           }
           __syncthreads();
-          if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, a.iters, L.scal[2], threadIdx.x, opts_h);
+          if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, a.iters, L.scal[2], threadIdx.x, nbh, opts_h);
           else pgs_sweeps(L, learned_h ? a.mlp_iters : a.iters, L.scal[2], threadIdx.x, kThreads, opts_h);
           __syncthreads();
           if (!learned_h && s == a.n_steps - 1 && sub == a.n_sub - 1) {
@@ -2792,7 +2870,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         }
       }
       __syncthreads();   // the helper waves (if any) enter the sweeps with this wave
-      if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, sweeps, ncol, threadIdx.x, opts);
+      if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, sweeps, ncol, threadIdx.x, nb, opts);
       else pgs_sweeps(L, sweeps, ncol, threadIdx.x, kThreads, opts);
       __syncthreads();
       timer.mark(L, lane, 5);

@@ -466,7 +466,7 @@ int32_t build_layout(jg_world* w) {
                   jg::window_words(c.nbp) + 2 * (int64_t)jg::kCandPerBody * c.nbp + 3) & ~(int64_t)3;
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     } else {
-      c.lds = (size_t)jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) * 4;
+      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) + (c.lat ? jg::lat_words(c.nbp) : 0)) * 4;
       if (c.lds > 160 * 1024)
         return fail(JG_ECAPACITY, "a launch class needs " + std::to_string(c.lds) + " bytes of LDS (max 163840)");
       c.gwords = ((int64_t)jg::kManPackWords * c.pc + 3) & ~(int64_t)3;
