@@ -105,7 +105,7 @@ struct StepArgs {
   int32_t manifold_mode;       // 0: literal silhouettes; 1: reference-face clipping
   int64_t step0;
   // capacities of this launch (LDS layout)
-  int32_t lat;     // 1: one tower per 256-thread workgroup (small batches), sweeps from registers
+  int32_t lat;     // small batches: threads of the workgroup that steps one tower (0: not one)
   int32_t nbp;     // bodies per pack
   int32_t pc;      // manifolds per pack
   int32_t tpc;     // towers per pack
@@ -151,10 +151,12 @@ constexpr int kCandPerBody = 16;
 // the candidate ring, towers, pushes, broadphase windows) and, with `bodies`, the body arrays
 // that the serial walks (broadphase, colouring) read: positions, AABB half sizes and colour
 // masks, flags, colouring lane masks (9 words per body)
+constexpr int kMostWaves = 8;     // waves of a workgroup that share a step
+constexpr int kWaveWords = kMostWaves * kMaxColours + 3 * (kMostWaves + 1);   // their colour counts and list starts
 constexpr int kHotBodyWords = 9;
 __host__ __device__ inline int64_t hot_words(int nbp, int tpc, int ppc, bool bodies) {
   int64_t w = 2 * kPhases + 2 * (kMaxColours + 1) + 16 + kRing + (int64_t)tpc * kTowerWords +
-              (int64_t)ppc * kPushWords + window_words(nbp);
+              (int64_t)ppc * kPushWords + window_words(nbp) + kWaveWords;
   if (bodies) w += (int64_t)kHotBodyWords * nbp;
   return w;
 }
@@ -183,10 +185,18 @@ const void* step_variant_learned_pack();
 const void* step_variant_learned_island();
 const void* step_variant_learned_island_hot();
 
-// a small batch's workgroups also hold their bodies' velocities for the sweeps, from the next multiple
-// of four words on
+// a small batch's workgroups also have (from the next multiple of four words on) a region for their
+// waves' candidate rings, the colouring's lists (kLatBodyWords words per body), the waves' colour counts
+// and the bodies' velocities during the sweeps, one after the other; each wave leaves its narrowphase's
+// colliding pairs (code, normal and depth) in a list of the pack's device block
 constexpr int kLatBodyWords = 8;
-inline int64_t lat_words(int nbp) { return 3 + (int64_t)kLatBodyWords * nbp; }
+__host__ __device__ inline int lat_shared_words(int nbp, int threads) {
+  const int rings = (threads / kWave) * kRing, counts = kMostWaves * kMaxColours, bodies = kLatBodyWords * nbp;
+  const int w = rings > counts ? rings : counts;
+  return w > bodies ? w : bodies;
+}
+inline int64_t lat_words(int nbp, int threads) { return 3 + lat_shared_words(nbp, threads); }
+inline int64_t lat_dev_words(int pc, int threads) { return (int64_t)(threads / kWave) * (kManSatWords + 1) * pc; }
 
 // queues one launch of the step kernel; returns the hipError_t of the launch (0 = success)
 int launch_step(const StepArgs& a, size_t lds_bytes, void* stream);

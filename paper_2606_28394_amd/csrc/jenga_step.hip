@@ -50,7 +50,7 @@ namespace {
 
 constexpr uint32_t kGround = 0xffffu;
 constexpr int kIslandWaves = 8;   // waves of a workgroup that steps an island in device memory
-constexpr int kLatencyWaves = 4;  // waves of a workgroup that steps one tower of a small batch
+constexpr int kLatencyWaves = 8;  // most waves of a workgroup that steps one tower of a small batch
 
 // A barrier among the lanes of one wave.  Every phase runs on one wave (the workgroup's first),
 // so this is all its steps need: LDS and device-memory accesses of one wave are performed in
@@ -62,6 +62,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 constexpr int kWindows = 4;      // broadphase register windows: packs of up to 256 bodies
+constexpr int kLatList = 8;      // entries of a body's colouring list in a small batch (in Lds::vw)
 constexpr uint32_t kErrCand = 1u, kErrMan = 2u, kErrCol = 4u, kErrNan = 8u;
 
 struct Lds {
@@ -107,6 +108,11 @@ struct Lds {
   float* wbox;        // global packs: per 64-body window, AABB lo[3], hi[3] (broadphase)
   uint32_t* cand;     // global packs: the broadphase candidates of a step, canonical order
   float* vw;          // small batches: the bodies' velocities during the sweeps, eight words each
+                      // (free before them: the colouring's lists)
+  float* csat;        // islands: the narrowphase's normal and depth by candidate slot
+  int32_t* wcol;      // several waves: colour counts and positions per wave
+  int32_t* seg;       // several waves: per wave, hits of its narrowphase; their canonical starts; the
+                      // starts of its results (kMostWaves + 1 words each)
   uint32_t* cslot;    // global packs: kCandPerBody candidate slots per body (the walk's output)
   int nbp, pc;
 };
@@ -170,13 +176,24 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
     L.tfb = L.tfc = nullptr;
   }
   L.vw = nullptr;
+  L.wcol = L.seg = nullptr;
   if (a.lat) {
     p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses
-    L.vw = take(kLatBodyWords * nb);
+    // the waves' candidate rings, then the colouring's lists, then the waves' colour counts, then the
+    // sweeps' velocities share one region; the list starts take the pack's own ring
+    L.vw = take(lat_shared_words(nb, a.lat));
+    L.seg = (int32_t*)L.ring;
+    L.ring = (uint32_t*)L.vw;
+    L.wcol = (int32_t*)L.vw;
   }
   L.wbox = a.in_gmem ? take((int)window_words(nb)) : nullptr;
   L.cand = a.in_gmem ? (uint32_t*)take(kCandPerBody * nb) : nullptr;
   L.cslot = a.in_gmem ? (uint32_t*)take(kCandPerBody * nb) : nullptr;
+  L.csat = nullptr;
+  if (a.in_gmem) {
+    p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses (the region's base is aligned)
+    L.csat = take(4 * kCandPerBody * nb);
+  }
   // the colouring's lane masks reuse the sorted-manifold words (free until the manifolds are
   // written)
   L.lmlo = L.mab;
@@ -197,6 +214,8 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
     L.pb = (int32_t*)htake(np); L.ps = (int32_t*)htake(np); L.pn = (int32_t*)htake(np);
     L.pf = htake(3 * np); L.pwd = htake(np); L.px0 = htake(3 * np);
     L.wbox = htake((int)window_words(nb));
+    L.wcol = (int32_t*)htake(kMostWaves * kMaxColours);
+    L.seg = (int32_t*)htake(3 * (kMostWaves + 1));
     if (hot_bodies) {
       L.x = htake(3 * nb); L.hm = htake(3 * nb); L.flag = (uint32_t*)htake(nb);
       L.lmlo = (uint32_t*)htake(nb); L.lmhi = (uint32_t*)htake(nb);
@@ -1337,32 +1356,33 @@ __device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const 
   }
 }
 
-// The sweeps of a tower stepped by a workgroup of kNthr threads (small batches).  Lane pair
-// p = tid / 2 owns colour-sorted manifolds p and p + kNthr / 2 for the whole solve, in registers (about
+// The sweeps of a tower stepped by a workgroup of nthr threads (small batches).  Lane pair
+// p = tid / 2 owns colour-sorted manifolds p and p + nthr / 2 for the whole solve, in registers (about
 // 90 each), so a visit only reads and writes its body's velocities, two 16-byte LDS accesses each way.
 // A step's sweeps are a chain of visits (20 sweeps of 7 to 9 colours), so the instructions of one visit
-// and its LDS round trip are what counts: about 210 instead of 546.  Two manifolds to a pair cover
-// towers of up to 256 manifolds (28 levels) at the two waves per SIMD that let a CU hold two towers;
-// with one to a pair the 156 manifolds of 18 levels had fallen back to pgs_sweeps.  The bits are those
+// and its LDS round trip are what counts: about 210 instead of 546.  Two manifolds to a pair of a
+// four-wave workgroup cover towers of up to 256 manifolds (28 levels) at the two waves per SIMD that
+// let a CU hold two towers (with one to a pair the 156 manifolds of 18 levels had fallen back to
+// pgs_sweeps: 429 us a step, now 204); eight waves cover 512.  The bits are those
 // of pgs_sweeps (the pair mode, which single lanes match bit for bit).  A tower with more
 // manifolds, or the disc friction variant, takes pgs_sweeps.  Every thread passes the same barriers.
-template <int kNthr>
-__device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int ncol, int tid, int nb, const SolveOpts& o) {
+__device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int ncol, int tid, int nthr, int nb,
+                                               const SolveOpts& o) {
   const int nkept = L.coloff[ncol];
-  if (nkept > kNthr || o.cone) {
-    pgs_sweeps(L, sweeps, ncol, tid, kNthr, o);
+  if (nkept > nthr || o.cone) {
+    pgs_sweeps(L, sweeps, ncol, tid, nthr, o);
     return;
   }
   const int p = tid >> 1, NB = L.nbp;
   const bool is_b = (tid & 1) != 0;
   float4* const vw = reinterpret_cast<float4*>(L.vw);
-  for (int i = tid; i < nb; i += kNthr) {
+  for (int i = tid; i < nb; i += nthr) {
     vw[2 * i] = make_float4(L.v[i], L.v[NB + i], L.v[2 * NB + i], L.w[i]);
     vw[2 * i + 1] = make_float4(L.w[NB + i], L.w[2 * NB + i], 0.f, 0.f);
   }
   OwnedManifold m0, m1;   // (both lanes of a pair have a manifold, or neither)
   own_manifold(L, p, nkept, is_b, o.bias, m0);
-  own_manifold(L, p + kNthr / 2, nkept, is_b, o.bias, m1);
+  own_manifold(L, p + nthr / 2, nkept, is_b, o.bias, m1);
   __syncthreads();
   for (int it = 0; it < sweeps; ++it) {
     for (int c = 0; c < ncol; ++c) {
@@ -1371,7 +1391,7 @@ __device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int nco
       __syncthreads();
     }
   }
-  for (int i = tid; i < nb; i += kNthr) {
+  for (int i = tid; i < nb; i += nthr) {
     const float4 a = vw[2 * i], b = vw[2 * i + 1];
     L.v[i] = a.x; L.v[NB + i] = a.y; L.v[2 * NB + i] = a.z;
     L.w[i] = a.w; L.w[NB + i] = b.x; L.w[2 * NB + i] = b.y;
@@ -1383,7 +1403,7 @@ __device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int nco
       for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(m0.lam[4 * c], m0.lam[4 * c + 1], m0.lam[4 * c + 2], m0.lam[4 * c + 3]);
     }
     if (m1.col >= 0) {
-      float4* rec = reinterpret_cast<float4*>(mdev(L, p + kNthr / 2));
+      float4* rec = reinterpret_cast<float4*>(mdev(L, p + nthr / 2));
 #pragma unroll
       for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(m1.lam[4 * c], m1.lam[4 * c + 1], m1.lam[4 * c + 2], m1.lam[4 * c + 3]);
     }
@@ -1793,9 +1813,18 @@ __device__ __forceinline__ void bias_targets(const Lds& L, int i, int j, bool gr
   }
 }
 
+// where the narrowphase of several waves left canonical pair p's normal and depth
+__device__ __forceinline__ int sat_slot(const Lds& L, int nw, int p) {
+  const int32_t* pre = L.seg + (kMostWaves + 1);
+  const int32_t* start = pre + (kMostWaves + 1);
+  int w = 0;
+  while (w + 1 < nw && p >= pre[w + 1]) ++w;
+  return start[w] + (p - pre[w]);
+}
+
 template <bool kExt>
-__device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a, int first, int stride, int nman,
-                                                bool keep_prev) {
+__device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a, const float* sat, int nw, int first,
+                                                int stride, int nman, bool keep_prev) {
   const int PC = L.pc;
   const int nprev = L.scal[4];
   for (int p = first; p < nman; p += stride) {
@@ -1806,7 +1835,7 @@ __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a,
     float n[3], depth;
     uint32_t slots;
     const int npts = manifold_geometry<kExt>(L, i, j, j == (int)kGround, a.manifold_mode, mdev(L, sidx), n, depth, slots,
-                                             L.msat + 4 * (size_t)p);
+                                             sat + 4 * (size_t)(nw > 1 ? sat_slot(L, nw, p) : p));
     // warm start: previous step's impulses of the same (pair, slot) if the normal barely turned
     int found = -1;
     if (keep_prev && nprev > 0) {
@@ -2209,16 +2238,15 @@ struct PhaseTimer {
 
 __device__ __forceinline__ uint64_t lane_lt_mask(int lane) { return lane ? ((~0ull) >> (64 - lane)) : 0ull; }
 
-// SAT on up to 64 ring entries starting at `head`; colliding pairs are appended (in order)
-// to the canonical list, a box pair's normal and depth beside it (msat), for its manifold.
-// Returns the new list length.
-__device__ __forceinline__ int narrow_chunk(const Lds& L, int head, int count, int nman, int lane) {
+// SAT on up to 64 candidates, one to a lane; colliding pairs are appended (in lane order) to a list of
+// `nhit`, a box pair's normal and depth beside it, for its manifold.  Returns the new list length
+// (entries beyond `cap` are counted, not written).
+__device__ __forceinline__ int narrow_chunk(const Lds& L, bool valid, uint32_t code, int nhit, int lane, uint32_t* codes,
+                                            float* sat, int cap) {
   const int NB = L.nbp;
   bool hit = false, ground = true;
-  uint32_t code = 0;
   float n[3] = {0.f, 0.f, 0.f}, depth = 0.f;
-  if (lane < count) {
-    code = L.ring[(head + lane) & (kRing - 1)];
+  if (valid) {
     const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
     ground = j == (int)kGround;
     if (ground) {
@@ -2236,13 +2264,297 @@ __device__ __forceinline__ int narrow_chunk(const Lds& L, int head, int count, i
   }
   const uint64_t bal = __ballot(hit);
   if (hit) {
-    const int idx = nman + __popcll(bal & lane_lt_mask(lane));
-    if (idx < L.pc) {
-      L.cab[idx] = code;
-      if (!ground) *reinterpret_cast<float4*>(L.msat + 4 * (size_t)idx) = make_float4(n[0], n[1], n[2], depth);
+    const int idx = nhit + __popcll(bal & lane_lt_mask(lane));
+    if (idx < cap) {
+      codes[idx] = code;
+      if (!ground) *reinterpret_cast<float4*>(sat + 4 * (size_t)idx) = make_float4(n[0], n[1], n[2], depth);
     }
   }
-  return nman + __popcll(bal);
+  return nhit + __popcll(bal);
+}
+
+// Broadphase and narrowphase of an on-chip pack's bodies i0 <= i < i1 (against every j > i) by one wave.
+// Lane l holds body 64 w + l of window w in registers (position, AABB, flags, tower); body i is
+// broadcast from its window with readlane, so the pair loop touches LDS only to append candidates to
+// the wave's ring; the SAT runs on every 64 of them, so the colliding pairs come out in canonical
+// order.  Returns their number; candidates are added to the towers' counts.
+__device__ __forceinline__ int on_chip_pairs(const Lds& L, float margin, int nb, int i0, int i1, int lane, uint32_t* ring,
+                                             uint32_t* codes, float* sat, int cap) {
+  const int NB = L.nbp;
+  int head = 0, tail = 0, nhit = 0;
+  float wx[kWindows][3], wh[kWindows][3];
+  uint32_t wf[kWindows];
+  int wt[kWindows];
+#pragma unroll
+  for (int w = 0; w < kWindows; ++w) {
+    const int j = w * kWave + lane;
+    const bool in = j < nb;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      wx[w][k] = in ? L.x[k * NB + j] : 0.f;
+      wh[w][k] = in ? L.hm[k * NB + j] : 0.f;
+    }
+    wf[w] = in ? L.flag[j] : 0u;
+    wt[w] = in ? L.tw[j] : -1;
+  }
+  const int nwin = (nb + kWave - 1) / kWave;
+  int cur_t = -1, cand_acc = 0;
+  for (int i = i0; i < i1; ++i) {
+    const int wi = i / kWave, li = i % kWave;
+    float xi[3], hi[3];
+    uint32_t fi = 0u;
+    int ti = 0;
+#pragma unroll
+    for (int w = 0; w < kWindows; ++w)
+      if (w == wi) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          xi[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wx[w][k]), li));
+          hi[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wh[w][k]), li));
+        }
+        fi = __builtin_amdgcn_readlane(wf[w], li);
+        ti = __builtin_amdgcn_readlane(wt[w], li);
+      }
+    if (!(fi & kActive)) continue;
+    if (ti != cur_t) {
+      if (lane == 0 && cur_t >= 0 && cand_acc) atomicAdd(&L.tcnt[cur_t * 4 + 0], (uint32_t)cand_acc);
+      cur_t = ti;
+      cand_acc = 0;
+    }
+    const bool dyni = (fi & kDynamic) != 0;
+#pragma unroll
+    for (int w = 0; w < kWindows; ++w) {
+      if (w < wi || w >= nwin) continue;
+      const int j = w * kWave + lane;
+      const bool hit = j > i && wt[w] == ti && (wf[w] & kActive) && (dyni || (wf[w] & kDynamic)) &&
+                       fabsf(xi[0] - wx[w][0]) <= hi[0] + wh[w][0] + margin &&
+                       fabsf(xi[1] - wx[w][1]) <= hi[1] + wh[w][1] + margin &&
+                       fabsf(xi[2] - wx[w][2]) <= hi[2] + wh[w][2] + margin;
+      const uint64_t bal = __ballot(hit);
+      if (hit) ring[(tail + __popcll(bal & lane_lt_mask(lane))) & (kRing - 1)] = ((uint32_t)i << 16) | (uint32_t)j;
+      const int cnt = __popcll(bal);
+      cand_acc += cnt;
+      tail += cnt;
+      if (tail - head >= kWave) {
+        wave_sync();
+        nhit = narrow_chunk(L, true, ring[(head + lane) & (kRing - 1)], nhit, lane, codes, sat, cap);
+        head += kWave;
+      }
+    }
+    // the ground comes last in body i's canonical row
+    if (dyni && (xi[2] - hi[2] <= margin)) {
+      if (lane == 0) ring[tail & (kRing - 1)] = ((uint32_t)i << 16) | kGround;
+      cand_acc += 1;
+      tail += 1;
+      if (tail - head >= kWave) {
+        wave_sync();
+        nhit = narrow_chunk(L, true, ring[(head + lane) & (kRing - 1)], nhit, lane, codes, sat, cap);
+        head += kWave;
+      }
+    }
+  }
+  if (lane == 0 && cur_t >= 0 && cand_acc) atomicAdd(&L.tcnt[cur_t * 4 + 0], (uint32_t)cand_acc);
+  wave_sync();
+  while (head < tail) {
+    const bool valid = lane < tail - head;
+    nhit = narrow_chunk(L, valid, valid ? ring[(head + lane) & (kRing - 1)] : 0u, nhit, lane, codes, sat, cap);
+    head += min(kWave, tail - head);
+  }
+  return nhit;
+}
+
+// Greedy first fit over the canonical list by one wave, 64 manifolds at a time: a lane is coloured once
+// every earlier manifold of its chunk that shares a dynamic body is coloured.  Lanes coloured in one
+// round share no body, and each sees exactly the colours of all its earlier neighbours, so the result
+// equals the sequential greedy colouring.  Colours go to cpos, their counts to colcnt.
+__device__ __forceinline__ void colour_chunks(const Lds& L, int nb, int nman, int lane) {
+  const int NB = L.nbp;
+  // per-body lane masks of the current chunk (the sorted-manifold words are free until the manifolds
+  // are written): lanes that touch body i, low and high 32 lanes
+  uint32_t* const lmlo = L.lmlo;
+  uint32_t* const lmhi = L.lmhi;
+  for (int i = lane; i < nb; i += kWave) { L.hm[i] = 0.f; L.hm[NB + i] = 0.f; lmlo[i] = 0u; lmhi[i] = 0u; }
+  wave_sync();
+  uint32_t* mask = (uint32_t*)L.hm;   // [word * nbp + body]
+  // (the next chunk's codes are loaded while this one is coloured)
+  uint32_t code_next = lane < nman ? L.cab[lane] : 0u;
+  for (int c0 = 0; c0 < nman; c0 += kWave) {
+    const int p = c0 + lane;
+    const bool valid = p < nman;
+    const uint32_t code = code_next;
+    code_next = p + kWave < nman ? L.cab[p + kWave] : 0u;
+    const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
+    const bool di = valid && (L.flag[i] & kDynamic);
+    const bool dj = valid && j != (int)kGround && (L.flag[j] & kDynamic);
+    // earlier lanes of the chunk that share a dynamic body with this one
+    uint32_t* const lmw = lane < 32 ? lmlo : lmhi;
+    const uint32_t lbit = 1u << (lane & 31);
+    if (di) atomicOr(&lmw[i], lbit);
+    if (dj) atomicOr(&lmw[j], lbit);
+    wave_sync();
+    uint64_t dep = 0ull;
+    if (di) dep |= ((uint64_t)lmhi[i] << 32) | lmlo[i];
+    if (dj) dep |= ((uint64_t)lmhi[j] << 32) | lmlo[j];
+    dep &= lane_lt_mask(lane);
+    wave_sync();
+    if (di) { lmlo[i] = 0u; lmhi[i] = 0u; }
+    if (dj) { lmlo[j] = 0u; lmhi[j] = 0u; }
+    bool done = !valid;
+    int col = -1;
+    while (true) {
+      const uint64_t donem = __ballot(done);
+      if (donem == ~0ull) break;
+      if (!done && (dep & ~donem) == 0ull) {
+        uint64_t u = 0ull;
+        if (di) u |= (uint64_t)mask[i] | ((uint64_t)mask[NB + i] << 32);
+        if (dj) u |= (uint64_t)mask[j] | ((uint64_t)mask[NB + j] << 32);
+        if (u != ~0ull) {
+          col = __ffsll((unsigned long long)~u) - 1;
+          const uint64_t bit = 1ull << col;
+          if (di) { mask[i] |= (uint32_t)bit; mask[NB + i] |= (uint32_t)(bit >> 32); }
+          if (dj) { mask[j] |= (uint32_t)bit; mask[NB + j] |= (uint32_t)(bit >> 32); }
+        }
+        done = true;
+      }
+      wave_sync();
+    }
+    if (valid) {
+      L.cpos[p] = col;
+      if (col >= 0) atomicAdd(&L.colcnt[col], 1);
+      else atomicOr((uint32_t*)&L.scal[3], kErrCol);
+    }
+  }
+  wave_sync();
+}
+
+// relaxed accesses to LDS words that other waves of the workgroup poll
+__device__ __forceinline__ uint32_t poll(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void post(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// keeps a wave's LDS accesses in program order (the LDS performs one wave's accesses in order)
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// The same colouring by every wave of a workgroup (bodies' words in LDS).  A manifold's turn on each of
+// its dynamic bodies is the number of earlier manifolds that touch it: those with the body second, all
+// before those with it first, and among the latter its place in the body's run.  A wave takes 64
+// manifolds of the canonical list at a time; a lane is coloured when both bodies' counters have reached
+// its turns, then advances them.  The first uncoloured manifold is always some wave's current one and
+// ready, so every wait ends; the rounds are bounded all the same.  One wave walking the list chunk by
+// chunk took 29 % of a 4,096-stone wall's step, about fifty rounds to a chunk; here the chains of
+// different courses run side by side.  list: `cap` words per body.  Returns false, the same on every
+// thread, when a body is second in more than `cap` manifolds (colour_chunks then does it).
+__device__ __forceinline__ bool colour_waves(const Lds& L, int nb, int nman, int tid, int nthr, uint32_t* list, int cap) {
+  const int NB = L.nbp, lane = tid & (kWave - 1), wave = tid / kWave;
+  uint32_t* const lo = (uint32_t*)L.hm;
+  uint32_t* const hi = lo + NB;
+  uint32_t* const turn = lo + 2 * NB;
+  uint32_t* const nsecond = L.lmlo;     // manifolds with body x second
+  uint32_t* const first = L.lmhi;       // first canonical manifold with body x first
+  for (int i = tid; i < nb; i += nthr) { lo[i] = 0u; hi[i] = 0u; turn[i] = 0u; nsecond[i] = 0u; }
+  if (tid == 0) L.scal[7] = 0;
+  __syncthreads();
+  for (int p = tid; p < nman; p += nthr) {
+    const uint32_t code = L.cab[p];
+    const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
+    if (p == 0 || (int)(L.cab[p - 1] >> 16) != i) first[i] = (uint32_t)p;
+    if (j != (int)kGround && (L.flag[j] & kDynamic)) {
+      const int k = (int)atomicAdd(&nsecond[j], 1u);
+      if (k < cap) list[j * cap + k] = (uint32_t)p;
+      else atomicOr((uint32_t*)&L.scal[7], 1u);
+    }
+  }
+  __syncthreads();
+  if (L.scal[7]) return false;
+  const int most = 64 * nman + 4096;    // rounds: far beyond what the longest chain takes
+  for (int c0 = wave * kWave; c0 < nman; c0 += nthr) {
+    const int p = c0 + lane;
+    const bool valid = p < nman;
+    const uint32_t code = valid ? L.cab[p] : 0u;
+    const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
+    const bool di = valid && (L.flag[i] & kDynamic);
+    const bool dj = valid && j != (int)kGround && (L.flag[j] & kDynamic);
+    const uint32_t ti = di ? nsecond[i] + ((uint32_t)p - first[i]) : 0u;
+    uint32_t tj = 0u;
+    if (dj)
+      for (int k = 0; k < (int)nsecond[j]; ++k) tj += list[j * cap + k] < (uint32_t)p ? 1u : 0u;
+    const int ia = di ? i : 0, jb = dj ? j : 0;   // (words that exist; unused where the body is static)
+    bool done = !valid;
+    int col = -1;
+    for (int round = 0; round < most; ++round) {
+      if (__all(done)) break;
+      const uint32_t ci = poll(turn + ia), cj = poll(turn + jb);
+      lds_order();                       // the masks are read after the turns, and written before them
+      const uint32_t ui0 = poll(lo + ia), ui1 = poll(hi + ia), uj0 = poll(lo + jb), uj1 = poll(hi + jb);
+      if (!done && (!di || ci == ti) && (!dj || cj == tj)) {
+        const uint64_t mi = di ? (uint64_t)ui0 | ((uint64_t)ui1 << 32) : 0ull;
+        const uint64_t mj = dj ? (uint64_t)uj0 | ((uint64_t)uj1 << 32) : 0ull;
+        const uint64_t u = mi | mj;
+        if (u != ~0ull) {
+          col = __ffsll((unsigned long long)~u) - 1;
+          const uint64_t bit = 1ull << col;
+          if (di) { post(lo + i, (uint32_t)(mi | bit)); post(hi + i, (uint32_t)((mi | bit) >> 32)); }
+          if (dj) { post(lo + j, (uint32_t)(mj | bit)); post(hi + j, (uint32_t)((mj | bit) >> 32)); }
+        }
+        lds_order();
+        if (di) post(turn + i, ti + 1u);
+        if (dj) post(turn + j, tj + 1u);
+        done = true;
+      }
+      lds_order();
+    }
+    if (valid) {
+      L.cpos[p] = col;
+      if (col >= 0) atomicAdd(&L.colcnt[col], 1);
+      else atomicOr((uint32_t*)&L.scal[3], kErrCol);
+    }
+    if (!__all(done) && lane == 0) atomicOr((uint32_t*)&L.scal[7], 1u);
+  }
+  __syncthreads();
+  return L.scal[7] == 0;
+}
+
+// Colour offsets from the counts in colcnt (one wave: a prefix sum over the 64 colours); colcnt becomes
+// each colour's next position, scal[2] the number of colours.
+__device__ __forceinline__ void colour_offsets(const Lds& L, int lane) {
+  const int cnt = L.colcnt[lane];
+  int incl = cnt;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int t = __shfl_up(incl, d);
+    if (lane >= d) incl += t;
+  }
+  L.coloff[lane + 1] = incl;
+  L.colcnt[lane] = incl - cnt;       // running position of each colour
+  if (lane == 0) L.coloff[0] = 0;
+  const uint64_t used = __ballot(cnt > 0);
+  if (lane == 0) L.scal[2] = used ? 64 - __clzll((long long)used) : 0;
+}
+
+// Colour-sorted positions of canonical manifolds [p0, p1) by one wave, canonical order inside each
+// colour; at[c] is colour c's next position.
+__device__ __forceinline__ void colour_positions(const Lds& L, int p0, int p1, int32_t* at, int lane) {
+  int col_next = p0 + lane < p1 ? L.cpos[p0 + lane] : -1;
+  for (int c0 = p0; c0 < p1; c0 += kWave) {
+    const int p = c0 + lane;
+    const int col = col_next;
+    col_next = p + kWave < p1 ? L.cpos[p + kWave] : -1;
+    int pos = -1;
+    uint64_t pending = __ballot(col >= 0);
+    while (pending) {
+      const int c = __builtin_amdgcn_readlane(col, __ffsll((unsigned long long)pending) - 1);
+      const uint64_t m = __ballot(col == c);
+      const int base = at[c];
+      if (col == c) pos = base + __popcll(m & lane_lt_mask(lane));
+      wave_sync();
+      if (lane == 0) at[c] = base + __popcll(m);
+      wave_sync();
+      pending &= ~m;
+    }
+    if (p < p1) L.cpos[p] = pos;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2252,10 +2564,14 @@ __device__ __forceinline__ int narrow_chunk(const Lds& L, int head, int count, i
 // variant does not carry the network's registers.
 // kGlobal: the pack's layout lives in its region of device memory instead of LDS.  The two are
 // separate instantiations so that the LDS variant's accesses compile to LDS instructions.
-// A device-memory variant runs several waves: the first runs every phase, and the others join
-// it where an island's work is wide (the broadphase walk, the manifolds, the sweeps, the residual
-// terms).  The plain variant runs kIslandWaves waves; the one with the network's registers (one
-// wave per SIMD) runs four, one per SIMD of the compute unit.
+// kLat (small batches): one tower per workgroup of several waves, on chip.
+// Every wave of a workgroup walks the same steps and passes the same barriers; a pack in LDS is one
+// wave, and its barriers are wave barriers.  An island's or a small batch's waves share every phase
+// that is not a scan: the broadphase and narrowphase (each wave's colliding pairs are one run of the
+// canonical list), the colouring (colour_waves), the manifolds, the network's chunks, the sweeps
+// (register-resident lane pairs for a small batch, pgs_sweeps_lat), the outputs and the integration.
+// The plain variant runs kIslandWaves waves; the one with the network's registers (one wave per SIMD)
+// runs four, one per SIMD of the compute unit.
 template <bool kLearned, bool kGlobal, bool kLat = false>
 constexpr int step_threads() {
   return kGlobal ? (kLearned ? kLearnedIslandWaves : kIslandWaves) * kWave : (kLat ? kLatencyWaves * kWave : kWave);
@@ -2269,66 +2585,21 @@ constexpr int step_threads() {
 // either compiles to flat instructions, which are as slow as device memory even on LDS).
 // kExt: the solver variants (disc friction, restitution targets, reference-face clipping) and the
 // episode criteria are compiled in; the default plain kernel carries none of their registers.
-// kLat (small batches): one tower per workgroup of kLatencyWaves waves; the first wave steps it as
-// a pack, the others join it in building the manifolds, in the sweeps (register-resident lane
-// pairs, pgs_sweeps_lat) and in the residual terms.
 template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false>
 __global__ void __launch_bounds__((step_threads<kLearned, kGlobal, kLat>()))
 __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
-  constexpr int kThreads = step_threads<kLearned, kGlobal, kLat>();
+  constexpr bool kMulti = kGlobal || kLat;   // several waves
   extern __shared__ __align__(16) float smem[];
   float* const dev = a.gmem + a.pack_goff[a.pack_first + blockIdx.x];
   const Lds L = carve(kGlobal ? dev + kManPackWords * a.pc : smem, dev, smem, kGlobal, kGlobal && kHot, a);
   const bool keep_prev = lds_mode(a) >= 1;   // previous-step store kept (warm start or records)
-  if constexpr (kThreads > kWave) {
-    if (threadIdx.x >= kWave) {
-      // helper waves: per substep they join the first wave in the broadphase walk (islands in
-      // device memory), in building the manifolds, in the sweeps and in the residual terms, each
-      // between a barrier where it enters and one where it leaves (the same barriers, in the
-      // same order, as the first wave's) (with the learned warm start they share the network's
-      // chunks too; the sweeps after it are mlp_iters, and its own residual and fallback stay
-      // with the first wave)
-      const int pkh = a.pack_first + blockIdx.x;
-      const int nbh = a.pack_body0[pkh + 1] - a.pack_body0[pkh];
-      const bool learned_h = kLearned && a.warm_start == 2;
-      const int slot0h = a.pack_slot0[pkh];
-      const float gdt_h = sqrtf(a.g[0] * a.g[0] + a.g[1] * a.g[1] + a.g[2] * a.g[2]) * a.dt;
-      const SolveOpts opts_h = {a.restitution, kExt && a.friction_cone != 0, kExt && a.restitution_bias != 0};
-      for (int s = 0; s < a.n_steps; ++s)
-        for (int sub = 0; sub < a.n_sub; ++sub) {
-          if constexpr (kGlobal) {
-            __syncthreads();
-            island_walk_rounds(L, a.margin, nbh, threadIdx.x / kWave, kThreads / kWave, threadIdx.x % kWave);
-            __syncthreads();
-          }
-          __syncthreads();
-          build_manifolds<kExt>(L, a, threadIdx.x, kThreads, L.scal[5], keep_prev);
-          __syncthreads();
-          if constexpr (kLearned) {
-            const bool rec_h = a.feat_out != nullptr && s == a.n_steps - 1 && sub == a.n_sub - 1;
-            if (learned_h || rec_h) {
-              const int wv = threadIdx.x / kWave;
-              __syncthreads();
-              learned_chunks(L, a, L.coloff[L.scal[2]], slot0h, gdt_h, learned_h, rec_h, wv, kThreads / kWave,
-                             threadIdx.x % kWave, L.xs ? L.xs + wv * kStageWords : nullptr);
-              __syncthreads();
-            }
-          }
-          __syncthreads();
-          if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, a.iters, L.scal[2], threadIdx.x, nbh, opts_h);
-          else pgs_sweeps(L, learned_h ? a.mlp_iters : a.iters, L.scal[2], threadIdx.x, kThreads, opts_h);
-          __syncthreads();
-          if (!learned_h && s == a.n_steps - 1 && sub == a.n_sub - 1) {
-            __syncthreads();
-            residual_parts(L, L.scal[5], threadIdx.x, kThreads, reinterpret_cast<float*>(L.cab),
-                           reinterpret_cast<float*>(L.cpos), nullptr, opts_h);
-            __syncthreads();
-          }
-        }
-      return;
-    }
-  }
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x;
+  const int nthr = kMulti ? (int)blockDim.x : kWave;
+  const int lane = kMulti ? tid & (kWave - 1) : tid, wave = kMulti ? tid / kWave : 0, nw = kMulti ? nthr / kWave : 1;
+  auto sync = [] {
+    if constexpr (kMulti) __syncthreads();
+    else wave_sync();
+  };
   const int pk = a.pack_first + blockIdx.x;
   const int gb0 = a.pack_body0[pk], nb = a.pack_body0[pk + 1] - gb0;
   const int gt0 = a.pack_tower0[pk], nt = a.pack_tower0[pk + 1] - gt0;
@@ -2337,10 +2608,10 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
   const int NB = L.nbp, PC = L.pc, CAP = a.cap;
   PhaseTimer timer;
   timer.last = (unsigned long long)clock64();
-  if (lane < kPhases) L.cyc[lane] = 0ull;
+  if (tid < kPhases) L.cyc[tid] = 0ull;
 
   // ---- load the pack ----
-  for (int i = lane; i < nb; i += kWave) {
+  for (int i = tid; i < nb; i += nthr) {
     const int g = gb0 + i;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -2362,7 +2633,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       for (int k = 0; k < 3; ++k) { L.v[k * NB + i] = 0.f; L.w[k * NB + i] = 0.f; }
     }
   }
-  for (int t = lane; t < nt; t += kWave) {
+  for (int t = tid; t < nt; t += nthr) {
     L.tb0[t] = a.tower_body0[gt0 + t] - gb0;
     L.tb1[t] = a.tower_body0[gt0 + t + 1] - gb0;
     L.mu[t] = a.tower_mu[gt0 + t];
@@ -2378,7 +2649,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     L.tres[2 * t] = 0.f;
     L.tres[2 * t + 1] = 0.f;
   }
-  for (int r = lane; r < np; r += kWave) {
+  for (int r = tid; r < np; r += nthr) {
     const int g = gp0 + r;
     L.pb[r] = a.push_body[g] - gb0;
     L.ps[r] = a.push_start[g];
@@ -2387,19 +2658,18 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     for (int k = 0; k < 3; ++k) { L.pf[3 * r + k] = a.push_force[3 * g + k]; L.px0[3 * r + k] = a.push_x0[3 * g + k]; }
     L.pwd[r] = a.push_withdraw[g];
   }
-  if (lane == 0) {
-    L.scal[3] = 0;                                   // error bits
-    // an on-chip pack holds at most kWindows x 64 bodies (the host sizes them so)
-    if (!kGlobal && nb > kWindows * kWave) L.scal[3] = kErrCand;
+  if (tid == 0) {
+    // error bits (an on-chip pack holds at most kWindows x 64 bodies, the host sizes them so)
+    L.scal[3] = !kGlobal && nb > kWindows * kWave ? kErrCand : 0;
     L.scal[4] = keep_prev ? a.prev_count[pk] : 0;    // previous-step manifolds
   }
   if constexpr (kLearned) {
     if (a.warm_start == 2)
-      for (int t = lane; t < nt; t += kWave) { L.tfc[2 * t] = 0u; L.tfc[2 * t + 1] = 0u; }
+      for (int t = tid; t < nt; t += nthr) { L.tfc[2 * t] = 0u; L.tfc[2 * t + 1] = 0u; }
   }
   if (keep_prev) {
     const int npv = a.prev_count[pk];
-    for (int p = lane; p < npv; p += kWave) {
+    for (int p = tid; p < npv; p += nthr) {
       const int g = slot0 + p;
       L.pkey[p] = a.prev_key[g];
       L.pslot[p] = __float_as_uint(a.prev_data[16 * g + 3]);
@@ -2409,9 +2679,9 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = a.prev_data[16 * g + 4 + k];
     }
   }
-  wave_sync();
+  sync();
   // a tower with a non-finite body (state set by the host) is frozen from the first step on
-  for (int i = lane; i < nb; i += kWave) {
+  for (int i = tid; i < nb; i += nthr) {
     if (!(L.flag[i] & kActive)) continue;
     bool finite = true;
 #pragma unroll
@@ -2424,32 +2694,32 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       atomicOr((uint32_t*)&L.scal[3], kErrNan);
     }
   }
-  wave_sync();
-  timer.mark(L, lane, 0);
+  sync();
+  timer.mark(L, tid, 0);
 
   const float dt = a.dt, e = a.restitution;
   const SolveOpts opts = {e, kExt && a.friction_cone != 0, kExt && a.restitution_bias != 0};
   for (int s = 0; s < a.n_steps; ++s) {
     const int64_t step = a.step0 + s;
-    for (int r = lane; r < np; r += kWave)
+    for (int r = tid; r < np; r += nthr)
       if ((int64_t)L.ps[r] == step) {
         const int b = L.pb[r];
 #pragma unroll
         for (int k = 0; k < 3; ++k) L.px0[3 * r + k] = L.x[k * NB + b];
       }
-    wave_sync();
+    sync();
     for (int sub = 0; sub < a.n_sub; ++sub) {
       const bool last = (s == a.n_steps - 1) && (sub == a.n_sub - 1);
       // ---- the bodies of a frozen tower (non-finite state, found at the launch's start or by
       // the integration) or of an episode at rest are held: they neither move nor collide and keep
       // their state ----
-      for (int i = lane; i < nb; i += kWave) {
+      for (int i = tid; i < nb; i += nthr) {
         const uint32_t f = L.flag[i];
         if ((f & kActive) && (L.tfz[L.tw[i]] & 3u)) L.flag[i] = (f & ~kActive) | kHeld;
       }
-      wave_sync();
+      wave_sync();   // (a thread's next loop visits the same bodies)
       // ---- 1. external forces; 2. frames ----
-      for (int i = lane; i < nb; i += kWave) {
+      for (int i = tid; i < nb; i += nthr) {
         const uint32_t f = L.flag[i];
         const bool moving = (f & (kActive | kDynamic)) == (kActive | kDynamic);
         if (moving) {
@@ -2483,338 +2753,201 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         L.Iw[4 * NB + i] = R[0] * d[0] * R[6] + R[1] * d[1] * R[7] + R[2] * d[2] * R[8];
         L.Iw[5 * NB + i] = R[3] * d[0] * R[6] + R[4] * d[1] * R[7] + R[5] * d[2] * R[8];
       }
-      for (int c = lane; c <= kMaxColours; c += kWave) L.colcnt[c] = 0;
-      for (int t = lane; t < nt; t += kWave) {
+      for (int c = tid; c <= kMaxColours; c += nthr) L.colcnt[c] = 0;
+      for (int t = tid; t < nt; t += nthr) {
         L.tcnt[t * 4 + 3] = 0u;
         L.tc0[t] = 0;
         L.tc1[t] = 0;
         L.tpts[t] = 0;
       }
-      wave_sync();
-      timer.mark(L, lane, 1);
+      sync();
+      timer.mark(L, tid, 1);
 
       // ---- 3 + 4. broadphase in canonical order, narrowphase on every 64 candidates ----
-      // Lane l holds body 64 w + l of window w in registers (position, AABB, flags, tower);
-      // body i is broadcast from its window with readlane, so the pair loop touches LDS only
-      // to append candidates to the ring.
-      int head = 0, tail = 0, nman = 0;
-      if constexpr (kGlobal) {
-        // islands in device memory (one tower each).  Bounding boxes of 64-body windows filter
-        // the pair tests; each lane then walks its own body's candidates j > i in ascending
-        // order, the ground last, into that body's own slots.  A scan of the counts gives each
-        // body its place in the canonical list, the runs are copied there, and the SAT runs on
-        // that list 64 at a time, so the candidates keep their canonical order.
-        const int nwin = (nb + kWave - 1) / kWave;
-        for (int w = lane; w < nwin; w += kWave) {
-          float lo[3] = {3.0e38f, 3.0e38f, 3.0e38f}, hi[3] = {-3.0e38f, -3.0e38f, -3.0e38f};
-          for (int j = w * kWave; j < min(nb, (w + 1) * kWave); ++j) {
-            if (!(L.flag[j] & kActive)) continue;
+      int nman;
+      const float* sat = L.msat;   // normals and depths of the colliding pairs
+      if constexpr (kMulti) {
+        int32_t* const hits = L.seg;
+        int32_t* const pre = hits + (kMostWaves + 1);
+        int32_t* const start = pre + (kMostWaves + 1);
+        uint32_t* codes;   // this wave's colliding pairs
+        int mine = 0;
+        if constexpr (kGlobal) {
+          // islands in device memory (one tower each).  Bounding boxes of 64-body windows filter
+          // the pair tests; each lane then walks its own body's candidates j > i in ascending
+          // order, the ground last, into that body's own slots.  A scan of the counts gives each
+          // body its place in the canonical list, the runs are copied there, and the SAT runs on
+          // that list 64 at a time, each wave on one stretch of it.
+          const int nwin = (nb + kWave - 1) / kWave;
+          for (int w = wave; w < nwin; w += nw) {
+            const int j = w * kWave + lane;
+            const bool in = j < nb && (L.flag[j] & kActive);
+            float lo[3], hi[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-              lo[k] = fminf(lo[k], L.x[k * NB + j] - L.hm[k * NB + j]);
-              hi[k] = fmaxf(hi[k], L.x[k * NB + j] + L.hm[k * NB + j]);
+              lo[k] = in ? L.x[k * NB + j] - L.hm[k * NB + j] : 3.0e38f;
+              hi[k] = in ? L.x[k * NB + j] + L.hm[k * NB + j] : -3.0e38f;
+            }
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                lo[k] = fminf(lo[k], __shfl_xor(lo[k], d));
+                hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], d));
+              }
+            if (lane == 0) {
+#pragma unroll
+              for (int k = 0; k < 3; ++k) { L.wbox[6 * w + k] = lo[k]; L.wbox[6 * w + 3 + k] = hi[k]; }
             }
           }
+          sync();
+          // one walk: each body's candidates into its own kCandPerBody slots, counts into the (still
+          // unused) colouring lane masks; an exclusive scan of the counts places each body's run in
+          // the canonical list, and the runs are copied there.  A body with more candidates than
+          // its slots keeps the first kCandPerBody (flagged).
+          uint32_t* const cnt = L.lmlo;
+          uint32_t* const off = L.lmhi;
+          island_walk_rounds(L, a.margin, nb, wave, nw, lane);
+          sync();   // every body's candidates are in its slots
+          if (wave == 0) {
+            uint32_t run = 0;
+            for (int i0 = 0; i0 < nb; i0 += kWave) {
+              const int i = i0 + lane;
+              const uint32_t c = i < nb ? cnt[i] : 0u;
+              uint32_t incl = c;
 #pragma unroll
-          for (int k = 0; k < 3; ++k) { L.wbox[6 * w + k] = lo[k]; L.wbox[6 * w + 3 + k] = hi[k]; }
-        }
-        wave_sync();
-        // one walk: each body's candidates into its own kCandPerBody slots, counts into the (still
-        // unused) colouring lane masks; an exclusive scan of the counts places each body's run in
-        // the canonical list, and the runs are copied there.  A body with more candidates than
-        // its slots keeps the first kCandPerBody (flagged).  The helper waves share the walk.
-        uint32_t* const cnt = L.lmlo;
-        if constexpr (kThreads > kWave) {
-          __syncthreads();   // window boxes, frames and flags are in place; the helpers enter
-          island_walk_rounds(L, a.margin, nb, 0, kThreads / kWave, lane);
-          __syncthreads();   // every body's candidates are in its slots
-        } else {
-          island_walk_rounds(L, a.margin, nb, 0, 1, lane);
-          wave_sync();
-        }
-        uint32_t run = 0;
-        for (int i0 = 0; i0 < nb; i0 += kWave) {
-          const int i = i0 + lane;
-          const uint32_t c = i < nb ? cnt[i] : 0u;
-          uint32_t incl = c;
-#pragma unroll
-          for (int d = 1; d < kWave; d <<= 1) {
-            const uint32_t t = __shfl_up(incl, d);
-            if (lane >= d) incl += t;
+              for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t t = __shfl_up(incl, d);
+                if (lane >= d) incl += t;
+              }
+              if (i < nb) off[i] = run + incl - c;
+              run += __shfl(incl, kWave - 1);
+            }
+            if (lane == 0) {
+              L.scal[6] = (int)run;
+              L.tcnt[0] += run;   // an island is one tower (kept candidates)
+            }
           }
-          if (i < nb) {
-            const uint32_t off = run + incl - c;
+          sync();
+          for (int i = tid; i < nb; i += nthr) {
+            const uint32_t c = cnt[i], o = off[i];
             uint32_t v[kCandPerBody];
 #pragma unroll
             for (int k = 0; k < kCandPerBody; ++k)
               if (k < (int)c) v[k] = L.cslot[i * kCandPerBody + k];
 #pragma unroll
             for (int k = 0; k < kCandPerBody; ++k)
-              if (k < (int)c) L.cand[off + k] = v[k];
+              if (k < (int)c) L.cand[o + k] = v[k];
           }
-          run += __shfl(incl, kWave - 1);
-        }
-        const int total = (int)run;
-        wave_sync();
-        for (int c0 = 0; c0 < total; c0 += kWave) {
-          const int n = min(kWave, total - c0);
-          // narrow_chunk reads the ring: stage the next 64 candidates there
-          if (lane < n) L.ring[(head + lane) & (kRing - 1)] = L.cand[c0 + lane];
-          wave_sync();
-          nman = narrow_chunk(L, head, n, nman, lane);
-          head += n;
-          wave_sync();
-        }
-        tail = head;
-        if (lane == 0) L.tcnt[0] += (uint32_t)run;   // an island is one tower (kept candidates)
-      } else {
-        float wx[kWindows][3], wh[kWindows][3];
-        uint32_t wf[kWindows];
-        int wt[kWindows];
-#pragma unroll
-        for (int w = 0; w < kWindows; ++w) {
-          const int j = w * kWave + lane;
-          const bool in = j < nb;
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            wx[w][k] = in ? L.x[k * NB + j] : 0.f;
-            wh[w][k] = in ? L.hm[k * NB + j] : 0.f;
-          }
-          wf[w] = in ? L.flag[j] : 0u;
-          wt[w] = in ? L.tw[j] : -1;
-        }
-        const int nwin = (nb + kWave - 1) / kWave;
-        int cur_t = -1, cand_acc = 0;
-        for (int i = 0; i < nb; ++i) {
-          const int wi = i / kWave, li = i % kWave;
-          float xi[3], hi[3];
-          uint32_t fi = 0u;
-          int ti = 0;
-#pragma unroll
-          for (int w = 0; w < kWindows; ++w)
-            if (w == wi) {
-#pragma unroll
-              for (int k = 0; k < 3; ++k) {
-                xi[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wx[w][k]), li));
-                hi[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wh[w][k]), li));
-              }
-              fi = __builtin_amdgcn_readlane(wf[w], li);
-              ti = __builtin_amdgcn_readlane(wt[w], li);
-            }
-          if (!(fi & kActive)) continue;
-          if (ti != cur_t) {
-            if (lane == 0 && cur_t >= 0 && cand_acc) L.tcnt[cur_t * 4 + 0] += (uint32_t)cand_acc;
-            cur_t = ti;
-            cand_acc = 0;
-          }
-          const bool dyni = (fi & kDynamic) != 0;
-#pragma unroll
-          for (int w = 0; w < kWindows; ++w) {
-            if (w < wi || w >= nwin) continue;
-            const int j = w * kWave + lane;
-            const bool hit = j > i && wt[w] == ti && (wf[w] & kActive) && (dyni || (wf[w] & kDynamic)) &&
-                             fabsf(xi[0] - wx[w][0]) <= hi[0] + wh[w][0] + a.margin &&
-                             fabsf(xi[1] - wx[w][1]) <= hi[1] + wh[w][1] + a.margin &&
-                             fabsf(xi[2] - wx[w][2]) <= hi[2] + wh[w][2] + a.margin;
-            const uint64_t bal = __ballot(hit);
-            if (hit) L.ring[(tail + __popcll(bal & lane_lt_mask(lane))) & (kRing - 1)] = ((uint32_t)i << 16) | (uint32_t)j;
-            const int cnt = __popcll(bal);
-            cand_acc += cnt;
-            tail += cnt;
-            if (tail - head >= kWave) {
-              wave_sync();
-              nman = narrow_chunk(L, head, kWave, nman, lane);
-              head += kWave;
-            }
-          }
-          // the ground comes last in body i's canonical row
-          if (dyni && (xi[2] - hi[2] <= a.margin)) {
-            if (lane == 0) L.ring[tail & (kRing - 1)] = ((uint32_t)i << 16) | kGround;
-            cand_acc += 1;
-            tail += 1;
-            if (tail - head >= kWave) {
-              wave_sync();
-              nman = narrow_chunk(L, head, kWave, nman, lane);
-              head += kWave;
-            }
-          }
-        }
-        if (lane == 0 && cur_t >= 0 && cand_acc) L.tcnt[cur_t * 4 + 0] += (uint32_t)cand_acc;
-      }
-      wave_sync();
-      while (head < tail) {
-        const int cnt = min(kWave, tail - head);
-        nman = narrow_chunk(L, head, cnt, nman, lane);
-        head += cnt;
-      }
-      if (nman > PC) {
-        if (lane == 0) L.scal[3] |= kErrMan;
-        nman = PC;
-      }
-      wave_sync();
-      timer.mark(L, lane, 2);
-
-      // ---- 5. tower ranges of the canonical list; greedy first-fit colouring ----
-      if (nt == 1) {
-        if (lane == 0 && nman > 0) { L.tc0[0] = 0; L.tc1[0] = nman; }
-      } else {
-        for (int p = lane; p < nman; p += kWave) {
-          const int t = L.tw[L.cab[p] >> 16];
-          if (p == 0 || L.tw[L.cab[p - 1] >> 16] != t) L.tc0[t] = p;
-          if (p == nman - 1 || L.tw[L.cab[p + 1] >> 16] != t) L.tc1[t] = p + 1;
-        }
-      }
-      // per-body lane masks of the current chunk (the sorted-manifold words are free until the
-      // manifolds are written): lanes that touch body i, low and high 32 lanes
-      uint32_t* const lmlo = L.lmlo;
-      uint32_t* const lmhi = L.lmhi;
-      for (int i = lane; i < nb; i += kWave) { L.hm[i] = 0.f; L.hm[NB + i] = 0.f; lmlo[i] = 0u; lmhi[i] = 0u; }
-      wave_sync();
-      uint32_t* mask = (uint32_t*)L.hm;   // [word * nbp + body]
-      // Greedy first fit in canonical order, 64 manifolds at a time: a lane is coloured once
-      // every earlier manifold of its chunk that shares a dynamic body is coloured.  Lanes
-      // coloured in one round share no body, and each sees exactly the colours of all its
-      // earlier neighbours, so the result equals the sequential greedy colouring.
-      // (the next chunk's codes are loaded while this one is coloured)
-      uint32_t code_next = lane < nman ? L.cab[lane] : 0u;
-      for (int c0 = 0; c0 < nman; c0 += kWave) {
-        const int p = c0 + lane;
-        const bool valid = p < nman;
-        const uint32_t code = code_next;
-        code_next = p + kWave < nman ? L.cab[p + kWave] : 0u;
-        const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
-        const bool di = valid && (L.flag[i] & kDynamic);
-        const bool dj = valid && j != (int)kGround && (L.flag[j] & kDynamic);
-        // earlier lanes of the chunk that share a dynamic body with this one
-        uint32_t* const lmw = lane < 32 ? lmlo : lmhi;
-        const uint32_t lbit = 1u << (lane & 31);
-        if (di) atomicOr(&lmw[i], lbit);
-        if (dj) atomicOr(&lmw[j], lbit);
-        wave_sync();
-        uint64_t dep = 0ull;
-        if (di) dep |= ((uint64_t)lmhi[i] << 32) | lmlo[i];
-        if (dj) dep |= ((uint64_t)lmhi[j] << 32) | lmlo[j];
-        dep &= lane_lt_mask(lane);
-        wave_sync();
-        if (di) { lmlo[i] = 0u; lmhi[i] = 0u; }
-        if (dj) { lmlo[j] = 0u; lmhi[j] = 0u; }
-        bool done = !valid;
-        int col = -1;
-        if constexpr (kGlobal) {
-          // An island's chunks take many rounds (its canonical order runs along chains of
-          // touching stones), so the rounds stay in registers: the colours a lane may not take
-          // are those its bodies got in earlier chunks (read once) and those of the earlier lanes
-          // of this chunk it depends on, folded in (by broadcast) in the round after each is
-          // coloured; the chunk's colours go into the body masks at its end.
-          uint64_t u = 0ull;
-          if (di) u |= (uint64_t)mask[i] | ((uint64_t)mask[NB + i] << 32);
-          if (dj) u |= (uint64_t)mask[j] | ((uint64_t)mask[NB + j] << 32);
-          uint64_t fresh = 0ull;   // lanes coloured in the previous round (wave-uniform)
-          while (true) {
-            for (uint64_t f = fresh; f != 0ull; f &= f - 1ull) {
-              const int k = __ffsll((unsigned long long)f) - 1;
-              const int ck = __builtin_amdgcn_readlane(col, k);
-              if (ck >= 0 && ((dep >> k) & 1ull)) u |= 1ull << ck;
-            }
-            const uint64_t donem = __ballot(done);
-            if (donem == ~0ull) break;
-            const bool ready = !done && (dep & ~donem) == 0ull;
-            if (ready) {
-              if (u != ~0ull) col = __ffsll((unsigned long long)~u) - 1;
-              done = true;
-            }
-            fresh = __ballot(ready);
-          }
-          // lanes that share a body set different bits
-          if (valid && col >= 0) {
-            const uint64_t bit = 1ull << col;
-            if (di) { atomicOr(&mask[i], (uint32_t)bit); atomicOr(&mask[NB + i], (uint32_t)(bit >> 32)); }
-            if (dj) { atomicOr(&mask[j], (uint32_t)bit); atomicOr(&mask[NB + j], (uint32_t)(bit >> 32)); }
-          }
-          wave_sync();   // the masks are complete before the next chunk reads them
-        } else {
-          // a pack's chunks take few rounds, each colouring many lanes: the masks stay in LDS
-          while (true) {
-            const uint64_t donem = __ballot(done);
-            if (donem == ~0ull) break;
-            if (!done && (dep & ~donem) == 0ull) {
-              uint64_t u = 0ull;
-              if (di) u |= (uint64_t)mask[i] | ((uint64_t)mask[NB + i] << 32);
-              if (dj) u |= (uint64_t)mask[j] | ((uint64_t)mask[NB + j] << 32);
-              if (u != ~0ull) {
-                col = __ffsll((unsigned long long)~u) - 1;
-                const uint64_t bit = 1ull << col;
-                if (di) { mask[i] |= (uint32_t)bit; mask[NB + i] |= (uint32_t)(bit >> 32); }
-                if (dj) { mask[j] |= (uint32_t)bit; mask[NB + j] |= (uint32_t)(bit >> 32); }
-              }
-              done = true;
-            }
+          sync();
+          // a wave's stretch: whole chunks of 64; its colliding pairs replace its candidates in place
+          const int total = L.scal[6];
+          const int per = ((total + kWave - 1) / kWave + nw - 1) / nw * kWave;
+          const int c0 = min(total, wave * per), c1 = min(total, c0 + per);
+          codes = L.cand + c0;
+          sat = L.csat;
+          for (int c = c0; c < c1; c += kWave) {
+            const bool valid = c + lane < c1;
+            mine = narrow_chunk(L, valid, valid ? L.cand[c + lane] : 0u, mine, lane, codes, L.csat + 4 * (size_t)c0, c1 - c0);
             wave_sync();
           }
+          if (lane == 0) start[wave] = c0;
+        } else {
+          // a small batch's tower: each wave takes a stretch of the bodies i, and its own list
+          float* const wsat = dev + (size_t)kManPackWords * PC;
+          codes = reinterpret_cast<uint32_t*>(wsat + (size_t)4 * nw * PC) + (size_t)wave * PC;
+          const int per = (nb + nw - 1) / nw;
+          mine = on_chip_pairs(L, a.margin, nb, min(nb, wave * per), min(nb, (wave + 1) * per), lane, L.ring + wave * kRing,
+                               codes, wsat + (size_t)4 * wave * PC, PC);
+          sat = wsat;
+          if (lane == 0) start[wave] = wave * PC;
         }
-        if (valid) {
-          L.cpos[p] = col;
-          if (col >= 0) atomicAdd(&L.colcnt[col], 1);
-          else atomicOr((uint32_t*)&L.scal[3], kErrCol);
+        if (lane == 0) hits[wave] = mine;
+        sync();
+        // the waves' runs, in wave order, are the canonical list
+        int before = 0;
+        nman = 0;
+        for (int w = 0; w < nw; ++w) {
+          if (w == wave) before = nman;
+          nman += hits[w];
         }
+        if (lane == 0) pre[wave] = before;
+        for (int k = lane; k < mine && before + k < PC; k += kWave) L.cab[before + k] = codes[k];
+      } else {
+        nman = on_chip_pairs(L, a.margin, nb, 0, nb, lane, L.ring, L.cab, L.msat, PC);
       }
-      wave_sync();
-      // colour offsets (wave prefix sum over the 64 colour counts)
-      {
-        const int cnt = L.colcnt[lane];
-        int incl = cnt;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-          const int t = __shfl_up(incl, d);
-          if (lane >= d) incl += t;
-        }
-        L.coloff[lane + 1] = incl;
-        L.colcnt[lane] = incl - cnt;       // running position of each colour
-        if (lane == 0) L.coloff[0] = 0;
-        const uint64_t used = __ballot(cnt > 0);
-        if (lane == 0) L.scal[2] = used ? 64 - __clzll((long long)used) : 0;
+      if (nman > PC) {
+        if (tid == 0) atomicOr((uint32_t*)&L.scal[3], kErrMan);
+        nman = PC;
       }
-      wave_sync();
-      // colour-sorted positions, canonical order inside each colour
-      int col_next = lane < nman ? L.cpos[lane] : -1;
-      for (int c0 = 0; c0 < nman; c0 += kWave) {
-        const int p = c0 + lane;
-        const int col = col_next;
-        col_next = p + kWave < nman ? L.cpos[p + kWave] : -1;
-        int pos = -1;
-        uint64_t pending = __ballot(col >= 0);
-        while (pending) {
-          const int c = __builtin_amdgcn_readlane(col, __ffsll((unsigned long long)pending) - 1);
-          const uint64_t m = __ballot(col == c);
-          const int base = L.colcnt[c];
-          if (col == c) pos = base + __popcll(m & lane_lt_mask(lane));
-          wave_sync();
-          if (lane == 0) L.colcnt[c] = base + __popcll(m);
-          wave_sync();
-          pending &= ~m;
+      sync();
+      timer.mark(L, tid, 2);
+
+      // ---- 5. tower ranges of the canonical list; greedy first-fit colouring, colour-sorted slots ----
+      if constexpr (kMulti) {
+        if (tid == 0 && nman > 0) { L.tc0[0] = 0; L.tc1[0] = nman; }   // one tower
+        bool coloured = false;
+        if constexpr (kLat || kHot) {
+          coloured = colour_waves(L, nb, nman, tid, nthr, kLat ? reinterpret_cast<uint32_t*>(L.vw) : L.cslot,
+                                  kLat ? kLatList : kCandPerBody);
+          if (!coloured)
+            for (int c = tid; c <= kMaxColours; c += nthr) L.colcnt[c] = 0;
         }
-        if (p < nman) {
-          L.cpos[p] = pos;
+        if (!coloured) {
+          sync();
+          if (wave == 0) colour_chunks(L, nb, nman, lane);
+        }
+        // each wave ranks one stretch of the list; its colours start where the earlier waves' end
+        int32_t* const at = L.wcol + wave * kMaxColours;
+        const int per = ((nman + kWave - 1) / kWave + nw - 1) / nw * kWave;
+        const int p0 = min(nman, wave * per), p1 = min(nman, p0 + per);
+        at[lane] = 0;
+        sync();
+        for (int p = p0 + lane; p < p1; p += kWave) {
+          const int c = L.cpos[p];
+          if (c >= 0) atomicAdd(&at[c], 1);
+        }
+        sync();
+        if (wave == 0) {
+          colour_offsets(L, lane);
+          int next = L.colcnt[lane];
+          for (int w = 0; w < nw; ++w) {
+            const int c = L.wcol[w * kMaxColours + lane];
+            L.wcol[w * kMaxColours + lane] = next;
+            next += c;
+          }
+          if (lane == 0) L.tcnt[3] = (uint32_t)L.scal[2];
+        }
+        sync();
+        colour_positions(L, p0, p1, at, lane);
+      } else {
+        if (nt == 1) {
+          if (lane == 0 && nman > 0) { L.tc0[0] = 0; L.tc1[0] = nman; }
+        } else {
+          for (int p = lane; p < nman; p += kWave) {
+            const int t = L.tw[L.cab[p] >> 16];
+            if (p == 0 || L.tw[L.cab[p - 1] >> 16] != t) L.tc0[t] = p;
+            if (p == nman - 1 || L.tw[L.cab[p + 1] >> 16] != t) L.tc1[t] = p + 1;
+          }
+        }
+        colour_chunks(L, nb, nman, lane);
+        for (int p = lane; p < nman; p += kWave) {
+          const int col = L.cpos[p];
           if (col >= 0) atomicMax(&L.tcnt[(nt == 1 ? 0 : L.tw[L.cab[p] >> 16]) * 4 + 3], (uint32_t)(col + 1));
         }
+        colour_offsets(L, lane);
+        wave_sync();
+        colour_positions(L, 0, nman, L.colcnt, lane);
       }
-      wave_sync();
-      timer.mark(L, lane, 3);
+      sync();
+      timer.mark(L, tid, 3);
       const int ncol = L.scal[2];
       const int nkept = L.coloff[ncol];
 
       // ---- 6. manifolds into colour-sorted slots (+ warm start lookup) ----
-      // (an island's helper waves join in between the two barriers)
-      if constexpr (kThreads > kWave) {
-        L.scal[5] = nman;
-        __syncthreads();
-        build_manifolds<kExt>(L, a, threadIdx.x, kThreads, nman, keep_prev);
-        __syncthreads();
-      } else {
-        build_manifolds<kExt>(L, a, lane, kWave, nman, keep_prev);
-        wave_sync();
-      }
-      timer.mark(L, lane, 4);
+      build_manifolds<kExt>(L, a, sat, nw, tid, nthr, nman, keep_prev);
+      sync();
+      timer.mark(L, tid, 4);
 
       // ---- learned warm start: features, network, initial impulses; feature records ----
       bool learned = false;
@@ -2822,39 +2955,33 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         learned = a.warm_start == 2;
         const bool rec = a.feat_out != nullptr && last;
         if (learned)
-          for (int i = lane; i < nb; i += kWave)
+          for (int i = tid; i < nb; i += nthr)
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
               L.vsave[k * NB + i] = L.v[k * NB + i];
               L.vsave[(3 + k) * NB + i] = L.w[k * NB + i];
             }
         if (learned || rec) {
+          // (each wave of an island has its own staging rows)
           const float gdt = sqrtf(a.g[0] * a.g[0] + a.g[1] * a.g[1] + a.g[2] * a.g[2]) * dt;
-          if constexpr (kThreads > kWave) {
-            // an island's helper waves take chunks too, each with its own staging rows
-            __syncthreads();
-            learned_chunks(L, a, nkept, slot0, gdt, learned, rec, 0, kThreads / kWave, lane, L.xs);
-            __syncthreads();
-          } else {
-            learned_chunks(L, a, nkept, slot0, gdt, learned, rec, 0, 1, lane, L.xs);
-          }
-          wave_sync();
+          learned_chunks(L, a, nkept, slot0, gdt, learned, rec, wave, nw, lane, L.xs ? L.xs + wave * kStageWords : nullptr);
+          sync();
         }
         if (keep_prev && a.warm_start == 0) {
           // records without a warm start: the key lookup filled ml only to feed the features
           // (on every step, so the solve starts from zero whether or not this step records)
-          for (int m = lane; m < nkept; m += kWave)
+          for (int m = tid; m < nkept; m += nthr)
 #pragma unroll
             for (int k = 0; k < 12; ++k) mdev(L, m)[12 + k] = 0.f;
-          wave_sync();
+          sync();
         }
       }
 
       // ---- 7. warm-start impulses, then PGS sweeps, colour by colour ----
       if (a.warm_start == 1) {
         for (int col = 0; col < ncol; ++col) {
-          for (int m = L.coloff[col] + lane; m < L.coloff[col + 1]; m += kWave) warm_apply_manifold(L, m);
-          wave_sync();
+          for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) warm_apply_manifold(L, m);
+          sync();
         }
       }
       int sweeps = a.iters;
@@ -2862,66 +2989,74 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         if (learned) {
           const float gdt = sqrtf(a.g[0] * a.g[0] + a.g[1] * a.g[1] + a.g[2] * a.g[2]) * dt;
           for (int col = 0; col < ncol; ++col) {
-            for (int m = L.coloff[col] + lane; m < L.coloff[col + 1]; m += kWave)
+            for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr)
               learned_apply_manifold(L, m, L.mu[L.tw[L.mab[m] >> 16]], gdt, opts.cone);
-            wave_sync();
+            sync();
           }
           sweeps = a.mlp_iters;
         }
       }
-      __syncthreads();   // the helper waves (if any) enter the sweeps with this wave
-      if constexpr (kLat) pgs_sweeps_lat<kThreads>(L, sweeps, ncol, threadIdx.x, nb, opts);
-      else pgs_sweeps(L, sweeps, ncol, threadIdx.x, kThreads, opts);
-      __syncthreads();
-      timer.mark(L, lane, 5);
+      if constexpr (kLat) pgs_sweeps_lat(L, sweeps, ncol, tid, nthr, nb, opts);
+      else pgs_sweeps(L, sweeps, ncol, tid, nthr, opts);
+      sync();
+      timer.mark(L, tid, 5);
 
       // ---- learned warm start: residual, and the plain solve again for towers above tau ----
       if constexpr (kLearned) {
         if (learned) {
-          tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, nullptr, opts);
-          wave_sync();
-          int any = 0;
-          for (int t = lane; t < nt; t += kWave) {
-            const uint32_t fb = L.tres[2 * t] > a.fallback_tau ? 1u : 0u;
-            L.tfb[t] = fb;
-            any |= (int)fb;
+          residual_parts(L, nman, tid, nthr, L.rpart, L.rpart + PC, nullptr, opts);
+          sync();
+          if (wave == 0) {
+            tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, nullptr, opts, false);
+            wave_sync();
+            int any = 0;
+            for (int t = lane; t < nt; t += kWave) {
+              const uint32_t fb = L.tres[2 * t] > a.fallback_tau ? 1u : 0u;
+              L.tfb[t] = fb;
+              any |= (int)fb;
+            }
+            any = __any(any);
+            if (lane == 0) L.scal[8] = any;
           }
-          wave_sync();
-          any = __any(any);   // one wave per workgroup: a wave vote is the workgroup's
-          if (any) {
-            for (int i = lane; i < nb; i += kWave)
+          sync();
+          if (L.scal[8]) {
+            for (int i = tid; i < nb; i += nthr)
               if (L.tfb[L.tw[i]])
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                   L.v[k * NB + i] = L.vsave[k * NB + i];
                   L.w[k * NB + i] = L.vsave[(3 + k) * NB + i];
                 }
-            for (int m = lane; m < nkept; m += kWave)
+            for (int m = tid; m < nkept; m += nthr)
               if (L.tfb[L.tw[L.mab[m] >> 16]])
 #pragma unroll
                 for (int k = 0; k < 12; ++k) mdev(L, m)[12 + k] = 0.f;
-            wave_sync();
+            sync();
             for (int it = 0; it < a.iters; ++it) {
               for (int col = 0; col < ncol; ++col) {
-                for (int m = L.coloff[col] + lane; m < L.coloff[col + 1]; m += kWave) {
+                for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) {
                   const int t = L.tw[L.mab[m] >> 16];
                   if (L.tfb[t]) solve_manifold(L, m, opts);
                 }
-                wave_sync();
+                sync();
               }
             }
-            for (int t = lane; t < nt; t += kWave)
-              if (L.tfb[t]) { L.tfc[2 * t] += 1u; L.tfc[2 * t + 1] += (uint32_t)L.tpts[t]; }
-            tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, L.tfb, opts);
+            residual_parts(L, nman, tid, nthr, L.rpart, L.rpart + PC, L.tfb, opts);
+            sync();
+            if (wave == 0) {
+              for (int t = lane; t < nt; t += kWave)
+                if (L.tfb[t]) { L.tfc[2 * t] += 1u; L.tfc[2 * t + 1] += (uint32_t)L.tpts[t]; }
+              tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, L.tfb, opts, false);
+            }
           }
-          wave_sync();
-          timer.mark(L, lane, 7);
+          sync();
+          timer.mark(L, tid, 7);
         }
       }
 
       // ---- contacts of the final step; warm-start store ----
       if (last) {
-        for (int m = lane; m < nkept; m += kWave) {
+        for (int m = tid; m < nkept; m += nthr) {
           int col = 0;
           while (col + 1 < ncol && L.coloff[col + 1] <= m) ++col;
           const int a_ = (int)(L.mab[m] >> 16);
@@ -2953,13 +3088,13 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
             }
           }
         }
-        if (lane == 0) a.out_count[pk] = nkept;
+        if (tid == 0) a.out_count[pk] = nkept;
       }
       if (keep_prev) {
         // canonical-order store of this step's impulses (dropped pairs keep their key, no points)
-        for (int p = lane; p < nman; p += kWave) { L.pkey[p] = L.cab[p]; L.pslot[p] = 0u; }
-        wave_sync();
-        for (int m = lane; m < nkept; m += kWave) {
+        for (int p = tid; p < nman; p += nthr) { L.pkey[p] = L.cab[p]; L.pslot[p] = 0u; }
+        sync();
+        for (int m = tid; m < nkept; m += nthr) {
           const int p = L.mcanon[m];
           const uint32_t meta = L.mmeta[m];
           const int npts = (int)(meta & 15u);
@@ -2968,30 +3103,25 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
           for (int k = 0; k < 3; ++k) L.pnrm[k * PC + p] = mdev(L, m)[24 + k];
           for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = mdev(L, m)[12 + k];
         }
-        if (lane == 0) L.scal[4] = nman;
+        if (tid == 0) L.scal[4] = nman;
       }
-      wave_sync();
-      timer.mark(L, lane, 6);
+      sync();
+      timer.mark(L, tid, 6);
 
       // ---- 8. residual of the launch's last solve, the one the outputs report (the learned
       // variant took it before the outputs, for its fallback) ----
       if (!learned && last) {
         float* const psum = reinterpret_cast<float*>(L.cab);
         float* const pmax = reinterpret_cast<float*>(L.cpos);
-        if constexpr (kThreads > kWave) {
-          // an island's helper waves join in the pairs' terms
-          __syncthreads();
-          residual_parts(L, nman, threadIdx.x, kThreads, psum, pmax, nullptr, opts);
-          __syncthreads();
-          tower_residuals(L, nman, nt, lane, psum, pmax, nullptr, opts, false);
-        } else {
-          tower_residuals(L, nman, nt, lane, psum, pmax, nullptr, opts);
-        }
-        timer.mark(L, lane, 7);
+        residual_parts(L, nman, tid, nthr, psum, pmax, nullptr, opts);
+        sync();
+        if (wave == 0) tower_residuals(L, nman, nt, lane, psum, pmax, nullptr, opts, false);
+        sync();
+        timer.mark(L, tid, 7);
       }
 
       // ---- 9. integrate ----
-      for (int i = lane; i < nb; i += kWave) {
+      for (int i = tid; i < nb; i += nthr) {
         const uint32_t f = L.flag[i];
         if ((f & (kActive | kDynamic)) != (kActive | kDynamic)) continue;
         if (!integrate_body(L, i, a.mass[gb0 + i], dt)) {
@@ -2999,21 +3129,21 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
           atomicOr(&L.tfz[L.tw[i]], 1u);   // frozen from the next substep on
         }
       }
-      wave_sync();
-      timer.mark(L, lane, 8);
+      sync();
+      timer.mark(L, tid, 8);
       // ---- 10. Baumgarte position correction, colour by colour ----
       for (int col = 0; col < ncol; ++col) {
-        for (int m = L.coloff[col] + lane; m < L.coloff[col + 1]; m += kWave) {
+        for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) {
           const uint32_t ab = L.mab[m];
           const int j = (int)(ab & 0xffffu);
           baumgarte_pair(L, (int)(ab >> 16), j, j == (int)kGround, mdev(L, m), a.beta, a.slop);
         }
-        wave_sync();
+        sync();
       }
-      timer.mark(L, lane, 9);
+      timer.mark(L, tid, 9);
     }
     // ---- withdrawal of pushed bodies ----
-    for (int r = lane; r < np; r += kWave) {
+    for (int r = tid; r < np; r += nthr) {
       const int b = L.pb[r];
       if (!(L.pwd[r] > 0.f) || step < (int64_t)L.ps[r] || !(L.flag[b] & kActive) || (L.tfz[L.tw[b]] & 4u)) continue;
       float dx[3], f[3];
@@ -3025,17 +3155,17 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         for (int k = 0; k < 3; ++k) { L.v[k * NB + b] = 0.f; L.w[k * NB + b] = 0.f; }
       }
     }
-    wave_sync();
+    sync();
     // ---- episode criteria at the end of the step (the pack's manifold block is free scratch
     // until the next step's manifolds) ----
     if (kExt && a.ep_state) {
-      episode_update(L, a, gt0, gb0, nt, lane, step, L.md);
-      wave_sync();
+      if (wave == 0) episode_update(L, a, gt0, gb0, nt, lane, step, L.md);
+      sync();
     }
   }
 
   // ---- write the pack back (a body without mass keeps its stored velocity) ----
-  for (int i = lane; i < nb; i += kWave) {
+  for (int i = tid; i < nb; i += nthr) {
     const int g = gb0 + i;
     const bool dyn = (L.flag[i] & kDynamic) != 0;
 #pragma unroll
@@ -3051,7 +3181,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     const uint32_t f = L.flag[i];
     a.flags[g] = (f & kHeld) ? ((f & ~kHeld) | kActive) : f;
   }
-  for (int t = lane; t < nt; t += kWave) {
+  for (int t = tid; t < nt; t += nthr) {
     const int g = gt0 + t;
 #pragma unroll
     for (int k = 0; k < 3; ++k) a.tower_count[4 * g + k] += L.tcnt[4 * t + k];
@@ -3060,20 +3190,20 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     a.tower_res[2 * g + 1] = L.tres[2 * t + 1];
     a.tower_frozen[g] = L.tfz[t] & 1u;
   }
-  for (int r = lane; r < np; r += kWave) {
+  for (int r = tid; r < np; r += nthr) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) a.push_x0[3 * (gp0 + r) + k] = L.px0[3 * r + k];
   }
   if constexpr (kLearned) {
     if (a.warm_start == 2)
-      for (int t = lane; t < nt; t += kWave) {
+      for (int t = tid; t < nt; t += nthr) {
         a.tower_fallback[2 * (gt0 + t)] += L.tfc[2 * t];
         a.tower_fallback[2 * (gt0 + t) + 1] += L.tfc[2 * t + 1];
       }
   }
   if (keep_prev) {
     const int npv = L.scal[4];
-    for (int p = lane; p < npv; p += kWave) {
+    for (int p = tid; p < npv; p += nthr) {
       const int g = slot0 + p;
       a.prev_key[g] = L.pkey[p];
       a.prev_data[16 * g + 3] = __uint_as_float(L.pslot[p]);
@@ -3082,15 +3212,15 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
 #pragma unroll
       for (int k = 0; k < 12; ++k) a.prev_data[16 * g + 4 + k] = L.plam[k * PC + p];
     }
-    if (lane == 0) a.prev_count[pk] = npv;
+    if (tid == 0) a.prev_count[pk] = npv;
   }
-  if (lane == 0 && L.scal[3]) {
+  if (tid == 0 && L.scal[3]) {
     a.pack_error[pk] |= (uint32_t)L.scal[3];
     atomicOr(a.err_flag, (uint32_t)L.scal[3]);
   }
-  timer.mark(L, lane, 0);
-  wave_sync();
-  if (a.phase_cycles && lane < kPhases) atomicAdd(&a.phase_cycles[lane], L.cyc[lane]);
+  timer.mark(L, tid, 0);
+  sync();
+  if (a.phase_cycles && tid < kPhases) atomicAdd(&a.phase_cycles[tid], L.cyc[tid]);
 }
 
 #if JG_STEP_PART == 0
@@ -4020,7 +4150,7 @@ int step_launch_config(const StepArgs& a, const void** func, unsigned* block_thr
     threads = step_threads<false, true>();
   } else if (a.lat) {
     *func = step_variant_lat(ext);
-    threads = step_threads<false, false, true>();
+    threads = (unsigned)a.lat;
   } else {
     *func = step_variant_pack(ext);
   }

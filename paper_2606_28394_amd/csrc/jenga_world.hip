@@ -93,7 +93,7 @@ struct jg_world {
     size_t lds = 0;
     bool global = false;     // packs keep their state in device memory (islands too large for LDS)
     bool hot_bodies = false; // global packs: the serial walks' body arrays in LDS
-    bool lat = false;        // one tower per workgroup of four waves (small batches)
+    int lat = 0;             // threads of a workgroup that steps one tower (small batches; 0: not one)
     int64_t gwords = 0;      // words of one pack's device region
   };
   std::vector<PackClass> classes;   // launch classes, in pack order
@@ -273,7 +273,7 @@ int32_t build_layout(jg_world* w) {
   // an on-chip pack holds at most kRegBodies bodies (the register broadphase); larger islands
   // are kept in device memory, one tower each
   int target = w->prm.pack_bodies > 0 ? std::min(w->prm.pack_bodies, jg::kRegBodies) : 0;
-  bool lat = false;
+  int lat = 0;
   if (target <= 0) {
     const bool wide = w->prm.warm_start == 2 || w->prm.record_features;
     const size_t budget = wide ? 40 * 1024 : 20 * 1024;
@@ -288,8 +288,9 @@ int32_t build_layout(jg_world* w) {
       target = 1;
       if (!(w->prm.manifolds_per_body > 0.f)) mpb = 6.0f;
       // at most two towers per CU: each gets a workgroup of four waves (two per CU at two waves
-      // per SIMD), which share its manifolds, sweeps and residual
-      lat = w->prm.small_batch >= 0 && !wide && (int64_t)order.size() <= 2 * (int64_t)cus;
+      // per SIMD), or of eight where every tower has a CU to itself, which share its step
+      if (w->prm.small_batch >= 0 && !wide && (int64_t)order.size() <= 2 * (int64_t)cus)
+        lat = (int64_t)order.size() <= (int64_t)cus ? 8 * jg::kWave : 4 * jg::kWave;
     }
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -377,7 +378,7 @@ int32_t build_layout(jg_world* w) {
       c.first = (int)b;
       c.per_cu = per_cu;
       c.global = bins[b].global;
-      c.lat = lat && !bins[b].global;
+      c.lat = bins[b].global ? 0 : lat;
       w->classes.push_back(c);
     }
     jg_world::PackClass& c = w->classes.back();
@@ -410,7 +411,7 @@ int32_t build_layout(jg_world* w) {
   // allow run at the same occupancy: one launch holds them all (with the largest pack's LDS, as
   // long as that still fits the register-bound count), so that they share one launch tail
   {
-    const int reg_cap = lat ? 2 : ((w->prm.warm_start == 2 || w->prm.record_features) ? 4 : 8);
+    const int reg_cap = lat ? 8 * jg::kWave / lat : ((w->prm.warm_start == 2 || w->prm.record_features) ? 4 : 8);
     for (size_t k = 1; k < w->classes.size();) {
       jg_world::PackClass& into = w->classes[k - 1];
       const jg_world::PackClass& from = w->classes[k];
@@ -463,13 +464,13 @@ int32_t build_layout(jg_world* w) {
       // (with the network, every wave of the island has its own staging rows)
       c.gwords = ((int64_t)jg::kManPackWords * c.pc + jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) +
                   (mode == 2 ? (int64_t)(jg::kLearnedIslandWaves - 1) * jg::kStageWords : 0) +
-                  jg::window_words(c.nbp) + 2 * (int64_t)jg::kCandPerBody * c.nbp + 3) & ~(int64_t)3;
+                  jg::window_words(c.nbp) + (2 + 4) * (int64_t)jg::kCandPerBody * c.nbp + 3 + 3) & ~(int64_t)3;
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     } else {
-      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) + (c.lat ? jg::lat_words(c.nbp) : 0)) * 4;
+      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) + (c.lat ? jg::lat_words(c.nbp, c.lat) : 0)) * 4;
       if (c.lds > 160 * 1024)
         return fail(JG_ECAPACITY, "a launch class needs " + std::to_string(c.lds) + " bytes of LDS (max 163840)");
-      c.gwords = ((int64_t)jg::kManPackWords * c.pc + 3) & ~(int64_t)3;
+      c.gwords = ((int64_t)jg::kManPackWords * c.pc + (c.lat ? jg::lat_dev_words(c.pc, c.lat) : 0) + 3) & ~(int64_t)3;
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     }
     for (int k = 0; k < c.count; ++k) w->pack_slot0.push_back(w->pack_slot0.back() + c.pc);
@@ -1075,7 +1076,7 @@ int32_t jg_step_batch(jg_world* w, int32_t n_steps) {
     cls[k].gmem = w->d_gmem.p;
     cls[k].in_gmem = c.global ? 1 : 0;
     cls[k].hot_bodies = c.hot_bodies ? 1 : 0;
-    cls[k].lat = c.lat ? 1 : 0;
+    cls[k].lat = c.lat;
     cls[k].pack_goff = w->d_pack_goff.p;
   }
   if (w->prm.use_graph) {
