@@ -217,11 +217,13 @@ int32_t set_error(int32_t code, const std::string& msg);
 // ------------------------------------------------------------------------------------------------
 constexpr int kMegaThreads = 256;
 constexpr int kMegaBodyWords = 26;   // x3 q4 v3 w3 he3 invm Iw6 hm3 (SoA, stride nb)
-constexpr int kMegaBodyU32 = 8;      // flag, tower (0), colour mask lo, hi, cell, candidate count,
-                                     // candidate offset, cell-sorted body (stride nb)
+constexpr int kMegaBodyU32 = 8;      // flag, tower (0), colour mask lo, hi, cell (then near boxes), candidate
+                                     // offset (then first workgroup of the sweeps), last workgroup,
+                                     // cell-sorted body (stride nb)
 constexpr int kMegaScal = 256;       // scalar words (counters, colour tables)
+constexpr int kMegaBarWords = 32 * 17;   // barrier: a line each for the root, eight counters, eight generations
 constexpr int kMegaStagedPartition = 2048;  // colouring partitions up to this size are walked in LDS
-constexpr int kMegaChunk = 1024;            // pairs staged in LDS per walk chunk
+constexpr int kMegaLdsBytes = 160 * 1024;   // LDS of a workgroup: one to a CU
 
 struct MegaArgs {
   float *x, *q, *v, *w;
@@ -246,6 +248,7 @@ struct MegaArgs {
   float* body;                 // kMegaBodyWords * nb
   uint32_t* ubody;             // kMegaBodyU32 * nb
   int32_t* cells;              // 2 * (ncell_cap + 1): counts, starts
+  float* cellrec;              // 8 * nb: the bodies' boxes in cell order; in the sweeps their velocities
   int32_t ncell_cap;
   uint32_t* cand;              // 3 * cand_cap: body a, body b (~0u: the ground), collide flag / position
   int32_t cand_cap;
@@ -257,6 +260,8 @@ struct MegaArgs {
   float* red;                  // 2 * gridDim partial sums (residual)
   int32_t* ired;               // 2 * gridDim integer partials (scans, counts)
   int32_t* scal;               // kMegaScal words
+  uint32_t* bar;               // kMegaBarWords words of the grid-wide barrier (zero before the first launch),
+                               // then one per workgroup: the steps it has done
   // contacts of the launch's last step, canonical order (npts 0: a pair dropped by the colouring)
   int32_t *out_a, *out_b;
   uint32_t* out_meta;          // npts | colour << 4 | slots << 12

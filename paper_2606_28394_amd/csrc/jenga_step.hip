@@ -30,13 +30,13 @@
 //   9 integration: x += dt v, q from Eq. (quat_int) with world-frame omega,
 //     omega re-derived from the angular momentum (Eq. (newton_euler), torque free)
 //  10 Baumgarte correction (Eq. (baumgarte)), colour by colour
-#include <hip/hip_cooperative_groups.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <mutex>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "jenga_device.h"
 #include "mlp_device.h"
@@ -1253,7 +1253,46 @@ struct OwnedManifold {
   int body, col;         // body -1: the ground; col -1: no manifold
 };
 
-// Registers of colour-sorted manifold m (none when m >= nkept): the terms of a visit's own arithmetic.
+// This lane's side of a manifold from its record d, frame F, its body's inverse inertia and mass (S) and
+// dAB = F (x_A - x_B): the terms of a visit's own arithmetic.
+__device__ __forceinline__ void own_side(const ManPoints& d, const Frame& F, const LBody& S, const float dAB[3], bool is_b,
+                                         OwnedManifold& w) {
+  const float sg = is_b ? 1.f : -1.f;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) w.f[k] = sg * F.f[k / 3][k % 3];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float r[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] = is_b ? d.r[3 * j + k] + dAB[k] : d.r[3 * j + k];
+    SideRow<0> t0;
+    SideRow<1> t1;
+    SideRow<2> t2;
+    t0.build(S, r);
+    t1.build(S, r);
+    t2.build(S, r);
+    const float k0 = t0.kpart(S), k1 = t1.kpart(S), k2 = t2.kpart(S);
+    const float rk[3] = {__builtin_amdgcn_rcpf(k0 + pair_swap(k0)), __builtin_amdgcn_rcpf(k1 + pair_swap(k1)),
+                         __builtin_amdgcn_rcpf(k2 + pair_swap(k2))};
+    // a slot past the points is worked like the others, to no effect: its row has no lever arm, no
+    // response and no step (a branch per point would cost every visit its masks and register copies)
+    const bool point = j < d.np;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      w.i[9 * j + q] = point ? t0.i[q] : 0.f;
+      w.i[9 * j + 3 + q] = point ? t1.i[q] : 0.f;
+      w.i[9 * j + 6 + q] = point ? t2.i[q] : 0.f;
+      w.r[3 * j + q] = point ? r[q] : 0.f;
+      w.rk[3 * j + q] = point ? rk[q] : 0.f;
+      w.lam[3 * j + q] = point ? d.l[3 * j + q] : 0.f;
+    }
+    w.tb[j] = d.tb[j];
+  }
+  w.im = S.im;
+  w.mu = d.mu;
+}
+
+// Registers of colour-sorted manifold m (none when m >= nkept).
 __device__ __forceinline__ void own_manifold(const Lds& L, int m, int nkept, bool is_b, bool bias, OwnedManifold& w) {
   w.col = -1;
   if (m >= nkept) return;
@@ -1273,62 +1312,16 @@ __device__ __forceinline__ void own_manifold(const Lds& L, int m, int nkept, boo
     for (int k = 0; k < 3; ++k) dx[k] = L.x[k * L.nbp + a_] - L.x[k * L.nbp + b_];
     to_local(F, dx, dAB);
   }
-  const float sg = is_b ? 1.f : -1.f;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) w.f[k] = sg * F.f[k / 3][k % 3];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float r[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      r[k] = is_b ? d.r[3 * j + k] + dAB[k] : d.r[3 * j + k];
-      w.r[3 * j + k] = r[k];
-    }
-    SideRow<0> t0;
-    SideRow<1> t1;
-    SideRow<2> t2;
-    t0.build(S, r);
-    t1.build(S, r);
-    t2.build(S, r);
-    const float k0 = t0.kpart(S), k1 = t1.kpart(S), k2 = t2.kpart(S);
-    w.rk[3 * j] = __builtin_amdgcn_rcpf(k0 + pair_swap(k0));
-    w.rk[3 * j + 1] = __builtin_amdgcn_rcpf(k1 + pair_swap(k1));
-    w.rk[3 * j + 2] = __builtin_amdgcn_rcpf(k2 + pair_swap(k2));
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      w.i[9 * j + q] = t0.i[q];
-      w.i[9 * j + 3 + q] = t1.i[q];
-      w.i[9 * j + 6 + q] = t2.i[q];
-    }
-    w.tb[j] = d.tb[j];
-    // a slot past the points is worked like the others, to no effect: its row has no lever arm, no
-    // response and no step (a branch per point would cost every visit its masks and register copies)
-    const bool point = j < d.np;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) w.i[9 * j + k] = point ? w.i[9 * j + k] : 0.f;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      w.r[3 * j + k] = point ? w.r[3 * j + k] : 0.f;
-      w.rk[3 * j + k] = point ? w.rk[3 * j + k] : 0.f;
-      w.lam[3 * j + k] = point ? d.l[3 * j + k] : 0.f;
-    }
-  }
-  w.im = S.im;
-  w.mu = d.mu;
+  own_side(d, F, S, dAB, is_b, w);
   w.body = is_b && ground ? -1 : me;
   int col = 0;
   while (L.coloff[col + 1] <= m) ++col;
   w.col = col;
 }
 
-// A visit of an owned manifold.  vw: the bodies' velocities, eight words each (v, w, two unused).
-__device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const SolveOpts& o) {
-  float4 p = make_float4(0.f, 0.f, 0.f, 0.f), q = p;
-  if (w.body >= 0) {
-    p = vw[2 * w.body];
-    q = vw[2 * w.body + 1];
-  }
-  const float v[3] = {p.x, p.y, p.z}, om[3] = {p.w, q.x, q.y};
+// The rows of a visit of an owned manifold: v, om are this lane's body's velocities, with the visit's
+// change on return.
+__device__ __forceinline__ void rows_owned(OwnedManifold& w, float v[3], float om[3], const SolveOpts& o) {
   Frame F;
 #pragma unroll
   for (int k = 0; k < 9; ++k) F.f[k / 3][k % 3] = w.f[k];
@@ -1345,14 +1338,27 @@ __device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const 
     row_pair_cached<1>(S, w.r + 3 * j, w.i + 9 * j + 3, w.rk[3 * j + 1], w.lam[3 * j + 1], bound, o, 0.f);
     row_pair_cached<2>(S, w.r + 3 * j, w.i + 9 * j + 6, w.rk[3 * j + 2], w.lam[3 * j + 2], bound, o, 0.f);
   }
-  if (w.im > 0.f) {
-    float dv[3], dw[3], gv[3], gw[3];
+  float dv[3], dw[3], gv[3], gw[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) { dv[k] = S.v[k] - S.v0[k]; dw[k] = S.w[k] - S.w0[k]; }
-    to_world(F, dv, gv);
-    to_world(F, dw, gw);
-    vw[2 * w.body] = make_float4(v[0] + gv[0], v[1] + gv[1], v[2] + gv[2], om[0] + gw[0]);
-    vw[2 * w.body + 1] = make_float4(om[1] + gw[1], om[2] + gw[2], 0.f, 0.f);
+  for (int k = 0; k < 3; ++k) { dv[k] = S.v[k] - S.v0[k]; dw[k] = S.w[k] - S.w0[k]; }
+  to_world(F, dv, gv);
+  to_world(F, dw, gw);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { v[k] += gv[k]; om[k] += gw[k]; }
+}
+
+// A visit of an owned manifold.  vw: the bodies' velocities, eight words each (v, w, two unused).
+__device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const SolveOpts& o) {
+  float4 p = make_float4(0.f, 0.f, 0.f, 0.f), q = p;
+  if (w.body >= 0) {
+    p = vw[2 * w.body];
+    q = vw[2 * w.body + 1];
+  }
+  float v[3] = {p.x, p.y, p.z}, om[3] = {p.w, q.x, q.y};
+  rows_owned(w, v, om, o);
+  if (w.im > 0.f) {
+    vw[2 * w.body] = make_float4(v[0], v[1], v[2], om[0]);
+    vw[2 * w.body + 1] = make_float4(om[1], om[2], 0.f, 0.f);
   }
 }
 
@@ -1926,9 +1932,20 @@ __device__ __forceinline__ bool integrate_body(const Lds& L, int i, float m, flo
   return finite;
 }
 
+// Words that several workgroups of a grid-wide island write in turn (kShared): never in a cache.
+template <bool kShared>
+__device__ __forceinline__ void add_to(float* p, float d) {
+  if constexpr (kShared)
+    __hip_atomic_store(p, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + d, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p += d;
+}
+
 // Baumgarte position correction of one colliding pair (Eq. (baumgarte), reading R19), from its
 // record's depth and normal: x_A -= beta m_A^-1 c n, x_B += beta m_B^-1 c n with
 // c = max(0, depth - slop) / (m_A^-1 + m_B^-1), dynamic bodies only.
+template <bool kShared = false>
 __device__ __forceinline__ void baumgarte_pair(const Lds& L, int i, int j, bool ground, const float* rec, float beta,
                                                float slop) {
   const int NB = L.nbp;
@@ -1941,8 +1958,13 @@ __device__ __forceinline__ void baumgarte_pair(const Lds& L, int i, int j, bool 
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const float nk = rec[24 + k];
-    if (di) L.x[k * NB + i] -= beta * ia * corr * nk;
-    if (dj) L.x[k * NB + j] += beta * ib * corr * nk;
+    if constexpr (kShared) {
+      if (di) add_to<true>(&L.x[k * NB + i], -(beta * ia * corr * nk));
+      if (dj) add_to<true>(&L.x[k * NB + j], beta * ib * corr * nk);
+    } else {
+      if (di) L.x[k * NB + i] -= beta * ia * corr * nk;
+      if (dj) L.x[k * NB + j] += beta * ib * corr * nk;
+    }
   }
 }
 
@@ -3228,17 +3250,22 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
 // Islands stepped by the whole GPU (Sec. "Discussion and Implications for Anastylosis": site-scale
 // walls).  One cooperative launch runs every step; its phases are separated by grid-wide barriers
 // and every workgroup passes the same barriers in the same order (all loop bounds below are
-// uniform: launch parameters or scalars read after a barrier).  Body indices are 32-bit (the
-// ground is -1).  The stages are those of a pack, grid-wide:
+// uniform: launch parameters or scalars read after a barrier).  The sweeps have none: a body's visits
+// are counted with its velocities.  Body indices are 32-bit (the ground is -1).  A step of a
+// 100,000-stone wall takes 1.83 ms (9.9 ms with library barriers between the colours): of its 4.3 M cycles
+// the sweeps take 1.8, the colouring 0.86, the candidates 0.48, the uniform grid, manifolds, outputs and
+// position correction 0.1 to 0.2 each.  The stages are those of a pack, grid-wide:
 //   forces, frames -> uniform-grid broadphase (cells of the largest AABB plus the margin, 27
 //   neighbour cells, each body's candidates j > i sorted, the ground last: the canonical list with
 //   no per-body cap) -> SAT -> compaction -> partitioned greedy colouring (four passes: inside
 //   partitions of `partition` bodies, then between neighbouring partitions even / odd, then the
-//   rest, each pass in canonical order; one thread per partition or partition pair) -> colour sort
+//   rest, each pass in canonical order; one workgroup per partition or partition pair) -> colour sort
 //   -> manifolds -> PGS colour by colour -> outputs, residual -> integration -> Baumgarte colour
 //   by colour -> withdrawal at the end of a step.
 // ------------------------------------------------------------------------------------------------
 namespace mega {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum {
   sFrozen = 0, sErr, sNcand, sNman, sNcol, sCand, sMans, sPtsAll,
@@ -3269,6 +3296,103 @@ __device__ __forceinline__ Lds view(const MegaArgs& a) {
   return L;
 }
 
+// The barrier of every workgroup of the grid (all resident: the launch is cooperative).  Workgroups arrive
+// at one of eight counters (blockIdx mod 8 is the XCD a workgroup runs on), the last of each at a root
+// counter, and the last there advances the eight generation words that they wait on; the counters only
+// grow, so nothing is reset.  A small grid arrives at the root alone: one trip through memory less, but
+// every arrival in one line (2,400 against 3,400 cycles with 32 workgroups, 4,900 against 3,700 with 128).
+// Before it arrives, a workgroup's stores have been performed (s_waitcnt in every wave, then
+// __syncthreads) and its XCD's L2 written back; after it the caches are invalidated.  Each of the two
+// costs about 16 cycles per workgroup of the grid (one XCD's workgroups queue for its L2), so with 256
+// workgroups a barrier takes 12,600 cycles, 4,200 of them without the caches.
+struct GridBarrier {
+  static constexpr int kGroups = 8, kLine = 32;   // words: root, then the group counters, then their generations
+  static constexpr uint32_t kFlat = 32;           // workgroups up to which arrivals go to the root alone
+  uint32_t* w;
+  uint32_t gen;
+  __device__ __forceinline__ uint32_t* line(uint32_t k) const { return w + k * kLine; }
+  __device__ __forceinline__ uint32_t* my_gen() const { return line(1 + kGroups + blockIdx.x % kGroups); }
+  __device__ __forceinline__ static uint32_t arrivals(uint32_t* p) {
+    return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+  }
+  __device__ __forceinline__ explicit GridBarrier(uint32_t* words) : w(words) {
+    // (no generation can advance before this workgroup has arrived)
+    gen = __hip_atomic_load(my_gen(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void sync() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      const uint32_t G = gridDim.x, g = blockIdx.x % kGroups, groups = min((uint32_t)kGroups, G), next = gen + 1u;
+      bool open;
+      if (G <= kFlat) open = arrivals(line(0)) == G * next;
+      else open = arrivals(line(1 + g)) == (G - g + kGroups - 1) / kGroups * next && arrivals(line(0)) == groups * next;
+      if (open)
+        for (uint32_t k = 0; k < groups; ++k)
+          __hip_atomic_store(line(1 + kGroups + k), next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      while (__hip_atomic_load(my_gen(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) __builtin_amdgcn_s_sleep(1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    ++gen;
+    __syncthreads();
+  }
+};
+
+// Steps that only workgroups with bodies in common must take in order (a colour of the sweeps or of the
+// position correction): each posts how many it has done, and waits for those it shares bodies with,
+// workgroups lo to hi, to have done as many.  Between steps the shared words are read and written past
+// the caches.  A post and a poll take about 2,000 cycles, and a workgroup that is late holds up its
+// neighbours only; the grid's light barrier took 8,000 to 9,000 of a colour's 20,000 cycles.
+struct NeighbourSteps {
+  uint32_t* done;          // steps done, per workgroup
+  int lo = 0, hi = 0;
+  uint32_t n = 0;          // steps this workgroup has done
+  __device__ __forceinline__ void post() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are performed
+    __syncthreads();
+    ++n;
+    if (threadIdx.x == 0) __hip_atomic_store(done + blockIdx.x, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void wait() {
+    if (threadIdx.x < kWave) {
+      bool ready;
+      do {
+        ready = true;
+        for (int b = lo + (int)threadIdx.x; b <= hi; b += kWave)
+          ready = ready && __hip_atomic_load(done + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n;
+      } while (!__all(ready));
+    }
+    __syncthreads();
+  }
+};
+
+// The bodies' velocities during the sweeps, which several workgroups write: 32 bytes each, two pieces of 16
+// (v and w), read and written past the caches (the scope bit of an agent-scope access).  The fourth word
+// of a piece counts the visits that the body has had: a visit waits for its number, so that the data is its
+// own signal, and no barrier stands between the colours.  A lane's aligned 16 bytes are one request.
+struct SharedVelocities {
+  static constexpr int kAgent = 16;   // cache policy: SC1
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ SharedVelocities(float* p, int nb)
+      : r(__builtin_amdgcn_make_buffer_rsrc(p, 0, (int)((uint32_t)nb * 32u), 0x00027000)) {}   // raw, range checked
+  // returns whether both pieces are the visit's
+  __device__ __forceinline__ bool load(int i, uint32_t visit, float v[3], float w[3]) const {
+    asm volatile("" ::: "memory");   // (read again each time)
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(r, (uint32_t)i * 32u, 0, kAgent);
+    const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(r, (uint32_t)i * 32u + 16u, 0, kAgent);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { v[k] = __uint_as_float(a[k]); w[k] = __uint_as_float(b[k]); }
+    return a[3] == visit && b[3] == visit;
+  }
+  __device__ __forceinline__ void store(int i, uint32_t visits, const float v[3], const float w[3]) const {
+    const u32x4 a = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), visits};
+    const u32x4 b = {__float_as_uint(w[0]), __float_as_uint(w[1]), __float_as_uint(w[2]), visits};
+    __builtin_amdgcn_raw_buffer_store_b128(a, r, (uint32_t)i * 32u, 0, kAgent);
+    __builtin_amdgcn_raw_buffer_store_b128(b, r, (uint32_t)i * 32u + 16u, 0, kAgent);
+  }
+};
+
 // block-wide sums (and a second sum) through LDS; every thread gets the results
 __device__ __forceinline__ void block_sum2(int32_t* sh, int32_t* sh2, int& x, int& y) {
   sh[threadIdx.x] = x;
@@ -3289,7 +3413,7 @@ __device__ __forceinline__ void block_sum2(int32_t* sh, int32_t* sh2, int& x, in
 // Exclusive prefix sums of v[0, n) in place over the whole grid; returns the total.  Thread t
 // scans the run [t per, (t + 1) per); the workgroups' sums go through ired (one barrier inside).
 // The caller passes a barrier before anyone reads v.
-__device__ int grid_scan(cooperative_groups::grid_group& grid, int32_t* v, int n, int32_t* ired, int32_t* sh,
+__device__ int grid_scan(GridBarrier& grid, int32_t* v, int n, int32_t* ired, int32_t* sh,
                          int32_t* sh2) {
   const int T = (int)gridDim.x * kMegaThreads;
   const int gt = (int)blockIdx.x * kMegaThreads + (int)threadIdx.x;
@@ -3368,27 +3492,102 @@ __device__ __forceinline__ Grid make_grid(const int32_t* S, float margin, int ca
   return G;
 }
 
-// greedy first fit of canonical pair m = (a, b) over the colour masks of its dynamic bodies
-__device__ __forceinline__ void colour_pair(int m, int a, int b, const uint32_t* flag, uint32_t* mlo, uint32_t* mhi,
-                                            int32_t* col_of, int32_t* S) {
-  const bool da = (flag[a] & kDynamic) != 0, db = b >= 0 && (flag[b] & kDynamic);
-  uint64_t u = 0ull;
-  if (da) u |= (uint64_t)mlo[a] | ((uint64_t)mhi[a] << 32);
-  if (db) u |= (uint64_t)mlo[b] | ((uint64_t)mhi[b] << 32);
-  int col = -1;
-  if (u != ~0ull) {
-    col = __ffsll((unsigned long long)~u) - 1;
-    const uint64_t bit = 1ull << col;
-    if (da) { mlo[a] |= (uint32_t)bit; mhi[a] |= (uint32_t)(bit >> 32); }
-    if (db) { mlo[b] |= (uint32_t)bit; mhi[b] |= (uint32_t)(bit >> 32); }
-  } else {
-    atomicOr(&S[sErr], (int)kErrCol);
+// a body's colour mask in LDS or, agent-wide, in device memory
+template <bool kLds>
+__device__ __forceinline__ uint32_t mask_read(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool kLds>
+__device__ __forceinline__ void mask_add(uint32_t* p, uint32_t bit) {
+  (void)__hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Greedy first fit for a wave's first n lanes' pairs in lane order (i, j: their dynamic bodies, -1 if none),
+// over the bodies' colour masks; returns the lane's colour, -1 if none is free.  Turn `turn` of the list
+// waits until the turns before it are done.  The chain from a pair to the next is a lane's free colours
+// read into scalars, the first of them, and that bit out of those of the later lanes that share a body.
+template <bool kLds>
+__device__ __forceinline__ int colour_group(int n, int i, int j, uint32_t* mlo, uint32_t* mhi, int32_t* turns,
+                                            uint32_t turn) {
+  constexpr int kStep = 4;   // (a wave is a whole number of them; lanes from n on have no free colour and share nothing)
+  const int lane = (int)threadIdx.x & (kWave - 1);
+  const int ki = i >= 0 ? i : (int)0x80000000 + lane, kj = j >= 0 ? j : (int)0xc0000000 + lane;   // (none: shared with no lane)
+  int slo = 0, shi = 0;      // the later lanes that share a body with this one
+  for (int k0 = 0; k0 < n; k0 += kStep)
+#pragma unroll
+    for (int k = k0; k < k0 + kStep; ++k) {
+      const int ik = __builtin_amdgcn_readlane(ki, k), jk = __builtin_amdgcn_readlane(kj, k);
+      uint64_t s = __ballot(ki == ik) | __ballot(ki == jk) | __ballot(kj == ik) | __ballot(kj == jk);
+      s &= ~1ull << k;
+      slo = lane == k ? (int)(uint32_t)s : slo;
+      shi = lane == k ? (int)(uint32_t)(s >> 32) : shi;
+    }
+  while (poll(reinterpret_cast<uint32_t*>(turns)) != turn) {}
+  lds_order();
+  uint32_t lo = lane < n ? ~0u : 0u, hi = lo;
+  if (i >= 0) { lo &= ~mask_read<kLds>(mlo + i); hi &= ~mask_read<kLds>(mhi + i); }
+  if (j >= 0) { lo &= ~mask_read<kLds>(mlo + j); hi &= ~mask_read<kLds>(mhi + j); }
+  for (int k0 = 0; k0 < n; k0 += kStep)
+#pragma unroll
+    for (int k = k0; k < k0 + kStep; ++k) {
+      const uint64_t f = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, k) |
+                         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, k) << 32);
+      uint64_t s = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(slo, k) |
+                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(shi, k) << 32);
+      s = f != 0ull ? s : 0ull;
+      const uint64_t keep = ~(1ull << (__builtin_ctzll(f | (1ull << 63))));
+      const bool shared = __builtin_amdgcn_inverse_ballot_w64(s);
+      const uint32_t klo = lo & (uint32_t)keep, khi = hi & (uint32_t)(keep >> 32);
+      lo = shared ? klo : lo;
+      hi = shared ? khi : hi;
+    }
+  const int col = lo ? __builtin_ctz(lo) : (hi ? 32 + __builtin_ctz(hi) : -1);
+  if (col >= 0) {
+    uint32_t* const half = col < 32 ? mlo : mhi;
+    if (i >= 0) mask_add<kLds>(half + i, 1u << (col & 31));
+    if (j >= 0) mask_add<kLds>(half + j, 1u << (col & 31));
   }
-  col_of[m] = col;
+  if (!kLds) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the masks are changed before the turn ends)
+  lds_order();
+  if (lane == 0) post(reinterpret_cast<uint32_t*>(turns), turn + 1u);
+  return col;
+}
+
+// a body's inverse inertia in the frame F and its inverse mass (zero for the ground, which reads body 0's
+// words); they do not change during the sweeps
+__device__ __forceinline__ void local_inertia(const float I[6], float im, bool ground, const Frame& F, LBody& b) {
+  float Iw[6], g[3][3];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) Iw[k] = ground ? 0.f : I[k];
+  b.im = ground ? 0.f : im;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) sym_mulx(Iw, F.f[j], g[j]);
+  b.I[0] = dot3x(F.f[0], g[0]); b.I[1] = dot3x(F.f[1], g[1]); b.I[2] = dot3x(F.f[2], g[2]);
+  b.I[3] = dot3x(F.f[0], g[1]); b.I[4] = dot3x(F.f[0], g[2]); b.I[5] = dot3x(F.f[1], g[2]);
+}
+__device__ __forceinline__ void local_inertia(const Lds& L, int i, bool ground, const Frame& F, LBody& b) {
+  float I[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) I[k] = L.Iw[k * L.nbp + i];
+  local_inertia(I, L.invm[i], ground, F, b);
+}
+
+// body i's velocities (v, w as they were read) with the visit's change, for a dynamic body
+__device__ __forceinline__ void shared_change(const SharedVelocities& vw, int i, const Frame& F, const LBody& b, float v[3],
+                                              float w[3]) {
+  if (!(b.im > 0.f)) return;
+  float dv[3], dw[3], gv[3], gw[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { dv[k] = b.v[k] - b.v0[k]; dw[k] = b.w[k] - b.w0[k]; }
+  to_world(F, dv, gv);
+  to_world(F, dw, gw);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { v[k] += gv[k]; w[k] += gw[k]; }
+  vw.store(i, 0u, v, w);
 }
 
 // one PGS visit of the record at `rec` (pair a, b; b < 0: the ground), one thread
-__device__ __forceinline__ void solve_rec(const Lds& L, float* rec, const float* tbp, int a, int b, int np, float mu,
+__device__ __forceinline__ void solve_rec(const Lds& L, const SharedVelocities& vw, float* rec, const float* tbp, int a, int b, int np, float mu,
                                           const SolveOpts& o) {
   float r[12], l[12], tb[4];
   const float4* r4 = reinterpret_cast<const float4*>(rec);
@@ -3403,10 +3602,28 @@ __device__ __forceinline__ void solve_rec(const Lds& L, float* rec, const float*
   const float n[3] = {nd.x, nd.y, nd.z};
   tb[0] = o.bias ? t4.x : 0.f; tb[1] = o.bias ? t4.y : 0.f; tb[2] = o.bias ? t4.z : 0.f; tb[3] = o.bias ? t4.w : 0.f;
   const bool ground = b < 0;
+  const int NB = L.nbp, ob = ground ? 0 : b;
   Frame F;
+  make_frame(n, F);
+  float vA[3], wA[3], vB[3], wB[3], dAB[3] = {0.f, 0.f, 0.f};
   LBody A, B;
-  float dAB[3];
-  pair_open(L, a, ground ? 0 : b, ground, n, F, A, B, dAB);
+  vw.load(a, 0u, vA, wA);
+  vw.load(ob, 0u, vB, wB);
+  local_inertia(L, a, false, F, A);
+  local_inertia(L, ob, ground, F, B);
+  if (ground) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { vB[k] = 0.f; wB[k] = 0.f; }
+  } else {
+    float d[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] = L.x[k * NB + a] - L.x[k * NB + b];
+    to_local(F, d, dAB);
+  }
+  to_local(F, vA, A.v); to_local(F, wA, A.w);
+  to_local(F, vB, B.v); to_local(F, wB, B.w);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) { A.v0[k] = A.v[k]; A.w0[k] = A.w[k]; B.v0[k] = B.v[k]; B.w0[k] = B.w[k]; }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     if (j < np) {
@@ -3415,26 +3632,129 @@ __device__ __forceinline__ void solve_rec(const Lds& L, float* rec, const float*
       solve_point(A, B, rA, rB, &l[3 * j], mu, o, tb[j]);
     }
   }
-  store_local(L, a, F, A);
-  if (!ground) store_local(L, b, F, B);
+  shared_change(vw, a, F, A, vA, wA);
+  if (!ground) shared_change(vw, b, F, B, vB, wB);
   float4* w4 = reinterpret_cast<float4*>(rec);
 #pragma unroll
   for (int c = 0; c < 3; ++c) w4[3 + c] = make_float4(l[4 * c], l[4 * c + 1], l[4 * c + 2], l[4 * c + 3]);
 }
 
+constexpr int kNear = 16;       // near boxes of a body that the walk keeps in registers
+
+// LDS of a workgroup of the grid-wide kernel, in words: reductions and scans, the colours' offsets, then a
+// region for the colouring (four words per body of two staged partitions, and their dynamic flags) and,
+// in the sweeps, for the records of the workgroup's lane pairs.
+constexpr int kPairs = kMegaThreads / 2;      // lane pairs of a workgroup
+constexpr int kRecWords = 31;                 // a record in LDS: r 12, impulses 12, n 3, bodies 2, points and colour, slot
+constexpr int kLdsFixed = 4 * kMegaThreads + 136;
+constexpr int kLdsVisits = (kMegaLdsBytes / 4 - kLdsFixed) / (kRecWords * kPairs);   // a pair's records that fit
+static_assert(kLdsFixed + 2 * 2 * kMegaStagedPartition <= kMegaLdsBytes / 4, "staged partitions");
+
+// What a lane reads for its side of a visit, but for the impulses and velocities: the slot's record (from LDS,
+// word f at [f * kPairs], or from memory) and its body's state.  Read before the visit before it is worked,
+// so that the way through the caches (4,900 cycles a visit with the preparation behind it) is hidden.
+struct PairRecord {
+  ManPoints d;
+  int a, b;      // b < 0: the ground
+  float dx[3], Iw[6], im;
+  uint32_t flag, mlo, mhi;
+};
+__device__ __forceinline__ void read_pair(const Lds& L, const uint32_t* mlo, const uint32_t* mhi, const uint32_t* l,
+                                          const float* rec, const float* tbp, int a, int b, int np, bool bias, bool is_b,
+                                          PairRecord& w) {
+  const int NB = L.nbp;
+  w.a = a; w.b = b; w.d.np = np;
+  if (l) {
+    w.a = (int)l[27 * kPairs];
+    w.b = (int)l[28 * kPairs];
+    w.d.np = (int)(l[29 * kPairs] & 15u);
+  }
+  const int ob = w.b < 0 ? 0 : w.b, me = is_b ? ob : w.a;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) w.dx[k] = L.x[k * NB + w.a] - L.x[k * NB + ob];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) w.Iw[k] = L.Iw[k * NB + me];
+  w.im = L.invm[me];
+  w.flag = L.flag[me];
+  w.mlo = mlo[me];
+  w.mhi = mhi[me];
+  if (l) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) w.d.r[k] = __uint_as_float(l[k * kPairs]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w.d.n[k] = __uint_as_float(l[(24 + k) * kPairs]);
+  } else {
+    const float4* r4 = reinterpret_cast<const float4*>(rec);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float4 x = r4[c];
+      w.d.r[4 * c] = x.x; w.d.r[4 * c + 1] = x.y; w.d.r[4 * c + 2] = x.z; w.d.r[4 * c + 3] = x.w;
+    }
+    const float4 nd = r4[6];
+    w.d.n[0] = nd.x; w.d.n[1] = nd.y; w.d.n[2] = nd.z;
+  }
+  const float4 t4 = bias ? *reinterpret_cast<const float4*>(tbp) : make_float4(0.f, 0.f, 0.f, 0.f);
+  w.d.tb[0] = t4.x; w.d.tb[1] = t4.y; w.d.tb[2] = t4.z; w.d.tb[3] = t4.w;
+}
+
+// The visit, ready but for the bodies' velocities, which visits before it may still change.
+__device__ __forceinline__ void prepare_pair(PairRecord& p, const uint32_t* l, const float* rec, bool is_b, float mu,
+                                             OwnedManifold& w) {
+  const bool ground = p.b < 0;
+  if (l) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) p.d.l[k] = __uint_as_float(l[(12 + k) * kPairs]);
+  } else {
+    const float4* r4 = reinterpret_cast<const float4*>(rec);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const float4 y = r4[3 + c];
+      p.d.l[4 * c] = y.x; p.d.l[4 * c + 1] = y.y; p.d.l[4 * c + 2] = y.z; p.d.l[4 * c + 3] = y.w;
+    }
+  }
+  float dAB[3] = {0.f, 0.f, 0.f};
+  Frame F;
+  make_frame(p.d.n, F);
+  LBody S;
+  local_inertia(p.Iw, p.im, is_b && ground, F, S);
+  if (!ground) to_local(F, p.dx, dAB);
+  own_side(p.d, F, S, dAB, is_b, w);
+  w.mu = mu;
+  w.body = is_b && ground ? -1 : (is_b ? p.b : p.a);
+}
+
+// (dynamic: its body has visits before this one, `visit` of them, to wait for, and after it)
+__device__ __forceinline__ void solve_prepared(const SharedVelocities& vw, OwnedManifold& w, bool dynamic, uint32_t visit,
+                                               const SolveOpts& o) {
+  float v[3], om[3];
+  while (!__all(vw.load(w.body < 0 ? 0 : w.body, visit, v, om) || !dynamic)) {}
+  if (w.body < 0) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { v[k] = 0.f; om[k] = 0.f; }
+  }
+  rows_owned(w, v, om, o);
+  if (dynamic) vw.store(w.body, visit + 1u, v, om);
+}
+
 }  // namespace mega
 
 __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
-  namespace cg = cooperative_groups;
   using namespace mega;
-  cg::grid_group grid = cg::this_grid();
-  __shared__ int32_t sh[kMegaThreads], sh2[kMegaThreads];
-  __shared__ float shf[kMegaThreads], shf2[kMegaThreads];
-  // partition walks: colour masks (2 words) and dynamic flags of up to two partitions, pairs
-  __shared__ uint32_t lmask[4 * kMegaStagedPartition];
-  __shared__ uint8_t ldyn[2 * kMegaStagedPartition];
-  __shared__ int32_t lpair[2 * kMegaChunk];
+  GridBarrier grid(a.bar);
   const int NB = a.nb, CAP = a.cap, CC = a.cand_cap;
+  extern __shared__ __align__(16) uint32_t mega_lds[];
+  int32_t* const sh = reinterpret_cast<int32_t*>(mega_lds);
+  int32_t* const sh2 = sh + kMegaThreads;
+  float* const shf = reinterpret_cast<float*>(mega_lds + 2 * kMegaThreads);
+  float* const shf2 = shf + kMegaThreads;
+  int32_t* const lbase = reinterpret_cast<int32_t*>(mega_lds + 4 * kMegaThreads);  // the workgroup's first slot of each colour
+  int32_t* const lcount = lbase + kMaxColours;                                     // and its slots there
+  int32_t* const lflag = lcount + kMaxColours;
+  uint32_t* const wlo = a.ubody + 5 * NB;   // first and last workgroup that works on a body (after the candidates)
+  uint32_t* const whi = a.ubody + 6 * NB;
+  NeighbourSteps steps;
+  steps.done = a.bar + kMegaBarWords;
+  uint32_t* const region = mega_lds + kLdsFixed;
   const int gt = (int)blockIdx.x * kMegaThreads + (int)threadIdx.x;
   const int GS = (int)gridDim.x * kMegaThreads;
   const Lds L = view(a);
@@ -3459,7 +3779,10 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
   int32_t* const far = a.part + a.nparts + 1;
   const float dt = a.dt;
   const SolveOpts opts = {a.restitution, a.friction_cone != 0, a.restitution_bias != 0};
-  const int PS = a.partition;
+  const int PS = min(a.partition, NB);   // (larger: one partition)
+  float4* const cellrec = reinterpret_cast<float4*>(a.cellrec);   // per cell-sorted body: position, AABB, flags, index
+  uint32_t* const near = reinterpret_cast<uint32_t*>(a.man);      // near boxes of each body (until the pairs are placed)
+  const int nnear = min(kNear, (int)min((int64_t)kNear, 7 * (int64_t)CC / NB));   // their slots per body
 
   // ---- load the island (inverse mass; the inverse inertia is taken where needed) ----
   for (int i = gt; i < NB; i += GS) {
@@ -3569,6 +3892,8 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
         S[sNcol] = 0;
       }
       if (gt < kMaxColours) S[sColCnt + gt] = 0;
+      steps.n = 0;
+      if (threadIdx.x == 0) __hip_atomic_store(steps.done + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       for (int c = gt; c <= a.ncell_cap; c += GS) { cstart[c] = 0; cfill[c] = 0; }
       grid.sync();
       // ---- 3. uniform grid: bounds of the active centres, largest AABB half size ----
@@ -3632,7 +3957,12 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
       grid.sync();
       for (int i = gt; i < NB; i += GS) {
         const int c = cellof[i];
-        if (c >= 0) cellbody[cstart[c] + atomicAdd(&cfill[c], 1)] = i;
+        if (c >= 0) {
+          const int k = cstart[c] + atomicAdd(&cfill[c], 1);
+          cellbody[k] = i;
+          cellrec[2 * k] = make_float4(L.x[i], L.x[NB + i], L.x[2 * NB + i], L.hm[i]);
+          cellrec[2 * k + 1] = make_float4(L.hm[NB + i], L.hm[2 * NB + i], __uint_as_float(L.flag[i]), __int_as_float(i));
+        }
       }
       grid.sync();
       // ---- candidates: per body i, the bodies j > i of the 27 neighbour cells that pass
@@ -3689,7 +4019,52 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
         }
         return cnt;
       };
-      for (int i = gt; i < NB; i += GS) ccount[i] = walk(i, nullptr, 0);
+      // One pass finds them: the three cells of a row along x are one run of cell-sorted records, read a
+      // few at a time; a body's hits stay sorted in registers and go to its slots.  A body with more near
+      // boxes than slots is walked again when its run has its place.
+      for (int i = gt; i < NB; i += GS) {
+        int boxes = 0, all = 0;
+        const uint32_t fi = L.flag[i];
+        if (fi & kActive) {
+          const bool dyni = (fi & kDynamic) != 0;
+          float xi[3], hi[3];
+          load3(L.x, NB, i, xi);
+          load3(L.hm, NB, i, hi);
+          uint32_t v[kNear];
+#pragma unroll
+          for (int q = 0; q < kNear; ++q) v[q] = ~0u;
+          int ci[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) ci[k] = min(G.n[k] - 1, max(0, (int)floorf((xi[k] - G.lo[k]) / G.h)));
+          const int x0 = max(0, ci[0] - 1), x1 = min(G.n[0] - 1, ci[0] + 1);
+          for (int cz = max(0, ci[2] - 1); cz <= min(G.n[2] - 1, ci[2] + 1); ++cz)
+            for (int cy = max(0, ci[1] - 1); cy <= min(G.n[1] - 1, ci[1] + 1); ++cy) {
+              const int row = (cz * G.n[1] + cy) * G.n[0];
+              const int k1 = cstart[row + x1 + 1];
+#pragma unroll 4
+              for (int k = cstart[row + x0]; k < k1; ++k) {
+                const float4 p = cellrec[2 * k], q = cellrec[2 * k + 1];
+                const uint32_t fj = __float_as_uint(q.z), j = (uint32_t)__float_as_int(q.w);
+                const bool hit = j > (uint32_t)i && (dyni || (fj & kDynamic)) &&   // (only active bodies are in cells)
+                                 fabsf(xi[0] - p.x) <= hi[0] + p.w + a.margin &&
+                                 fabsf(xi[1] - p.y) <= hi[1] + q.x + a.margin &&
+                                 fabsf(xi[2] - p.z) <= hi[2] + q.y + a.margin;
+                if (hit) {
+                  ++boxes;
+#pragma unroll
+                  for (int t = kNear - 1; t > 0; --t) v[t] = j < v[t - 1] ? v[t - 1] : min(j, v[t]);
+                  v[0] = min(j, v[0]);
+                }
+              }
+            }
+#pragma unroll
+          for (int q = 0; q < kNear; ++q)
+            if (q < boxes && q < nnear) near[(size_t)i * nnear + q] = v[q];
+          all = boxes + (dyni && (xi[2] - hi[2] <= a.margin) ? 1 : 0);
+        }
+        cellof[i] = boxes;      // (the cells are done with)
+        ccount[i] = all;
+      }
       grid.sync();
       const int ncand_all = grid_scan(grid, ccount, NB, a.ired, sh, sh2);
       if (gt == 0) S[sNcand] = min(ncand_all, CC);
@@ -3707,11 +4082,18 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
       for (int i = gt; i < NB; i += GS) {
         const int off = ccount[i], end = i + 1 < NB ? ccount[i + 1] : ncand_all;
         if (end > ncand || end == off) continue;
-        walk(i, cb + off, end - off);
+        const int boxes = cellof[i];
+        if (boxes > nnear) {
+          walk(i, cb + off, end - off);
+        } else {
+          for (int k = 0; k < boxes; ++k) cb[off + k] = near[(size_t)i * nnear + k];
+          if (off + boxes < end) cb[off + boxes] = ~0u;
+        }
         for (int k = off; k < end; ++k) ca[k] = (uint32_t)i;
       }
       grid.sync();
       // ---- 4. narrowphase (SAT, Sec. "Narrowphase: OBB SAT"; the ground: a vertex below z = 0) ----
+      for (int i = gt; i < NB; i += GS) { wlo[i] = ~0u; whi[i] = 0u; }   // (the candidates' offsets are done with)
       for (int k = gt; k < ncand; k += GS) {
         const int i = (int)ca[k];
         const uint32_t jb = cb[k];
@@ -3757,86 +4139,77 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
         if (p < a.nparts) far[p] = 0;
       }
       grid.sync();
-      if (PS <= kMegaStagedPartition) {
-        // one workgroup per partition (pass 1) or partition pair (passes 2, 3): the bodies' colour
-        // masks and dynamic flags and the pairs, in chunks, staged in LDS; its first thread walks them
+      // One workgroup per partition (pass 0: its own pairs) or partition pair (passes 1 and 2: those with the
+      // next partition), with the bodies' colour masks in LDS if they fit; last, one workgroup takes the
+      // pairs between partitions further apart.  The pairs depend on each other in long chains (a wall's
+      // courses), so they are taken one after the other, 64 of the list to a wave, the waves in turn; one
+      // that waits for its turn has its pairs and what they share with each other ready.  The three
+      // passes over a 100,000-stone wall take 0.83 M cycles; with a thread per partition it was 9 M, and
+      // with a pair coloured once its bodies' turns (polled in LDS) had come 2.3 M.
+      {
+        uint32_t* const clo = region;
+        uint32_t* const chi = clo + 2 * kMegaStagedPartition;
+        const int lane = (int)threadIdx.x & (kWave - 1), wv = (int)threadIdx.x / kWave;
+        const bool staged = PS <= kMegaStagedPartition;
+        // partition p's pairs whose second body is at `want`: the ground or this partition (0), the next (1),
+        // further (2)
+        auto walk_pairs = [&](auto lds, int p, int want) {
+          constexpr bool kLds = decltype(lds)::value;
+          const int b0 = p * PS, nbp = min((want == 0 ? 1 : 2) * PS, NB - b0);
+          const int m0 = a.part[p], m1 = a.part[p + 1];
+          if (kLds)
+            for (int i = (int)threadIdx.x; i < nbp; i += kMegaThreads) {
+              clo[i] = mlo[b0 + i];
+              chi[i] = mhi[b0 + i];
+            }
+          if (threadIdx.x == 0) { lflag[0] = 0; lflag[1] = 0; }
+          __syncthreads();
+          for (int c0 = m0 + wv * kWave; c0 < m1; c0 += kMegaThreads) {
+            const int m = c0 + lane;
+            const int ig = m < m1 ? man_a[m] : 0, jg = m < m1 ? man_b[m] : 0;
+            const int place = jg < b0 + PS ? 0 : (jg < b0 + 2 * PS ? 1 : 2);   // (b0 + 2 PS: below 2^31, bodies are below 2^29)
+            const bool in = m < m1 && place == want;
+            if (want == 0 && m < m1 && place == 2) atomicAdd(&lflag[1], 1);
+            // these pairs to the front of the wave, in order
+            const uint64_t ins = __ballot(in);
+            const int n = __popcll(ins), rank = __popcll(ins & ((1ull << lane) - 1));
+            const int base = kLds ? b0 : 0;
+            if (in) {
+              sh[wv * kWave + rank] = (L.flag[ig] & kDynamic) ? ig - base : -1;
+              sh2[wv * kWave + rank] = jg >= 0 && (L.flag[jg] & kDynamic) ? jg - base : -1;
+            }
+            lds_order();
+            const int i = lane < n ? sh[wv * kWave + lane] : -1, j = lane < n ? sh2[wv * kWave + lane] : -1;
+            const int got = colour_group<kLds>(n, i, j, kLds ? clo : mlo, kLds ? chi : mhi, lflag, (uint32_t)((c0 - m0) / kWave));
+            sh[wv * kWave + lane] = got;
+            lds_order();
+            if (in) {
+              const int col = sh[wv * kWave + rank];
+              man_col[m] = col;
+              if (col < 0) atomicOr(&S[sErr], (int)kErrCol);
+            }
+            lds_order();
+          }
+          __syncthreads();
+          if (kLds)
+            for (int i = (int)threadIdx.x; i < nbp; i += kMegaThreads) {
+              mlo[b0 + i] = clo[i];
+              mhi[b0 + i] = chi[i];
+            }
+          if (want == 0 && threadIdx.x == 0) far[p] = lflag[1];
+          __syncthreads();
+        };
         for (int pass = 0; pass < 3; ++pass) {
           for (int p = (int)blockIdx.x; p < a.nparts; p += (int)gridDim.x) {
             if (pass > 0 && (p & 1) != pass - 1) continue;
-            const int b0 = p * PS, nbp = min((pass == 0 ? 1 : 2) * PS, NB - b0);
-            for (int i = (int)threadIdx.x; i < nbp; i += kMegaThreads) {
-              lmask[2 * i] = mlo[b0 + i];
-              lmask[2 * i + 1] = mhi[b0 + i];
-              ldyn[i] = (L.flag[b0 + i] & kDynamic) ? 1 : 0;
-            }
-            int nfar = 0;
-            for (int c0 = a.part[p]; c0 < a.part[p + 1]; c0 += kMegaChunk) {
-              const int n = min(kMegaChunk, a.part[p + 1] - c0);
-              __syncthreads();
-              for (int k = (int)threadIdx.x; k < n; k += kMegaThreads) {
-                lpair[2 * k] = man_a[c0 + k] - b0;
-                lpair[2 * k + 1] = man_b[c0 + k];
-              }
-              __syncthreads();
-              if (threadIdx.x == 0) {
-                for (int k = 0; k < n; ++k) {
-                  // the second body's place: the ground or this partition (0), the next (1), further (2)
-                  const int i = lpair[2 * k], jg = lpair[2 * k + 1];
-                  const int j = jg < 0 ? -1 : jg - b0;
-                  const int where = j < PS ? 0 : (j < 2 * PS ? 1 : 2);
-                  if (pass == 0 && where == 2) ++nfar;
-                  if (where != (pass == 0 ? 0 : 1)) continue;
-                  const bool da = ldyn[i] != 0, db = j >= 0 && ldyn[j] != 0;
-                  uint64_t u = 0ull;
-                  if (da) u |= (uint64_t)lmask[2 * i] | ((uint64_t)lmask[2 * i + 1] << 32);
-                  if (db) u |= (uint64_t)lmask[2 * j] | ((uint64_t)lmask[2 * j + 1] << 32);
-                  int col = -1;
-                  if (u != ~0ull) {
-                    col = __ffsll((unsigned long long)~u) - 1;
-                    const uint64_t bit = 1ull << col;
-                    if (da) { lmask[2 * i] |= (uint32_t)bit; lmask[2 * i + 1] |= (uint32_t)(bit >> 32); }
-                    if (db) { lmask[2 * j] |= (uint32_t)bit; lmask[2 * j + 1] |= (uint32_t)(bit >> 32); }
-                  } else {
-                    atomicOr(&S[sErr], (int)kErrCol);
-                  }
-                  man_col[c0 + k] = col;
-                }
-              }
-            }
-            __syncthreads();
-            for (int i = (int)threadIdx.x; i < nbp; i += kMegaThreads) {
-              mlo[b0 + i] = lmask[2 * i];
-              mhi[b0 + i] = lmask[2 * i + 1];
-            }
-            if (pass == 0 && threadIdx.x == 0) far[p] = nfar;
-            __syncthreads();
+            if (staged) walk_pairs(std::true_type{}, p, pass == 0 ? 0 : 1);
+            else walk_pairs(std::false_type{}, p, pass == 0 ? 0 : 1);
           }
           grid.sync();
         }
-      } else {
-        // partitions too large to stage: one thread per partition (pair), from device memory
-        for (int pass = 0; pass < 3; ++pass) {
-          for (int p = gt; p < a.nparts; p += GS) {
-            if (pass > 0 && (p & 1) != pass - 1) continue;
-            for (int m = a.part[p]; m < a.part[p + 1]; ++m) {
-              const int i = man_a[m], j = man_b[m];
-              const int pj = j < 0 ? p : j / PS;
-              if (pass == 0 && pj > p + 1) ++far[p];
-              if ((pass == 0 && pj == p) || (pass > 0 && pj == p + 1)) colour_pair(m, i, j, L.flag, mlo, mhi, man_col, S);
-            }
-          }
-          grid.sync();
-        }
-      }
-      // the pairs between partitions further apart: one thread, canonical order
-      if (gt == 0) {
-        for (int p = 0; p < a.nparts; ++p) {
-          if (far[p] == 0) continue;
-          for (int m = a.part[p]; m < a.part[p + 1]; ++m) {
-            const int i = man_a[m], j = man_b[m];
-            if (j >= 0 && j / PS > p + 1) colour_pair(m, i, j, L.flag, mlo, mhi, man_col, S);
-          }
-        }
+        if (blockIdx.x == 0)
+          for (int p = 0; p < a.nparts; ++p)
+            if (far[p] != 0) walk_pairs(std::false_type{}, p, 2);
       }
       grid.sync();
       // colour-sorted slots (the order inside a colour is free: its pairs share no dynamic body):
@@ -3867,17 +4240,22 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
       }
       grid.sync();
       const int ncol = S[sNcol];
-      if (threadIdx.x < kMaxColours)
-        sh2[threadIdx.x] = sh[threadIdx.x] > 0 ? S[sColOff + threadIdx.x] + atomicAdd(&S[sColCur + threadIdx.x], sh[threadIdx.x])
-                                               : 0;
+      if (threadIdx.x < kMaxColours) {
+        lcount[threadIdx.x] = sh[threadIdx.x];
+        lbase[threadIdx.x] = sh[threadIdx.x] > 0 ? S[sColOff + threadIdx.x] + atomicAdd(&S[sColCur + threadIdx.x], sh[threadIdx.x])
+                                                 : 0;
+      }
       __syncthreads();
       for (int m = cm0 + (int)threadIdx.x; m < cm1; m += kMegaThreads) {
         const int c = man_col[m];
         int slot = -1;
         if (c >= 0) {
-          slot = sh2[c] + man_slot[m];
-          s_a[slot] = man_a[m];
-          s_b[slot] = man_b[m];
+          slot = lbase[c] + man_slot[m];
+          const int i = man_a[m], j = man_b[m];
+          s_a[slot] = i;
+          s_b[slot] = j;
+          if (L.flag[i] & kDynamic) { atomicMin(&wlo[i], blockIdx.x); atomicMax(&whi[i], blockIdx.x); }
+          if (j >= 0 && (L.flag[j] & kDynamic)) { atomicMin(&wlo[j], blockIdx.x); atomicMax(&whi[j], blockIdx.x); }
         }
         man_slot[m] = slot;
       }
@@ -3913,17 +4291,155 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
         }
         if (gt == 0) atomicAdd(&S[sCand], ncand);
       }
+      // the velocities for the sweeps (in place of the cells' records)
+      const SharedVelocities vw(a.cellrec, NB);
+      for (int i = gt; i < NB; i += GS) {
+        cellrec[2 * i] = make_float4(L.v[i], L.v[NB + i], L.v[2 * NB + i], 0.f);
+        cellrec[2 * i + 1] = make_float4(L.w[i], L.w[NB + i], L.w[2 * NB + i], 0.f);
+      }
       grid.sync();
       // ---- 7. PGS sweeps, colour by colour (Sec. "Contact Solver --- Projected Gauss-Seidel") ----
-      for (int it = 0; it < a.iters; ++it) {
-        for (int c = 0; c < ncol; ++c) {
-          const int c1 = S[sColOff + c + 1];
-          for (int slot = S[sColOff + c] + gt; slot < c1; slot += GS)
-            solve_rec(L, a.md + (size_t)slot * kManDevWords, a.mtb + 4 * (size_t)slot, s_a[slot], s_b[slot],
-                      (int)(s_meta[slot] & 15u), a.mu, opts);
-          grid.sync();
+      // A workgroup sweeps the slots of its own run of the canonical list, a colour's slots dealt to its lane
+      // pairs (pair p takes base + p, then every kPairs-th).  A pair keeps its records in LDS, and while its
+      // bodies' other visits are on their way it makes its next one ready in registers (frame, lever arms,
+      // responses, 1 / k: all that does not change during the sweeps).  A body's visits follow each other
+      // by number (SharedVelocities): its colour mask gives their count and this one's rank.  The waves go
+      // on without a barrier, each waiting for what its own pairs need; the first step in the order
+      // (sweep, colour) that is not done can always be taken, so every wait ends.  What bounds it is the
+      // chain of a sweep's colours: the rows of four points (3,000 cycles) and the velocities' way through
+      // memory (2,000).  Disc friction goes to single lanes, colours separated by NeighbourSteps.
+      {
+        int wl = (int)blockIdx.x, wh = wl;
+        for (int m = cm0 + (int)threadIdx.x; m < cm1; m += kMegaThreads) {
+          if (man_slot[m] < 0) continue;
+          const int i = man_a[m], j = man_b[m];
+          if (L.flag[i] & kDynamic) { wl = min(wl, (int)wlo[i]); wh = max(wh, (int)whi[i]); }
+          if (j >= 0 && (L.flag[j] & kDynamic)) { wl = min(wl, (int)wlo[j]); wh = max(wh, (int)whi[j]); }
+        }
+        if (threadIdx.x == 0) { lflag[0] = (int)blockIdx.x; lflag[1] = (int)blockIdx.x; }
+        __syncthreads();
+        atomicMin(&lflag[0], wl);
+        atomicMax(&lflag[1], wh);
+        __syncthreads();
+        steps.lo = lflag[0];
+        steps.hi = lflag[1];
+        const int pr = (int)threadIdx.x >> 1;
+        const bool is_b = (gt & 1) != 0;
+        uint32_t* const lrec = region + (threadIdx.x >> 1);
+        OwnedManifold cur;
+        PairRecord raw;
+        // a visit of the pair: its sweep, its number in the sweep, its colour and (past the records in LDS) its slot
+        struct Visit { int sweep, nth, at, slot; };
+        auto first_from = [&](Visit& v, int c) {
+          while (c < ncol && pr >= lcount[c]) ++c;
+          v.at = c;
+          v.slot = c < ncol ? lbase[c] + pr : 0;
+        };
+        auto advance = [&](Visit& v) {
+          ++v.nth;
+          if (v.slot + kPairs < lbase[v.at] + lcount[v.at]) v.slot += kPairs;
+          else first_from(v, v.at + 1);
+        };
+        auto record = [&](const Visit& v) { return v.nth < kLdsVisits ? lrec + v.nth * kRecWords * kPairs : nullptr; };
+        // the records into LDS; the visits of a sweep
+        int total = 0;
+        Visit first = {0, 0, ncol, 0}, over = first;
+        if (!opts.cone) {
+          Visit v = first;
+          for (first_from(v, 0); v.at < ncol; advance(v), ++total) {
+            if (v.nth == 0) first = v;
+            if (v.nth == kLdsVisits) over = v;
+            uint32_t* const l = record(v);
+            if (!l) continue;
+            const uint32_t* const rec = reinterpret_cast<const uint32_t*>(a.md + (size_t)v.slot * kManDevWords);
+            for (int k = (gt & 1); k < 27; k += 2) l[k * kPairs] = rec[k];
+            if (is_b) {
+              l[27 * kPairs] = (uint32_t)s_a[v.slot];
+              l[28 * kPairs] = (uint32_t)s_b[v.slot];
+              l[29 * kPairs] = (s_meta[v.slot] & 15u) | ((uint32_t)v.at << 4);
+              l[30 * kPairs] = (uint32_t)v.slot;
+            }
+          }
+        }
+        wave_sync();   // (a pair's lanes are in one wave)
+        auto next = [&](Visit v) {
+          if (v.nth + 1 == total) { v.nth = -1; ++v.sweep; }
+          if (v.nth + 1 < kLdsVisits) {
+            ++v.nth;
+            v.at = (int)(record(v)[29 * kPairs] >> 4);
+          } else if (v.nth + 1 == kLdsVisits) {
+            v = {v.sweep, over.nth, over.at, over.slot};
+          } else {
+            advance(v);
+          }
+          return v;
+        };
+        auto read = [&](const Visit& v) {
+          const uint32_t* const l = record(v);
+          int ia = 0, ib = 0, np = 0;
+          if (!l) { ia = s_a[v.slot]; ib = s_b[v.slot]; np = (int)(s_meta[v.slot] & 15u); }
+          const int slot = l ? (int)l[30 * kPairs] : v.slot;
+          read_pair(L, mlo, mhi, l, a.md + (size_t)slot * kManDevWords, a.mtb + 4 * (size_t)slot, ia, ib, np, opts.bias, is_b,
+                    raw);
+        };
+        bool dynamic = false;   // of the visit in `cur`: this lane's body's visits before it
+        uint32_t visit = 0u;
+        auto prepare = [&](const Visit& v) {
+          prepare_pair(raw, record(v), a.md + (size_t)v.slot * kManDevWords, is_b, a.mu, cur);
+          dynamic = cur.body >= 0 && (raw.flag & kDynamic);
+          const uint64_t mask = (uint64_t)raw.mlo | ((uint64_t)raw.mhi << 32);
+          visit = (uint32_t)v.sweep * (uint32_t)__popcll(mask) + (uint32_t)__popcll(mask & ((1ull << v.at) - 1));
+        };
+        Visit now = first;
+        if (total > 0) { read(now); prepare(now); }
+        for (int it = 0; it < a.iters; ++it) {
+          for (int c = 0; c < ncol; ++c) {
+            while (total > 0 && now.at == c && now.sweep == it) {
+              const Visit then = next(now);
+              read(then);
+              solve_prepared(vw, cur, dynamic, visit, opts);
+              if (!is_b) {
+                if (uint32_t* const l = record(now)) {
+#pragma unroll
+                  for (int k = 0; k < 12; ++k) l[(12 + k) * kPairs] = __float_as_uint(cur.lam[k]);
+                } else {
+                  float4* w4 = reinterpret_cast<float4*>(a.md + (size_t)now.slot * kManDevWords);
+#pragma unroll
+                  for (int k = 0; k < 3; ++k)
+                    w4[3 + k] = make_float4(cur.lam[4 * k], cur.lam[4 * k + 1], cur.lam[4 * k + 2], cur.lam[4 * k + 3]);
+                }
+              }
+              wave_sync();
+              now = then;
+              prepare(now);
+            }
+            if (opts.cone) {
+              for (int m = lbase[c] + (int)threadIdx.x; m < lbase[c] + lcount[c]; m += kMegaThreads)
+                solve_rec(L, vw, a.md + (size_t)m * kManDevWords, a.mtb + 4 * (size_t)m, s_a[m], s_b[m], (int)(s_meta[m] & 15u),
+                          a.mu, opts);
+              steps.post();
+              steps.wait();
+            }
+          }
+        }
+        // the impulses and the velocities back to where the rest of the step reads them
+        if (total > 0) {
+          for (Visit v = first; v.at < ncol; advance(v)) {
+            const uint32_t* const l = record(v);
+            if (!l) break;
+            uint32_t* const rec = reinterpret_cast<uint32_t*>(a.md + (size_t)v.slot * kManDevWords);
+            for (int k = (gt & 1); k < 12; k += 2) rec[12 + k] = l[(12 + k) * kPairs];
+          }
+        }
+        grid.sync();   // (a workgroup has waited for its neighbours only)
+        for (int i = gt; i < NB; i += GS) {
+          float v[3], w[3];
+          vw.load(i, 0u, v, w);
+          store3(L.v, NB, i, v);
+          store3(L.w, NB, i, w);
         }
       }
+      grid.sync();
       // ---- contacts of the launch's last step (canonical order) ----
       if (last) {
         for (int m = gt; m < nman; m += GS) {
@@ -4019,13 +4535,14 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
       grid.sync();
       // ---- 10. Baumgarte position correction (Eq. (baumgarte)), colour by colour ----
       for (int c = 0; c < ncol; ++c) {
-        const int c1 = S[sColOff + c + 1];
-        for (int slot = S[sColOff + c] + gt; slot < c1; slot += GS) {
+        for (int slot = lbase[c] + (int)threadIdx.x; slot < lbase[c] + lcount[c]; slot += kMegaThreads) {
           const int j = s_b[slot];
-          baumgarte_pair(L, s_a[slot], j < 0 ? 0 : j, j < 0, a.md + (size_t)slot * kManDevWords, a.beta, a.slop);
+          baumgarte_pair<true>(L, s_a[slot], j < 0 ? 0 : j, j < 0, a.md + (size_t)slot * kManDevWords, a.beta, a.slop);
         }
-        grid.sync();
+        steps.post();
+        steps.wait();
       }
+      grid.sync();
     }
     // ---- withdrawal of pushed bodies at the end of the step ----
     if (!S[sFrozen]) {
@@ -4118,7 +4635,8 @@ int ensure_lds_limit() {
   if (dev < 0 || dev >= kMaxDevices) return (int)hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(attr_mutex);
   if (!attr_set[dev]) {
-    const void* variants[11] = {step_variant_pack(false),          step_variant_pack(true),
+    const void* variants[12] = {(const void*)mega_kernel,
+                                step_variant_pack(false),          step_variant_pack(true),
                                 step_variant_lat(false),           step_variant_lat(true),
                                 step_variant_island(false, false), step_variant_island(false, true),
                                 step_variant_island(true, false),  step_variant_island(true, true),
@@ -4171,24 +4689,27 @@ int launch_step(const StepArgs& a, size_t lds_bytes, void* stream) {
 namespace jg {
 
 int mega_blocks(int bodies, int* blocks) {
+  if (int r = ensure_lds_limit()) return r;
   int dev = 0, cus = 0, per = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, mega_kernel, kMegaThreads, 0);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, mega_kernel, kMegaThreads, kMegaLdsBytes);
   if (e != hipSuccess) return (int)e;
-  const int most = std::max(1, std::min(per, 2)) * std::max(1, cus);
-  // a grid-wide barrier costs about 0.1 us per workgroup (their arrivals are serialised), a colour
-  // of the sweeps about 1.4 us per round of visits: about one workgroup per 3,072 bodies keeps
-  // a colour (about a quarter of the bodies in pairs) to a few rounds
-  *blocks = std::min(most, std::max(4, (bodies + 3071) / 3072));
+  const int most = std::max(1, per) * std::max(1, cus);
+  // Bodies per workgroup: the chain of the sweeps is shorter the fewer visits a wave has in a colour, and a
+  // barrier costs the more the larger the grid.  A 19,200-stone wall takes 2.70 M cycles a step at 75
+  // (256 workgroups), 2.47 M at 128, 2.69 M at 200 and 3.07 M at 280.
+  constexpr int kBodies = 128;
+  *blocks = std::min(most, std::max(4, (bodies + kBodies - 1) / kBodies));
   return 0;
 }
 
 int launch_mega(const MegaArgs& a, int blocks, void* stream) {
+  if (int e = ensure_lds_limit()) return e;
   MegaArgs args = a;
   void* params[] = {(void*)&args};
-  return (int)hipLaunchCooperativeKernel((const void*)mega_kernel, dim3((unsigned)blocks), dim3(kMegaThreads), params, 0,
-                                         (hipStream_t)stream);
+  return (int)hipLaunchCooperativeKernel((const void*)mega_kernel, dim3((unsigned)blocks), dim3(kMegaThreads), params,
+                                         kMegaLdsBytes, (hipStream_t)stream);
 }
 
 }  // namespace jg

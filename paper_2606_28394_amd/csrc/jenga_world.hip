@@ -163,13 +163,13 @@ struct jg_world {
   struct Mega {
     int tower = -1, g0 = 0, nb = 0, tslot = 0, p0 = 0, np = 0;
     int ncell_cap = 0, cand_cap = 0, nparts = 0, grid = 0;
-    DevBuf<float> body, md, red, out_geo, out_pts;
-    DevBuf<uint32_t> ubody, cand, out_meta, err;
+    DevBuf<float> body, cellrec, md, red, out_geo, out_pts;
+    DevBuf<uint32_t> ubody, cand, out_meta, err, bar;
     DevBuf<int32_t> cells, man, part, ired, scal, out_a, out_b, out_count;
     hipError_t release() {
       hipError_t first = hipSuccess;
-      for (hipError_t e : {body.release(), md.release(), red.release(), out_geo.release(), out_pts.release(),
-                           ubody.release(), cand.release(), out_meta.release(), err.release(), cells.release(),
+      for (hipError_t e : {body.release(), cellrec.release(), md.release(), red.release(), out_geo.release(), out_pts.release(),
+                           ubody.release(), cand.release(), out_meta.release(), err.release(), bar.release(), cells.release(),
                            man.release(), part.release(), ired.release(), scal.release(), out_a.release(),
                            out_b.release(), out_count.release()})
         if (first == hipSuccess) first = e;
@@ -544,6 +544,7 @@ int32_t build_layout(jg_world* w) {
       m.nparts = (int)((nb + (size_t)w->prm.colour_partition - 1) / (size_t)w->prm.colour_partition);
       const size_t C = (size_t)m.cand_cap;
       HIP_TRY(m.body.ensure(jg::kMegaBodyWords * nb));
+      HIP_TRY(m.cellrec.ensure(8 * nb));
       HIP_TRY(m.ubody.ensure(jg::kMegaBodyU32 * nb));
       HIP_TRY(m.cells.ensure(2 * ((size_t)m.ncell_cap + 1)));
       HIP_TRY(m.cand.ensure(3 * C));
@@ -560,8 +561,10 @@ int32_t build_layout(jg_world* w) {
       HIP_TRY(m.out_pts.ensure(24 * C));
       HIP_TRY(m.out_count.ensure(1));
       HIP_TRY(m.err.ensure(1));
+      HIP_TRY(m.bar.ensure(jg::kMegaBarWords + G));
       HIP_TRY(hipMemsetAsync(m.out_count.p, 0, sizeof(int32_t), w->stream));
       HIP_TRY(hipMemsetAsync(m.err.p, 0, sizeof(uint32_t), w->stream));
+      HIP_TRY(hipMemsetAsync(m.bar.p, 0, sizeof(uint32_t) * jg::kMegaBarWords, w->stream));
     }
   }
   w->layout_dirty = false;
@@ -1114,9 +1117,11 @@ int32_t jg_step_batch(jg_world* w, int32_t n_steps) {
     g.partition = w->prm.colour_partition;
     g.step0 = w->step;
     g.body = m.body.p; g.ubody = m.ubody.p; g.cells = m.cells.p; g.ncell_cap = m.ncell_cap;
+    g.cellrec = m.cellrec.p;
     g.cand = m.cand.p; g.cand_cap = m.cand_cap; g.man = m.man.p; g.md = m.md.p;
     g.mtb = m.md.p + (size_t)jg::kManDevWords * m.cand_cap;
     g.part = m.part.p; g.nparts = m.nparts; g.red = m.red.p; g.ired = m.ired.p; g.scal = m.scal.p;
+    g.bar = m.bar.p;
     g.out_a = m.out_a.p; g.out_b = m.out_b.p; g.out_meta = m.out_meta.p; g.out_geo = m.out_geo.p;
     g.out_pts = m.out_pts.p; g.out_count = m.out_count.p;
     if (int e = jg::launch_mega(g, m.grid, w->stream))

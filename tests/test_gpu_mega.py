@@ -6,7 +6,8 @@ grid-wide kernel against the oracle, which colours such towers with the same par
   impulses on the first step, velocities at the walls' 1e-3 after it);
 - one partition: the colouring is the canonical greedy one, so the grid-wide kernel must give
   what the island path (one workgroup, device memory) gives, to a few FP32 roundings;
-- a site-scale wall of 100,000 stones (100 courses x 1,000): one step against the oracle.
+- a site-scale wall of 100,000 stones (100 courses x 1,000): one step against the oracle;
+- small scenes for the kernel's other branches: one step against the oracle.
 """
 import os
 import sys
@@ -107,3 +108,35 @@ def test_site_scale_wall_matches_oracle(J, oracle):
     assert int(sc["tower_ptr"][-1]) == 100_000
     ow = oracle.OracleWorld(sc)
     _compare(J, oracle, sc, [(ow.x.copy(), ow.q.copy(), ow.v.copy(), ow.w.copy())], "wall 100x1000")
+
+
+def _crowded_slab(**params):
+    """A slab with 49 boxes on it: 50 colours, a body with 49 near boxes, and a lane pair with more
+    visits in a sweep than it has records in LDS."""
+    n = 7
+    he = [[2.0, 2.0, 0.1]] + [[0.1, 0.1, 0.1]] * (n * n)
+    mass = [900.0] + [4.0] * (n * n)
+    pos = [[0.0, 0.0, 0.1 - 1e-4]]
+    pos += [[0.5 * (i - 3), 0.5 * (j - 3), 0.3 - 2e-4] for i in range(n) for j in range(n)]
+    vel = np.zeros((n * n + 1, 3))
+    vel[0, 0] = 0.2
+    sb = W.SceneBuilder(dict(W.default_params(), **params), n_steps=4)
+    sb.add_tower(np.array(he), np.array(mass), np.array(pos), np.tile([1.0, 0.0, 0.0, 0.0], (n * n + 1, 1)), 0.5, vel,
+                 np.zeros((n * n + 1, 3)))
+    return sb.build()
+
+
+@pytest.mark.parametrize("label,courses,per_course,params", [
+    ("crowded slab", 0, 0, {}),
+    ("two stones", 1, 2, {}),
+    ("pairs between partitions far apart", 10, 48, dict(colour_partition=16)),
+    ("partitions too large for LDS", 48, 48, dict(colour_partition=2100)),
+    ("more near boxes than a walk keeps", 8, 16, dict(margin=0.5, mega_cand_per_body=120.0)),
+    ("disc friction", 8, 16, dict(friction_cone=1, colour_partition=32)),
+    ("restitution targets", 8, 16, dict(restitution=0.3, restitution_bias=1, colour_partition=32)),
+])
+def test_grid_wide_edges_match_oracle(J, oracle, label, courses, per_course, params):
+    """The kernel's branches at small sizes, one step against the oracle (the bounds of the walls)."""
+    sc = _wall(courses, per_course, mega_bodies=1, **params) if courses else _crowded_slab(mega_bodies=1)
+    ow = oracle.OracleWorld(sc)
+    _compare(J, oracle, sc, [(ow.x.copy(), ow.q.copy(), ow.v.copy(), ow.w.copy())], label)
