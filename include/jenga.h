@@ -137,10 +137,10 @@ typedef struct {
                             at the first body whose candidates do not fit, JG_ERR_CANDIDATES); 16 */
   int32_t small_batch;   /* 0: a batch with at most two towers per CU, stepped with the zero or the
                             previous-step start and no feature records, gets one workgroup of four
-                            waves per tower: the first steps it, all four build its manifolds, solve
-                            it (each lane pair keeping one manifold's row terms in registers for the
-                            whole solve) and sum its residual; the results are bit for bit those of
-                            one wave per tower; -1: never; default 0 */
+                            waves per tower (of eight with at most one tower per CU), which share
+                            every phase of its step; in the sweeps each lane pair keeps two
+                            manifolds' row terms in registers; the results are bit for bit those
+                            of one wave per tower; -1: never; default 0 */
   int32_t precision;     /* arithmetic of the step kernels: JG_FP32 (the only one built; default).
                             JG_FP64 makes jg_create_world return JG_EINVAL: an FP64 instantiation
                             would double every kernel's LDS and registers, and is not built */

@@ -50,7 +50,8 @@ struct StepArgs {
   float* gmem;                 // per-pack regions: the contact points' lever arms and impulses
                                // (kManDevWords per manifold slot), their restitution targets
                                // (kManBiasWords per slot), the narrowphase's normals and
-                               // depths (kManSatWords per slot), then, for a pack whose layout
+                               // depths (kManSatWords per slot), the pairs (kManPairWords per slot), a
+                               // one-wave pack's canonical list (kManListWords per slot), then, for a pack whose layout
                                // lives in device memory, the whole layout
   int32_t in_gmem;             // 1: this launch's packs keep their whole layout in gmem
   int32_t hot_bodies;          // in_gmem packs: 1 = the arrays of the serial walks also in LDS
@@ -106,6 +107,7 @@ struct StepArgs {
   int64_t step0;
   // capacities of this launch (LDS layout)
   int32_t lat;     // small batches: threads of the workgroup that steps one tower (0: not one)
+  int32_t many;    // one-wave packs: more than two to a SIMD of the GPU
   int32_t nbp;     // bodies per pack
   int32_t pc;      // manifolds per pack
   int32_t tpc;     // towers per pack
@@ -113,16 +115,21 @@ struct StepArgs {
 };
 
 constexpr int kBodyWords = 28;     // x3 q4 v3 w3 he3 invm flag tower Iw6 aabb/mask3
+constexpr int kListBodyWords = 2;  // colouring lane masks of their own (a one-wave pack: 1, the other is mask3's)
 constexpr int kTowerWords = 14;    // body range, mu, counters4, residual2, canonical range2, points, frozen
 constexpr int kPushWords = 10;
-constexpr int kManWords = 4;       // canonical (code, pos) + sorted (code, meta)
+constexpr int kManWords = 2;       // canonical pair (code, pos): in LDS where a workgroup has one tower; a
+                                   // one-wave pack keeps them in its device region
 constexpr int kManDevWords = 28;   // r_A 12, lambda 12, n 3, depth per sorted manifold, in the
                                    // pack's device region
+constexpr int kManPairWords = 4;   // its pair, points and slots, mu (one unused), beside the records: as part of
+                                   // them (a stride of 128 bytes) a 4,096-stone wall's step took 12 % longer
 constexpr int kManBiasWords = 4;   // restitution targets of a sorted manifold's points (after all
                                    // of the pack's records; used with restitution_bias only)
 constexpr int kManSatWords = 4;    // the narrowphase's normal and depth of a canonical colliding
                                    // pair (after the targets), reused to build its manifold
-constexpr int kManPackWords = kManDevWords + kManBiasWords + kManSatWords;   // per slot of a pack
+constexpr int kManListWords = 4;   // a one-wave pack's canonical pairs (kManWords; a multiple of 16 bytes)
+constexpr int kManPackWords = kManDevWords + kManBiasWords + kManSatWords + kManPairWords + kManListWords;   // per slot of a pack
 constexpr int kWarmWords = 18;     // sorted -> canonical map + previous step store (17)
 constexpr int kStageWords = 64 * 16 + 64 * 3;   // network input rows of one 64-point chunk (bf16)
 constexpr int kLearnedIslandWaves = 4;          // waves of a pack in device memory with the network
@@ -164,21 +171,30 @@ __host__ __device__ inline int64_t hot_words(int nbp, int tpc, int ppc, bool bod
 // LDS layout modes: 0 plain; 1 previous-step store (warm start from the previous step, or
 // feature records); 2 learned warm start: the store plus network input staging, saved
 // velocities (6 per body), residual partials (2 per manifold), fallback state (3 per tower).
-inline int64_t lds_words(int nbp, int pc, int tpc, int ppc, int mode) {
+// lists: the canonical pairs, both lane masks, the whole store and the learned start's terms are part of the
+// layout (small batches, islands); a one-wave pack has the sorted pairs' words on chip instead where the
+// network's registers leave LDS over (pairs_on_chip)
+inline bool pairs_on_chip(int mode, bool features) { return mode == 2 || features; }
+inline int64_t lds_words(int nbp, int pc, int tpc, int ppc, int mode, bool lists, bool pairs) {
   int64_t w = 0;
-  w += (int64_t)nbp * kBodyWords;
+  w += (int64_t)nbp * (kBodyWords + (lists ? kListBodyWords : 1));
   w += (int64_t)tpc * kTowerWords;
   w += (int64_t)ppc * kPushWords;
   w += 2 * (kMaxColours + 1) + 16 + kRing + 2 * kPhases;
-  w += (int64_t)pc * kManWords;
-  if (mode >= 1) w += (int64_t)pc * kWarmWords;
-  if (mode == 2) w += kStageWords + 6 * (int64_t)nbp + 2 * (int64_t)pc + 3 * (int64_t)tpc;
+  if (lists) w += (int64_t)pc * kManWords;
+  if (mode >= 1) w += lists ? (int64_t)pc * kWarmWords : pc;
+  if (mode == 2) w += kStageWords + 3 * (int64_t)tpc + (lists ? 6 * (int64_t)nbp + 2 * (int64_t)pc : 0);
+  if (pairs && !lists) w += (int64_t)kManPairWords * pc + 3;
   return w;
+}
+// what a one-wave pack keeps in its device block instead (after kManPackWords per slot)
+inline int64_t pack_store_words(int nbp, int pc, int mode) {
+  return (mode >= 1 ? (int64_t)pc * (kWarmWords - 1) : 0) + (mode == 2 ? 6 * (int64_t)nbp + 2 * (int64_t)pc : 0);
 }
 
 // the step kernel's variants (each defined by the build part that compiles it): packs on chip, small
 // batches, islands in device memory (hot: the walks' body arrays in LDS), and with the network
-const void* step_variant_pack(bool ext);
+const void* step_variant_pack(bool ext, bool many);
 const void* step_variant_lat(bool ext);
 const void* step_variant_island(bool hot, bool ext);
 const void* step_variant_learned_pack();
@@ -186,8 +202,8 @@ const void* step_variant_learned_island();
 const void* step_variant_learned_island_hot();
 
 // a small batch's workgroups also have (from the next multiple of four words on) a region for their
-// waves' candidate rings, the colouring's lists (kLatBodyWords words per body), the waves' colour counts
-// and the bodies' velocities during the sweeps, one after the other; each wave leaves its narrowphase's
+// waves' candidate rings, the waves' colour counts and the bodies' velocities (kLatBodyWords words per body)
+// during the sweeps, one after the other; each wave leaves its narrowphase's
 // colliding pairs (code, normal and depth) in a list of the pack's device block
 constexpr int kLatBodyWords = 8;
 __host__ __device__ inline int lat_shared_words(int nbp, int threads) {

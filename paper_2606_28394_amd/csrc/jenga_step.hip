@@ -1,10 +1,10 @@
 // Batched block stepping on gfx950: one workgroup (one 64-lane wave) owns a
-// "pack" of whole towers for every step of a launch.  Bodies, contact pairs and
-// colours stay in LDS; each contact manifold's lever arms, impulses, normal and
-// depth live in a per-pack block of device memory, read on every PGS visit with
-// the next manifold's record in flight while the current one is solved (this
-// keeps LDS per body small, so more waves share a CU).  The step is bound by
-// the vector ALUs.  A colour with at most half as many manifolds as threads is
+// "pack" of whole towers for every step of a launch.  Bodies and colours' masks
+// stay in LDS; the contact pairs, and each contact manifold's lever arms,
+// impulses, normal and depth, live in a per-pack block of device memory, read on
+// every PGS visit with the next manifold's record in flight while the current one
+// is solved (this keeps LDS per body small, so more waves share a CU: two or three
+// to a SIMD).  The step is bound by the vector ALUs.  A colour with at most half as many manifolds as threads is
 // solved by lane pairs, one body per lane (see pgs_sweeps).  An island too large
 // for LDS keeps its layout in device memory, one island per workgroup of eight
 // waves (see step_kernel).
@@ -52,17 +52,15 @@ constexpr uint32_t kGround = 0xffffu;
 constexpr int kIslandWaves = 8;   // waves of a workgroup that steps an island in device memory
 constexpr int kLatencyWaves = 8;  // most waves of a workgroup that steps one tower of a small batch
 
-// A barrier among the lanes of one wave.  Every phase runs on one wave (the workgroup's first),
-// so this is all its steps need: LDS and device-memory accesses of one wave are performed in
-// order.  Only the PGS sweeps of an island in device memory use the whole workgroup and its
-// barrier (__syncthreads).
+// A barrier among the lanes of one wave, all that a pack's steps need: LDS and device-memory
+// accesses of one wave are performed in order.  An island's and a small batch's waves share their
+// phases, with the workgroup's barrier (__syncthreads) between them.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 constexpr int kWindows = 4;      // broadphase register windows: packs of up to 256 bodies
-constexpr int kLatList = 8;      // entries of a body's colouring list in a small batch (in Lds::vw)
 constexpr uint32_t kErrCand = 1u, kErrMan = 2u, kErrCol = 4u, kErrNan = 8u;
 
 struct Lds {
@@ -89,9 +87,9 @@ struct Lds {
   uint32_t* cab;
   int32_t* cpos;
   // colour-sorted manifolds
-  uint32_t *mab, *mmeta;
   uint32_t *lmlo, *lmhi;   // colouring: per-body lane masks of the current chunk (low, high lanes)
   float* mtb;         // device block after the records: restitution targets, 4 per sorted manifold
+  uint32_t* mpair;    // device block, kManPairWords per sorted manifold: A << 16 | B, points and slots, mu
   float* md;          // device block, kManDevWords per sorted manifold: r_A [12] (contact frame
                       // (n, t1, t2)), lambda [12], n [3], depth (see mdev)
   float* msat;        // device block after the targets: the narrowphase's normal [3] and depth of
@@ -120,6 +118,10 @@ struct Lds {
 // the device-block record of sorted manifold m (16-byte aligned: kManDevWords is a multiple of 4)
 __device__ __forceinline__ float* mdev(const Lds& L, int m) { return L.md + (size_t)m * kManDevWords; }
 
+// its pair (A << 16 | B), and its points' count and vertex slots
+__device__ __forceinline__ uint32_t man_pair(const Lds& L, int m) { return L.mpair[kManPairWords * m]; }
+__device__ __forceinline__ uint32_t man_meta(const Lds& L, int m) { return L.mpair[kManPairWords * m + 1]; }
+
 // LDS layout mode of a launch (see lds_words)
 __device__ __forceinline__ int lds_mode(const StepArgs& a) {
   return a.warm_start == 2 ? 2 : ((a.warm_start == 1 || a.feat_out) ? 1 : 0);
@@ -129,8 +131,8 @@ __device__ __forceinline__ int lds_mode(const StepArgs& a) {
 // lever arms and impulses in device memory; with use_hot (packs kept in device memory), hot is
 // LDS for the small arrays listed in hot_words, and with hot_bodies for the walks' body arrays.
 // The flags are compile-time constants at the call, so every array has one address space.
-__device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool use_hot, bool hot_bodies,
-                                     const StepArgs& a) {
+__device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool use_hot, bool hot_bodies, bool lists,
+                                     bool far_store, bool pairs_on_chip, const StepArgs& a) {
   Lds L;
   L.nbp = a.nbp;
   L.pc = a.pc;
@@ -155,31 +157,50 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
   L.coloff = (int32_t*)take(kMaxColours + 1); L.colcnt = (int32_t*)take(kMaxColours + 1);
   L.scal = (int32_t*)take(16);
   L.ring = (uint32_t*)take(kRing);
-  L.cab = (uint32_t*)take(pc); L.cpos = (int32_t*)take(pc);
-  L.mab = (uint32_t*)take(pc); L.mmeta = (uint32_t*)take(pc);
   L.md = dev;
   L.mtb = dev + (size_t)kManDevWords * pc;
   L.msat = dev + (size_t)(kManDevWords + kManBiasWords) * pc;
-  if (mode >= 1) {
-    L.mcanon = (int32_t*)take(pc);
-    L.pkey = (uint32_t*)take(pc); L.pslot = (uint32_t*)take(pc); L.pnrm = take(3 * pc); L.plam = take(12 * pc);
+  L.mpair = (uint32_t*)(dev + (size_t)(kManDevWords + kManBiasWords + kManSatWords) * pc);
+  // The colouring's lane masks, and the canonical pairs.  A one-wave pack keeps the pairs in device memory
+  // (they are read in order, ahead of their use): with them and the sorted pairs' words in LDS a body
+  // took 42 words and a pack of 20 KB held 111 bodies, two thirds of the lanes of a colour's visits.
+  if (lists) {
+    L.cab = (uint32_t*)take(pc); L.cpos = (int32_t*)take(pc);
+    L.lmlo = (uint32_t*)take(nb); L.lmhi = (uint32_t*)take(nb);
   } else {
-    L.mcanon = nullptr;
-    L.pkey = L.pslot = nullptr;
-    L.pnrm = L.plam = nullptr;
+    L.cab = L.mpair + (size_t)kManPairWords * pc; L.cpos = (int32_t*)L.cab + pc;
+    L.lmlo = (uint32_t*)L.hm + 2 * nb; L.lmhi = (uint32_t*)take(nb);   // (the colour masks are hm's first two planes)
+  }
+  // The previous step's store, and the learned start's terms: a one-wave pack has only the keys, which are
+  // searched, on chip; the rest is in its device block, or (far_store) used where it lies between launches
+  // (sixteen words per pair: normal, points and slots, impulses).  All of it in LDS was 18 words per pair: four packs of 54
+  // bodies to a CU, and two rounds of them for 1,500 towers (4.85 ms for four steps, now 2.71).
+  float* far = dev + (size_t)kManPackWords * pc;
+  auto store = [&](int n) { float*& from = lists ? p : far; float* r = from; from += n; return r; };
+  L.mcanon = nullptr;
+  L.pkey = L.pslot = nullptr;
+  L.pnrm = L.plam = nullptr;
+  if (mode >= 1) {
+    L.pkey = (uint32_t*)take(pc);
+    L.mcanon = (int32_t*)store(pc);
+    if (!far_store) { L.pslot = (uint32_t*)store(pc); L.pnrm = store(3 * pc); L.plam = store(12 * pc); }
   }
   if (mode == 2) {
-    L.vsave = take(6 * nb); L.rpart = take(2 * pc);
+    L.vsave = store(6 * nb); L.rpart = store(2 * pc);
     L.tfb = (uint32_t*)take(nt); L.tfc = (uint32_t*)take(2 * nt);
   } else {
     L.vsave = L.rpart = nullptr;
     L.tfb = L.tfc = nullptr;
   }
+  if (pairs_on_chip) {
+    p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses
+    L.mpair = (uint32_t*)take(kManPairWords * pc);
+  }
   L.vw = nullptr;
   L.wcol = L.seg = nullptr;
   if (a.lat) {
     p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses
-    // the waves' candidate rings, then the colouring's lists, then the waves' colour counts, then the
+    // the waves' candidate rings, then the waves' colour counts, then the
     // sweeps' velocities share one region; the list starts take the pack's own ring
     L.vw = take(lat_shared_words(nb, a.lat));
     L.seg = (int32_t*)L.ring;
@@ -194,10 +215,6 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
     p = base + ((p - base + 3) & ~(ptrdiff_t)3);   // 16-byte accesses (the region's base is aligned)
     L.csat = take(4 * kCandPerBody * nb);
   }
-  // the colouring's lane masks reuse the sorted-manifold words (free until the manifolds are
-  // written)
-  L.lmlo = L.mab;
-  L.lmhi = L.mmeta;
   if (use_hot) {
     // a pack in device memory keeps its small arrays, and if they fit the arrays its serial
     // walks read, in LDS (the copies in its region stay unused)
@@ -860,7 +877,7 @@ __device__ __forceinline__ void manifold_open(const Lds& L, uint32_t ab, const f
 __device__ __forceinline__ void manifold_open(const Lds& L, int m, int& a, int& b, Frame& F, LBody& A, LBody& B,
                                               float dAB[3]) {
   const float n[3] = {mdev(L, m)[24], mdev(L, m)[25], mdev(L, m)[26]};
-  manifold_open(L, L.mab[m], n, a, b, F, A, B, dAB);
+  manifold_open(L, man_pair(L, m), n, a, b, F, A, B, dAB);
 }
 
 __device__ __forceinline__ void load_point(const Lds& L, int m, int j, const float dAB[3], float rA[3], float rB[3],
@@ -1086,9 +1103,10 @@ struct ManPoints {
 };
 
 __device__ __forceinline__ void fetch_points(const Lds& L, int m, ManPoints& d, bool bias) {
-  d.ab = L.mab[m];
-  d.np = (int)(L.mmeta[m] & 15u);
-  d.mu = L.mu[L.tw[d.ab >> 16]];
+  const uint4 pm = reinterpret_cast<const uint4*>(L.mpair)[m];
+  d.ab = pm.x;
+  d.np = (int)(pm.y & 15u);
+  d.mu = __uint_as_float(pm.z);
   // the whole record in seven 16-byte loads (slots past the manifold's points come along unused)
   const float4* rec = reinterpret_cast<const float4*>(mdev(L, m));
 #pragma unroll
@@ -1422,7 +1440,7 @@ __device__ __forceinline__ void warm_apply_manifold(const Lds& L, int m) {
   LBody A, B;
   float dAB[3];
   manifold_open(L, m, a, b, F, A, B, dAB);
-  const int np = (int)(L.mmeta[m] & 15u);
+  const int np = (int)(man_meta(L, m) & 15u);
   for (int j = 0; j < np; ++j) {
     float rA[3], rB[3], lam[3];
     load_point(L, m, j, dAB, rA, rB, lam);
@@ -1505,9 +1523,9 @@ __device__ __forceinline__ void residual_rec(const Lds& L, const float* rec, con
 // natural-map residual of one manifold: sum of squares and max |r| over its rows
 __device__ __forceinline__ void residual_manifold(const Lds& L, int m, float mu, const SolveOpts& o, float& sum,
                                                   float& mx) {
-  const uint32_t ab = L.mab[m];
+  const uint32_t ab = man_pair(L, m);
   const int b = (int)(ab & 0xffffu);
-  residual_rec(L, mdev(L, m), L.mtb + 4 * (size_t)m, (int)(ab >> 16), b, b == (int)kGround, (int)(L.mmeta[m] & 15u),
+  residual_rec(L, mdev(L, m), L.mtb + 4 * (size_t)m, (int)(ab >> 16), b, b == (int)kGround, (int)(man_meta(L, m) & 15u),
                mu, o, sum, mx);
 }
 
@@ -1521,7 +1539,7 @@ __device__ __forceinline__ void residual_manifold(const Lds& L, int m, float mu,
 // body at (x_A, y_A, 0) with the identity orientation.
 __device__ __forceinline__ void point_features(const Lds& L, int m, int j, float gdt, float f[mlp::kFeat]) {
   const int nb = L.nbp;
-  const uint32_t ab = L.mab[m];
+  const uint32_t ab = man_pair(L, m);
   const int ia = (int)(ab >> 16), ib = (int)(ab & 0xffffu);
   const bool ground = ib == (int)kGround;
   const float n[3] = {mdev(L, m)[24], mdev(L, m)[25], mdev(L, m)[26]};
@@ -1587,7 +1605,7 @@ __device__ __forceinline__ void learned_apply_manifold(const Lds& L, int m, floa
   LBody A, B;
   float dAB[3];
   manifold_open(L, m, a, b, F, A, B, dAB);
-  const int np = (int)(L.mmeta[m] & 15u);
+  const int np = (int)(man_meta(L, m) & 15u);
   for (int j = 0; j < np; ++j) {
     float rA[3], rB[3], y[3];
     load_point(L, m, j, dAB, rA, rB, y);
@@ -1624,7 +1642,7 @@ __device__ __forceinline__ void record_solution(const Lds& L, int m, float* rec)
   LBody A, B;
   float dAB[3];
   manifold_open(L, m, a, b, F, A, B, dAB);
-  const int np = (int)(L.mmeta[m] & 15u);
+  const int np = (int)(man_meta(L, m) & 15u);
   for (int j = 0; j < np; ++j) {
     float rA[3], rB[3], lam[3];
     load_point(L, m, j, dAB, rA, rB, lam);
@@ -1652,7 +1670,7 @@ __device__ __forceinline__ void residual_parts(const Lds& L, int nman, int first
     const int m = L.cpos[p];
     float sum = 0.f, mx = 0.f;
     if (m >= 0) {
-      const int t = L.tw[L.mab[m] >> 16];
+      const int t = L.tw[man_pair(L, m) >> 16];
       if (!only || only[t]) residual_manifold(L, m, L.mu[t], o, sum, mx);
     }
     psum[p] = sum;
@@ -1828,15 +1846,23 @@ __device__ __forceinline__ int sat_slot(const Lds& L, int nw, int p) {
   return start[w] + (p - pre[w]);
 }
 
-template <bool kExt>
+// kFar: the previous step's store lies in prev_data from slot `slot0` on (one-wave packs)
+template <bool kExt, bool kFar>
 __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a, const float* sat, int nw, int first,
-                                                int stride, int nman, bool keep_prev) {
+                                                int stride, int nman, bool keep_prev, int slot0) {
   const int PC = L.pc;
   const int nprev = L.scal[4];
+  // (the next pair's words are read while this one is worked)
+  int sidx_next = first < nman ? L.cpos[first] : -1;
+  uint32_t code_next = first < nman ? L.cab[first] : 0u;
   for (int p = first; p < nman; p += stride) {
-    const int sidx = L.cpos[p];
+    const int sidx = sidx_next;
+    const uint32_t code = code_next;
+    if (p + stride < nman) {
+      sidx_next = L.cpos[p + stride];
+      code_next = L.cab[p + stride];
+    }
     if (sidx < 0) continue;
-    const uint32_t code = L.cab[p];
     const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
     float n[3], depth;
     uint32_t slots;
@@ -1844,6 +1870,7 @@ __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a,
                                              sat + 4 * (size_t)(nw > 1 ? sat_slot(L, nw, p) : p));
     // warm start: previous step's impulses of the same (pair, slot) if the normal barely turned
     int found = -1;
+    float lam[12] = {0.f};
     if (keep_prev && nprev > 0) {
       int lo = 0, hi = nprev - 1;
       while (lo <= hi) {
@@ -1853,13 +1880,32 @@ __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a,
         if (kk < code) lo = mid + 1; else hi = mid - 1;
       }
       if (found >= 0) {
-        const float pn[3] = {L.pnrm[found], L.pnrm[PC + found], L.pnrm[2 * PC + found]};
-        if (!(dot3(pn, n) > 0.95f)) found = -1;
+        if constexpr (kFar) {
+          const float4* prev = reinterpret_cast<const float4*>(a.prev_data + 16 * (size_t)(slot0 + found));
+          const float4 pn = prev[0], u = prev[1], v = prev[2], w = prev[3];
+          const float last[12] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w, w.x, w.y, w.z, w.w};
+          const float nn[3] = {pn.x, pn.y, pn.z};
+          if (dot3(nn, n) > 0.95f) {
+            const uint32_t ps = __float_as_uint(pn.w);
+            const int pnp = (int)(ps & 15u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int r = 0; r < 4; ++r)
+                if (q < npts && r < pnp && ((ps >> (4 + 4 * r)) & 15u) == ((slots >> (4 * q)) & 15u)) {
+#pragma unroll
+                  for (int k = 0; k < 3; ++k) lam[3 * q + k] = last[3 * r + k];
+                }
+          }
+        } else {
+          const float pn[3] = {L.pnrm[found], L.pnrm[PC + found], L.pnrm[2 * PC + found]};
+          if (!(dot3(pn, n) > 0.95f)) found = -1;
+        }
       }
     }
     for (int q = 0; q < npts; ++q) {
       float l0 = 0.f, l1 = 0.f, l2 = 0.f;
-      if (found >= 0) {
+      if (!kFar && found >= 0) {
         const uint32_t ps = L.pslot[found];
         const int pnp = (int)(ps & 15u);
         const uint32_t sq = (slots >> (4 * q)) & 15u;
@@ -1870,19 +1916,24 @@ __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a,
             l2 = L.plam[(r * 3 + 2) * PC + found];
           }
       }
-      mdev(L, sidx)[12 + q * 3 + 0] = l0;
-      mdev(L, sidx)[12 + q * 3 + 1] = l1;
-      mdev(L, sidx)[12 + q * 3 + 2] = l2;
+      if (!kFar) {
+        mdev(L, sidx)[12 + q * 3 + 0] = l0;
+        mdev(L, sidx)[12 + q * 3 + 1] = l1;
+        mdev(L, sidx)[12 + q * 3 + 2] = l2;
+      }
+    }
+    if constexpr (kFar) {
+      // (slots past the points are read, to no effect)
+      float4* const rec = reinterpret_cast<float4*>(mdev(L, sidx));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) rec[3 + c] = make_float4(lam[4 * c], lam[4 * c + 1], lam[4 * c + 2], lam[4 * c + 3]);
     }
     if (kExt && a.restitution_bias)
       bias_targets(L, i, j, j == (int)kGround, mdev(L, sidx), L.mtb + 4 * (size_t)sidx, npts, n, a.g, a.dt, a.restitution);
-    L.mab[sidx] = code;
-    L.mmeta[sidx] = (uint32_t)npts | (slots << 12);
-    mdev(L, sidx)[27] = depth;
     if (keep_prev) L.mcanon[sidx] = p;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) mdev(L, sidx)[24 + k] = n[k];
     const int ti = L.tw[i];
+    reinterpret_cast<float4*>(mdev(L, sidx))[6] = make_float4(n[0], n[1], n[2], depth);
+    reinterpret_cast<uint4*>(L.mpair)[sidx] = make_uint4(code, (uint32_t)npts | (slots << 12), __float_as_uint(L.mu[ti]), 0u);
     atomicAdd(&L.tcnt[ti * 4 + 1], 1u);
     atomicAdd(&L.tcnt[ti * 4 + 2], (uint32_t)npts);
     atomicAdd(&L.tpts[ti], npts);
@@ -2076,7 +2127,7 @@ __device__ __forceinline__ void learned_chunks(const Lds& L, const StepArgs& a, 
   const uint4* net = (const uint4*)a.mlp;
   for (int m0 = first * (kWave / 4); m0 < nkept; m0 += stride * (kWave / 4)) {
     const int m = m0 + (lane >> 2), j = lane & 3;
-    const bool valid = m < nkept && j < (int)(L.mmeta[m] & 15u);
+    const bool valid = m < nkept && j < (int)(man_meta(L, m) & 15u);
     float f[mlp::kFeat];
     if (valid) point_features(L, m, j, gdt, f);
     else
@@ -2100,7 +2151,7 @@ __device__ __forceinline__ void learned_chunks(const Lds& L, const StepArgs& a, 
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int row = 16 * t + lane, mm = m0 + (row >> 2), jj = row & 3;
-          if (mm < nkept && jj < (int)(L.mmeta[mm] & 15u))
+          if (mm < nkept && jj < (int)(man_meta(L, mm) & 15u))
 #pragma unroll
             for (int k = 0; k < 3; ++k) mdev(L, mm)[12 + jj * 3 + k] = y[t][k] + prevd[3 * row + k];
         }
@@ -2320,7 +2371,7 @@ __device__ __forceinline__ int on_chip_pairs(const Lds& L, float margin, int nb,
     wt[w] = in ? L.tw[j] : -1;
   }
   const int nwin = (nb + kWave - 1) / kWave;
-  int cur_t = -1, cand_acc = 0;
+  int cur_t = -1, cand_acc = 0, wend = nwin;   // (the towers of a pack are runs of its bodies)
   for (int i = i0; i < i1; ++i) {
     const int wi = i / kWave, li = i % kWave;
     float xi[3], hi[3];
@@ -2342,11 +2393,12 @@ __device__ __forceinline__ int on_chip_pairs(const Lds& L, float margin, int nb,
       if (lane == 0 && cur_t >= 0 && cand_acc) atomicAdd(&L.tcnt[cur_t * 4 + 0], (uint32_t)cand_acc);
       cur_t = ti;
       cand_acc = 0;
+      wend = (__builtin_amdgcn_readfirstlane(L.tb1[ti]) + kWave - 1) / kWave;
     }
     const bool dyni = (fi & kDynamic) != 0;
 #pragma unroll
     for (int w = 0; w < kWindows; ++w) {
-      if (w < wi || w >= nwin) continue;
+      if (w < wi || w >= wend) continue;
       const int j = w * kWave + lane;
       const bool hit = j > i && wt[w] == ti && (wf[w] & kActive) && (dyni || (wf[w] & kDynamic)) &&
                        fabsf(xi[0] - wx[w][0]) <= hi[0] + wh[w][0] + margin &&
@@ -2391,8 +2443,7 @@ __device__ __forceinline__ int on_chip_pairs(const Lds& L, float margin, int nb,
 // equals the sequential greedy colouring.  Colours go to cpos, their counts to colcnt.
 __device__ __forceinline__ void colour_chunks(const Lds& L, int nb, int nman, int lane) {
   const int NB = L.nbp;
-  // per-body lane masks of the current chunk (the sorted-manifold words are free until the manifolds
-  // are written): lanes that touch body i, low and high 32 lanes
+  // per-body lane masks of the current chunk: lanes that touch body i, low and high 32 lanes
   uint32_t* const lmlo = L.lmlo;
   uint32_t* const lmhi = L.lmhi;
   for (int i = lane; i < nb; i += kWave) { L.hm[i] = 0.f; L.hm[NB + i] = 0.f; lmlo[i] = 0u; lmhi[i] = 0u; }
@@ -2444,6 +2495,7 @@ __device__ __forceinline__ void colour_chunks(const Lds& L, int nb, int nman, in
       L.cpos[p] = col;
       if (col >= 0) atomicAdd(&L.colcnt[col], 1);
       else atomicOr((uint32_t*)&L.scal[3], kErrCol);
+      if (col >= 0) atomicMax(&L.tcnt[L.tw[i] * 4 + 3], (uint32_t)(col + 1));
     }
   }
   wave_sync();
@@ -2459,83 +2511,94 @@ __device__ __forceinline__ void post(uint32_t* p, uint32_t v) {
 // keeps a wave's LDS accesses in program order (the LDS performs one wave's accesses in order)
 __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-// The same colouring by every wave of a workgroup (bodies' words in LDS).  A manifold's turn on each of
-// its dynamic bodies is the number of earlier manifolds that touch it: those with the body second, all
-// before those with it first, and among the latter its place in the body's run.  A wave takes 64
-// manifolds of the canonical list at a time; a lane is coloured when both bodies' counters have reached
-// its turns, then advances them.  The first uncoloured manifold is always some wave's current one and
-// ready, so every wait ends; the rounds are bounded all the same.  One wave walking the list chunk by
-// chunk took 29 % of a 4,096-stone wall's step, about fifty rounds to a chunk; here the chains of
-// different courses run side by side.  list: `cap` words per body.  Returns false, the same on every
-// thread, when a body is second in more than `cap` manifolds (colour_chunks then does it).
-__device__ __forceinline__ bool colour_waves(const Lds& L, int nb, int nman, int tid, int nthr, uint32_t* list, int cap) {
-  const int NB = L.nbp, lane = tid & (kWave - 1), wave = tid / kWave;
+// a body's colour mask in LDS or, agent-wide, in device memory
+template <bool kLds>
+__device__ __forceinline__ uint32_t mask_read(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+template <bool kLds>
+__device__ __forceinline__ void mask_add(uint32_t* p, uint32_t bit) {
+  (void)__hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Greedy first fit for a wave's first n lanes' pairs in lane order (i, j: their dynamic bodies, -1 if none),
+// over the bodies' colour masks; returns the lane's colour, -1 if none is free.  Turn `turn` of the list
+// waits until the turns before it are done.  The chain from a pair to the next is a lane's free colours
+// read into scalars, the first of them, and that bit out of those of the later lanes that share a body.
+template <bool kLds>
+__device__ __forceinline__ int colour_group(int n, int i, int j, uint32_t* mlo, uint32_t* mhi, int32_t* turns,
+                                            uint32_t turn) {
+  constexpr int kStep = 8;   // (a wave is a whole number of them; lanes from n on have no free colour and share nothing)
+  const int lane = (int)threadIdx.x & (kWave - 1);
+  const int ki = i >= 0 ? i : (int)0x80000000 + lane, kj = j >= 0 ? j : (int)0xc0000000 + lane;   // (none: shared with no lane)
+  int slo = 0, shi = 0;      // the later lanes that share a body with this one
+  for (int k0 = 0; k0 < n; k0 += kStep)
+#pragma unroll
+    for (int k = k0; k < k0 + kStep; ++k) {
+      const int ik = __builtin_amdgcn_readlane(ki, k), jk = __builtin_amdgcn_readlane(kj, k);
+      uint64_t s = __ballot(ki == ik) | __ballot(ki == jk) | __ballot(kj == ik) | __ballot(kj == jk);
+      s &= ~1ull << k;
+      slo = lane == k ? (int)(uint32_t)s : slo;
+      shi = lane == k ? (int)(uint32_t)(s >> 32) : shi;
+    }
+  while (poll(reinterpret_cast<uint32_t*>(turns)) != turn) {}
+  lds_order();
+  uint32_t lo = lane < n ? ~0u : 0u, hi = lo;
+  if (i >= 0) { lo &= ~mask_read<kLds>(mlo + i); hi &= ~mask_read<kLds>(mhi + i); }
+  if (j >= 0) { lo &= ~mask_read<kLds>(mlo + j); hi &= ~mask_read<kLds>(mhi + j); }
+  for (int k0 = 0; k0 < n; k0 += kStep)
+#pragma unroll
+    for (int k = k0; k < k0 + kStep; ++k) {
+      const uint64_t f = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, k) |
+                         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, k) << 32);
+      const uint64_t s = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(slo, k) |
+                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(shi, k) << 32);
+      const uint64_t keep = ~(f & (0ull - f));   // (no free colour: nothing taken)
+      const bool shared = __builtin_amdgcn_inverse_ballot_w64(s);
+      const uint32_t klo = lo & (uint32_t)keep, khi = hi & (uint32_t)(keep >> 32);
+      lo = shared ? klo : lo;
+      hi = shared ? khi : hi;
+    }
+  const int col = lo ? __builtin_ctz(lo) : (hi ? 32 + __builtin_ctz(hi) : -1);
+  if (col >= 0) {
+    uint32_t* const half = col < 32 ? mlo : mhi;
+    if (i >= 0) mask_add<kLds>(half + i, 1u << (col & 31));
+    if (j >= 0) mask_add<kLds>(half + j, 1u << (col & 31));
+  }
+  if (!kLds) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the masks are changed before the turn ends)
+  lds_order();
+  if (lane == 0) post(reinterpret_cast<uint32_t*>(turns), turn + 1u);
+  return col;
+}
+
+// The same colouring by every wave of a workgroup, the waves in turn.  A wave that waits has its manifolds and
+// what they share with each other ready, so the list advances at the chain's pace, about 50 cycles a
+// manifold.  One wave walking it in rounds took 29 % of a 4,096-stone wall's step; rounds by every wave,
+// each manifold waiting for its bodies' turns in LDS, 15 % (130 cycles a manifold).
+template <bool kLds>   // the bodies' masks are in LDS
+__device__ __forceinline__ void colour_turns(const Lds& L, int nb, int nman, int tid, int nthr) {
+  const int lane = tid & (kWave - 1);
   uint32_t* const lo = (uint32_t*)L.hm;
-  uint32_t* const hi = lo + NB;
-  uint32_t* const turn = lo + 2 * NB;
-  uint32_t* const nsecond = L.lmlo;     // manifolds with body x second
-  uint32_t* const first = L.lmhi;       // first canonical manifold with body x first
-  for (int i = tid; i < nb; i += nthr) { lo[i] = 0u; hi[i] = 0u; turn[i] = 0u; nsecond[i] = 0u; }
+  uint32_t* const hi = lo + L.nbp;
+  for (int i = tid; i < nb; i += nthr) { lo[i] = 0u; hi[i] = 0u; }
   if (tid == 0) L.scal[7] = 0;
   __syncthreads();
-  for (int p = tid; p < nman; p += nthr) {
-    const uint32_t code = L.cab[p];
-    const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
-    if (p == 0 || (int)(L.cab[p - 1] >> 16) != i) first[i] = (uint32_t)p;
-    if (j != (int)kGround && (L.flag[j] & kDynamic)) {
-      const int k = (int)atomicAdd(&nsecond[j], 1u);
-      if (k < cap) list[j * cap + k] = (uint32_t)p;
-      else atomicOr((uint32_t*)&L.scal[7], 1u);
-    }
-  }
-  __syncthreads();
-  if (L.scal[7]) return false;
-  const int most = 64 * nman + 4096;    // rounds: far beyond what the longest chain takes
-  for (int c0 = wave * kWave; c0 < nman; c0 += nthr) {
+  for (int c0 = tid - lane; c0 < nman; c0 += nthr) {
     const int p = c0 + lane;
     const bool valid = p < nman;
     const uint32_t code = valid ? L.cab[p] : 0u;
     const int i = (int)(code >> 16), j = (int)(code & 0xffffu);
     const bool di = valid && (L.flag[i] & kDynamic);
     const bool dj = valid && j != (int)kGround && (L.flag[j] & kDynamic);
-    const uint32_t ti = di ? nsecond[i] + ((uint32_t)p - first[i]) : 0u;
-    uint32_t tj = 0u;
-    if (dj)
-      for (int k = 0; k < (int)nsecond[j]; ++k) tj += list[j * cap + k] < (uint32_t)p ? 1u : 0u;
-    const int ia = di ? i : 0, jb = dj ? j : 0;   // (words that exist; unused where the body is static)
-    bool done = !valid;
-    int col = -1;
-    for (int round = 0; round < most; ++round) {
-      if (__all(done)) break;
-      const uint32_t ci = poll(turn + ia), cj = poll(turn + jb);
-      lds_order();                       // the masks are read after the turns, and written before them
-      const uint32_t ui0 = poll(lo + ia), ui1 = poll(hi + ia), uj0 = poll(lo + jb), uj1 = poll(hi + jb);
-      if (!done && (!di || ci == ti) && (!dj || cj == tj)) {
-        const uint64_t mi = di ? (uint64_t)ui0 | ((uint64_t)ui1 << 32) : 0ull;
-        const uint64_t mj = dj ? (uint64_t)uj0 | ((uint64_t)uj1 << 32) : 0ull;
-        const uint64_t u = mi | mj;
-        if (u != ~0ull) {
-          col = __ffsll((unsigned long long)~u) - 1;
-          const uint64_t bit = 1ull << col;
-          if (di) { post(lo + i, (uint32_t)(mi | bit)); post(hi + i, (uint32_t)((mi | bit) >> 32)); }
-          if (dj) { post(lo + j, (uint32_t)(mj | bit)); post(hi + j, (uint32_t)((mj | bit) >> 32)); }
-        }
-        lds_order();
-        if (di) post(turn + i, ti + 1u);
-        if (dj) post(turn + j, tj + 1u);
-        done = true;
-      }
-      lds_order();
-    }
+    const int col = colour_group<kLds>(min(kWave, nman - c0), di ? i : -1, dj ? j : -1, lo, hi, &L.scal[7],
+                                       (uint32_t)(c0 / kWave));
     if (valid) {
       L.cpos[p] = col;
       if (col >= 0) atomicAdd(&L.colcnt[col], 1);
       else atomicOr((uint32_t*)&L.scal[3], kErrCol);
     }
-    if (!__all(done) && lane == 0) atomicOr((uint32_t*)&L.scal[7], 1u);
   }
   __syncthreads();
-  return L.scal[7] == 0;
 }
 
 // Colour offsets from the counts in colcnt (one wave: a prefix sum over the 64 colours); colcnt becomes
@@ -2590,7 +2653,7 @@ __device__ __forceinline__ void colour_positions(const Lds& L, int p0, int p1, i
 // Every wave of a workgroup walks the same steps and passes the same barriers; a pack in LDS is one
 // wave, and its barriers are wave barriers.  An island's or a small batch's waves share every phase
 // that is not a scan: the broadphase and narrowphase (each wave's colliding pairs are one run of the
-// canonical list), the colouring (colour_waves), the manifolds, the network's chunks, the sweeps
+// canonical list), the colouring (colour_turns), the manifolds, the network's chunks, the sweeps
 // (register-resident lane pairs for a small batch, pgs_sweeps_lat), the outputs and the integration.
 // The plain variant runs kIslandWaves waves; the one with the network's registers (one wave per SIMD)
 // runs four, one per SIMD of the compute unit.
@@ -2607,13 +2670,20 @@ constexpr int step_threads() {
 // either compiles to flat instructions, which are as slow as device memory even on LDS).
 // kExt: the solver variants (disc friction, restitution targets, reference-face clipping) and the
 // episode criteria are compiled in; the default plain kernel carries none of their registers.
-template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false>
+// kMany: a batch of more packs than two waves per SIMD hold.  Three waves hide more of each other's latency
+// than the spills of a third fewer registers cost (16,384 falling towers: 8.98 ms for two steps, 7.95 with
+// three; of 1,500 towers, which are all resident either way, 2.00 and 2.12 ms).
+template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false, bool kMany = false>
 __global__ void __launch_bounds__((step_threads<kLearned, kGlobal, kLat>()))
-__attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
+__attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel(StepArgs a) {
   constexpr bool kMulti = kGlobal || kLat;   // several waves
+  // The previous step's store is used where it lies between launches by one-wave packs, but not by the solver
+  // variants: the compiler fused the reference-face clipping's products differently beside it, and a
+  // batch's bits must not depend on its route.
+  constexpr bool kFar = !kMulti && (kLearned || !kExt);
   extern __shared__ __align__(16) float smem[];
   float* const dev = a.gmem + a.pack_goff[a.pack_first + blockIdx.x];
-  const Lds L = carve(kGlobal ? dev + kManPackWords * a.pc : smem, dev, smem, kGlobal, kGlobal && kHot, a);
+  const Lds L = carve(kGlobal ? dev + kManPackWords * a.pc : smem, dev, smem, kGlobal, kGlobal && kHot, kMulti, kFar, kLearned && !kMulti, a);
   const bool keep_prev = lds_mode(a) >= 1;   // previous-step store kept (warm start or records)
   const int tid = threadIdx.x;
   const int nthr = kMulti ? (int)blockDim.x : kWave;
@@ -2694,11 +2764,13 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     for (int p = tid; p < npv; p += nthr) {
       const int g = slot0 + p;
       L.pkey[p] = a.prev_key[g];
-      L.pslot[p] = __float_as_uint(a.prev_data[16 * g + 3]);
+      if constexpr (!kFar) {
+        L.pslot[p] = __float_as_uint(a.prev_data[16 * g + 3]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) L.pnrm[k * PC + p] = a.prev_data[16 * g + k];
+        for (int k = 0; k < 3; ++k) L.pnrm[k * PC + p] = a.prev_data[16 * g + k];
 #pragma unroll
-      for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = a.prev_data[16 * g + 4 + k];
+        for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = a.prev_data[16 * g + 4 + k];
+      }
     }
   }
   sync();
@@ -2908,17 +2980,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       // ---- 5. tower ranges of the canonical list; greedy first-fit colouring, colour-sorted slots ----
       if constexpr (kMulti) {
         if (tid == 0 && nman > 0) { L.tc0[0] = 0; L.tc1[0] = nman; }   // one tower
-        bool coloured = false;
-        if constexpr (kLat || kHot) {
-          coloured = colour_waves(L, nb, nman, tid, nthr, kLat ? reinterpret_cast<uint32_t*>(L.vw) : L.cslot,
-                                  kLat ? kLatList : kCandPerBody);
-          if (!coloured)
-            for (int c = tid; c <= kMaxColours; c += nthr) L.colcnt[c] = 0;
-        }
-        if (!coloured) {
-          sync();
-          if (wave == 0) colour_chunks(L, nb, nman, lane);
-        }
+        colour_turns<kLat || kHot>(L, nb, nman, tid, nthr);
         // each wave ranks one stretch of the list; its colours start where the earlier waves' end
         int32_t* const at = L.wcol + wave * kMaxColours;
         const int per = ((nman + kWave - 1) / kWave + nw - 1) / nw * kWave;
@@ -2953,10 +3015,6 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
           }
         }
         colour_chunks(L, nb, nman, lane);
-        for (int p = lane; p < nman; p += kWave) {
-          const int col = L.cpos[p];
-          if (col >= 0) atomicMax(&L.tcnt[(nt == 1 ? 0 : L.tw[L.cab[p] >> 16]) * 4 + 3], (uint32_t)(col + 1));
-        }
         colour_offsets(L, lane);
         wave_sync();
         colour_positions(L, 0, nman, L.colcnt, lane);
@@ -2967,7 +3025,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       const int nkept = L.coloff[ncol];
 
       // ---- 6. manifolds into colour-sorted slots (+ warm start lookup) ----
-      build_manifolds<kExt>(L, a, sat, nw, tid, nthr, nman, keep_prev);
+      build_manifolds<kExt, kFar>(L, a, sat, nw, tid, nthr, nman, keep_prev, slot0);
       sync();
       timer.mark(L, tid, 4);
 
@@ -3012,7 +3070,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
           const float gdt = sqrtf(a.g[0] * a.g[0] + a.g[1] * a.g[1] + a.g[2] * a.g[2]) * dt;
           for (int col = 0; col < ncol; ++col) {
             for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr)
-              learned_apply_manifold(L, m, L.mu[L.tw[L.mab[m] >> 16]], gdt, opts.cone);
+              learned_apply_manifold(L, m, L.mu[L.tw[man_pair(L, m) >> 16]], gdt, opts.cone);
             sync();
           }
           sweeps = a.mlp_iters;
@@ -3050,14 +3108,14 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
                   L.w[k * NB + i] = L.vsave[(3 + k) * NB + i];
                 }
             for (int m = tid; m < nkept; m += nthr)
-              if (L.tfb[L.tw[L.mab[m] >> 16]])
+              if (L.tfb[L.tw[man_pair(L, m) >> 16]])
 #pragma unroll
                 for (int k = 0; k < 12; ++k) mdev(L, m)[12 + k] = 0.f;
             sync();
             for (int it = 0; it < a.iters; ++it) {
               for (int col = 0; col < ncol; ++col) {
                 for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) {
-                  const int t = L.tw[L.mab[m] >> 16];
+                  const int t = L.tw[man_pair(L, m) >> 16];
                   if (L.tfb[t]) solve_manifold(L, m, opts);
                 }
                 sync();
@@ -3081,10 +3139,10 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
         for (int m = tid; m < nkept; m += nthr) {
           int col = 0;
           while (col + 1 < ncol && L.coloff[col + 1] <= m) ++col;
-          const int a_ = (int)(L.mab[m] >> 16);
+          const int a_ = (int)(man_pair(L, m) >> 16);
           const int g = slot0 + m;
-          a.out_ab[g] = L.mab[m];
-          a.out_meta[g] = (L.mmeta[m] & 0x0ffff00fu) | ((uint32_t)col << 4);
+          a.out_ab[g] = man_pair(L, m);
+          a.out_meta[g] = (man_meta(L, m) & 0x0ffff00fu) | ((uint32_t)col << 4);
           a.out_tower[g] = L.tw[a_];
           const float nn[3] = {mdev(L, m)[24], mdev(L, m)[25], mdev(L, m)[26]};
           Frame F;
@@ -3095,7 +3153,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
           }
           a.out_geo[8 * g + 6] = mdev(L, m)[27];
           a.out_geo[8 * g + 7] = 0.f;
-          const int npts = (int)(L.mmeta[m] & 15u);
+          const int npts = (int)(man_meta(L, m) & 15u);
           if constexpr (kLearned) {
             if (a.feat_out) record_solution(L, m, a.feat_out + (size_t)g * 4 * kFeatRecord);
           }
@@ -3114,16 +3172,30 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       }
       if (keep_prev) {
         // canonical-order store of this step's impulses (dropped pairs keep their key, no points)
-        for (int p = tid; p < nman; p += nthr) { L.pkey[p] = L.cab[p]; L.pslot[p] = 0u; }
+        float4* const prev = reinterpret_cast<float4*>(a.prev_data) + 4 * (size_t)slot0;
+        for (int p = tid; p < nman; p += nthr) {
+          L.pkey[p] = L.cab[p];
+          if constexpr (!kFar) L.pslot[p] = 0u;
+          else if (L.cpos[p] < 0) a.prev_data[16 * (size_t)(slot0 + p) + 3] = 0.f;
+        }
         sync();
         for (int m = tid; m < nkept; m += nthr) {
           const int p = L.mcanon[m];
-          const uint32_t meta = L.mmeta[m];
+          const uint32_t meta = man_meta(L, m);
           const int npts = (int)(meta & 15u);
-          L.pslot[p] = (uint32_t)npts | (((meta >> 12) & 0xffffu) << 4);
+          const uint32_t ps = (uint32_t)npts | (((meta >> 12) & 0xffffu) << 4);
+          if constexpr (!kFar) {
+            L.pslot[p] = ps;
 #pragma unroll
-          for (int k = 0; k < 3; ++k) L.pnrm[k * PC + p] = mdev(L, m)[24 + k];
-          for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = mdev(L, m)[12 + k];
+            for (int k = 0; k < 3; ++k) L.pnrm[k * PC + p] = mdev(L, m)[24 + k];
+            for (int k = 0; k < 12; ++k) L.plam[k * PC + p] = mdev(L, m)[12 + k];
+          } else {
+            const float4* rec = reinterpret_cast<const float4*>(mdev(L, m));
+            const float4 nd = rec[6];
+            prev[4 * p] = make_float4(nd.x, nd.y, nd.z, __uint_as_float(ps));
+#pragma unroll
+            for (int c = 0; c < 3; ++c) prev[4 * p + 1 + c] = rec[3 + c];
+          }
         }
         if (tid == 0) L.scal[4] = nman;
       }
@@ -3154,13 +3226,20 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
       sync();
       timer.mark(L, tid, 8);
       // ---- 10. Baumgarte position correction, colour by colour ----
-      for (int col = 0; col < ncol; ++col) {
-        for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) {
-          const uint32_t ab = L.mab[m];
-          const int j = (int)(ab & 0xffffu);
-          baumgarte_pair(L, (int)(ab >> 16), j, j == (int)kGround, mdev(L, m), a.beta, a.slop);
+      {
+        // (a thread's first pair of the next colour is read while this one is worked)
+        uint32_t next = ncol > 0 && L.coloff[0] + tid < L.coloff[1] ? man_pair(L, L.coloff[0] + tid) : 0u;
+        for (int col = 0; col < ncol; ++col) {
+          uint32_t ab = next;
+          const int m1 = col + 1 < ncol ? L.coloff[col + 1] + tid : nkept;
+          next = m1 < nkept && m1 < L.coloff[col + 2] ? man_pair(L, m1) : 0u;
+          for (int m = L.coloff[col] + tid; m < L.coloff[col + 1]; m += nthr) {
+            if (m >= L.coloff[col] + nthr) ab = man_pair(L, m);
+            const int j = (int)(ab & 0xffffu);
+            baumgarte_pair(L, (int)(ab >> 16), j, j == (int)kGround, mdev(L, m), a.beta, a.slop);
+          }
+          sync();
         }
-        sync();
       }
       timer.mark(L, tid, 9);
     }
@@ -3228,11 +3307,13 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : 2))) step_kernel(StepArgs a) {
     for (int p = tid; p < npv; p += nthr) {
       const int g = slot0 + p;
       a.prev_key[g] = L.pkey[p];
-      a.prev_data[16 * g + 3] = __uint_as_float(L.pslot[p]);
+      if constexpr (!kFar) {
+        a.prev_data[16 * g + 3] = __uint_as_float(L.pslot[p]);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) a.prev_data[16 * g + k] = L.pnrm[k * PC + p];
+        for (int k = 0; k < 3; ++k) a.prev_data[16 * g + k] = L.pnrm[k * PC + p];
 #pragma unroll
-      for (int k = 0; k < 12; ++k) a.prev_data[16 * g + 4 + k] = L.plam[k * PC + p];
+        for (int k = 0; k < 12; ++k) a.prev_data[16 * g + 4 + k] = L.plam[k * PC + p];
+      }
     }
     if (tid == 0) a.prev_count[pk] = npv;
   }
@@ -3490,67 +3571,6 @@ __device__ __forceinline__ Grid make_grid(const int32_t* S, float margin, int ca
     G.h = 3.0e38f;
   }
   return G;
-}
-
-// a body's colour mask in LDS or, agent-wide, in device memory
-template <bool kLds>
-__device__ __forceinline__ uint32_t mask_read(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
-}
-template <bool kLds>
-__device__ __forceinline__ void mask_add(uint32_t* p, uint32_t bit) {
-  (void)__hip_atomic_fetch_or(p, bit, __ATOMIC_RELAXED, kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Greedy first fit for a wave's first n lanes' pairs in lane order (i, j: their dynamic bodies, -1 if none),
-// over the bodies' colour masks; returns the lane's colour, -1 if none is free.  Turn `turn` of the list
-// waits until the turns before it are done.  The chain from a pair to the next is a lane's free colours
-// read into scalars, the first of them, and that bit out of those of the later lanes that share a body.
-template <bool kLds>
-__device__ __forceinline__ int colour_group(int n, int i, int j, uint32_t* mlo, uint32_t* mhi, int32_t* turns,
-                                            uint32_t turn) {
-  constexpr int kStep = 4;   // (a wave is a whole number of them; lanes from n on have no free colour and share nothing)
-  const int lane = (int)threadIdx.x & (kWave - 1);
-  const int ki = i >= 0 ? i : (int)0x80000000 + lane, kj = j >= 0 ? j : (int)0xc0000000 + lane;   // (none: shared with no lane)
-  int slo = 0, shi = 0;      // the later lanes that share a body with this one
-  for (int k0 = 0; k0 < n; k0 += kStep)
-#pragma unroll
-    for (int k = k0; k < k0 + kStep; ++k) {
-      const int ik = __builtin_amdgcn_readlane(ki, k), jk = __builtin_amdgcn_readlane(kj, k);
-      uint64_t s = __ballot(ki == ik) | __ballot(ki == jk) | __ballot(kj == ik) | __ballot(kj == jk);
-      s &= ~1ull << k;
-      slo = lane == k ? (int)(uint32_t)s : slo;
-      shi = lane == k ? (int)(uint32_t)(s >> 32) : shi;
-    }
-  while (poll(reinterpret_cast<uint32_t*>(turns)) != turn) {}
-  lds_order();
-  uint32_t lo = lane < n ? ~0u : 0u, hi = lo;
-  if (i >= 0) { lo &= ~mask_read<kLds>(mlo + i); hi &= ~mask_read<kLds>(mhi + i); }
-  if (j >= 0) { lo &= ~mask_read<kLds>(mlo + j); hi &= ~mask_read<kLds>(mhi + j); }
-  for (int k0 = 0; k0 < n; k0 += kStep)
-#pragma unroll
-    for (int k = k0; k < k0 + kStep; ++k) {
-      const uint64_t f = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, k) |
-                         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, k) << 32);
-      uint64_t s = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(slo, k) |
-                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(shi, k) << 32);
-      s = f != 0ull ? s : 0ull;
-      const uint64_t keep = ~(1ull << (__builtin_ctzll(f | (1ull << 63))));
-      const bool shared = __builtin_amdgcn_inverse_ballot_w64(s);
-      const uint32_t klo = lo & (uint32_t)keep, khi = hi & (uint32_t)(keep >> 32);
-      lo = shared ? klo : lo;
-      hi = shared ? khi : hi;
-    }
-  const int col = lo ? __builtin_ctz(lo) : (hi ? 32 + __builtin_ctz(hi) : -1);
-  if (col >= 0) {
-    uint32_t* const half = col < 32 ? mlo : mhi;
-    if (i >= 0) mask_add<kLds>(half + i, 1u << (col & 31));
-    if (j >= 0) mask_add<kLds>(half + j, 1u << (col & 31));
-  }
-  if (!kLds) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the masks are changed before the turn ends)
-  lds_order();
-  if (lane == 0) post(reinterpret_cast<uint32_t*>(turns), turn + 1u);
-  return col;
 }
 
 // a body's inverse inertia in the frame F and its inverse mass (zero for the ground, which reads body 0's
@@ -4597,8 +4617,10 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
 
 // The step kernel's variants, by part of the build (this file is compiled once per part, side by side)
 #if JG_STEP_PART == 1
-const void* step_variant_pack(bool ext) {
-  return ext ? (const void*)step_kernel<false, false, false, true> : (const void*)step_kernel<false, false, false, false>;
+const void* step_variant_pack(bool ext, bool many) {
+  if (ext) return (const void*)step_kernel<false, false, false, true>;
+  return many ? (const void*)step_kernel<false, false, false, false, false, true>
+              : (const void*)step_kernel<false, false, false, false>;
 }
 #elif JG_STEP_PART == 2
 const void* step_variant_lat(bool ext) {
@@ -4635,8 +4657,9 @@ int ensure_lds_limit() {
   if (dev < 0 || dev >= kMaxDevices) return (int)hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(attr_mutex);
   if (!attr_set[dev]) {
-    const void* variants[12] = {(const void*)mega_kernel,
-                                step_variant_pack(false),          step_variant_pack(true),
+    const void* variants[13] = {(const void*)mega_kernel,
+                                step_variant_pack(false, false),   step_variant_pack(false, true),
+                                step_variant_pack(true, false),
                                 step_variant_lat(false),           step_variant_lat(true),
                                 step_variant_island(false, false), step_variant_island(false, true),
                                 step_variant_island(true, false),  step_variant_island(true, true),
@@ -4670,7 +4693,7 @@ int step_launch_config(const StepArgs& a, const void** func, unsigned* block_thr
     *func = step_variant_lat(ext);
     threads = (unsigned)a.lat;
   } else {
-    *func = step_variant_pack(ext);
+    *func = step_variant_pack(ext, a.many != 0);
   }
   *block_threads = threads;
   return 0;

@@ -177,6 +177,7 @@ struct jg_world {
     }
   };
   std::vector<Mega> megas;
+  bool many = false;                // more one-wave packs than two to a SIMD
   std::vector<int> mega_of_tower;   // tower id -> index in megas (-1: in a pack)
 };
 
@@ -266,31 +267,96 @@ int32_t build_layout(jg_world* w) {
   // workgroup (below) has LDS to spare and gets 6, room for a sinking or collapsing tower's pairs
   float mpb = w->prm.manifolds_per_body > 0.f ? w->prm.manifolds_per_body : 3.5f;
   const int mode = w->prm.warm_start == 2 ? 2 : ((w->prm.warm_start == 1 || w->prm.record_features) ? 1 : 0);
+  const bool pairs = jg::pairs_on_chip(mode, w->prm.record_features != 0);
   auto pc_of = [&](int nb) { return std::max(16, (int)std::ceil(mpb * nb)); };
-  auto lds_of = [&](int nb, int towers, int pushes) -> size_t {
-    return (size_t)jg::lds_words(nb, pc_of(nb), std::max(1, towers), std::max(1, pushes), mode) * 4;
+  int lat = 0;   // threads of a small batch's workgroups
+  auto layout_bytes = [&](int nb, int towers, int pushes, bool lists) -> size_t {
+    return (size_t)jg::lds_words(nb, pc_of(nb), std::max(1, towers), std::max(1, pushes), mode, lists, pairs) * 4;
   };
+  auto lds_of = [&](int nb, int towers, int pushes) { return layout_bytes(nb, towers, pushes, lat != 0); };
+  // workgroups with that much LDS to a CU (it is allocated in pieces of 1,280 bytes: ten of 15,360, nine of 15,368)
+  auto per_cu_lds = [](size_t bytes) { return (int)((160 * 1024) / std::max<size_t>(1280, (bytes + 1279) / 1280 * 1280)); };
   // an on-chip pack holds at most kRegBodies bodies (the register broadphase); larger islands
   // are kept in device memory, one tower each
   int target = w->prm.pack_bodies > 0 ? std::min(w->prm.pack_bodies, jg::kRegBodies) : 0;
-  int lat = 0;
+  // packs that the kernel's registers let a CU hold: the plain one three to a SIMD, the solver variants two,
+  // the network one
+  const bool wide = w->prm.warm_start == 2 || w->prm.record_features;
+  const bool variants = w->prm.friction_cone || w->prm.restitution_bias || w->prm.manifold_mode;
+  const int reg_packs = wide ? 4 : (variants ? 8 : 12);
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, w->prm.device) != hipSuccess) cus = 0;
   if (target <= 0) {
-    const bool wide = w->prm.warm_start == 2 || w->prm.record_features;
-    const size_t budget = wide ? 40 * 1024 : 20 * 1024;
-    target = 8;
-    while (lds_of(target + 1, 4, 8) <= budget) ++target;
-    // A batch with no more towers than the GPU holds workgroups at once gets one tower per pack:
-    // sharing a pack would only run towers one after another that could run side by side
-    // (the 450-tower removal batch steps 11 % faster so).
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, w->prm.device) == hipSuccess && cus > 0 &&
-        (int64_t)order.size() <= (int64_t)cus * (wide ? 4 : 8)) {
+    auto per_cu_of = [&](int nb) { return std::min(reg_packs, per_cu_lds(lds_of(nb, 4, w->pushes.empty() ? 1 : 8))); };
+    target = 8;   // bodies of a pack as the LDS allows with every wave that the registers do
+    while (target < jg::kRegBodies && per_cu_of(target + 1) >= reg_packs) ++target;
+    if (cus > 0 && (int64_t)order.size() <= (int64_t)cus * (wide ? 4 : 8)) {
+      // A batch with no more towers than the GPU holds workgroups at once gets one tower per pack:
+      // sharing a pack would only run towers one after another that could run side by side
+      // (the 450-tower removal batch steps 11 % faster so).
       target = 1;
       if (!(w->prm.manifolds_per_body > 0.f)) mpb = 6.0f;
       // at most two towers per CU: each gets a workgroup of four waves (two per CU at two waves
       // per SIMD), or of eight where every tower has a CU to itself, which share its step
       if (w->prm.small_batch >= 0 && !wide && (int64_t)order.size() <= 2 * (int64_t)cus)
         lat = (int64_t)order.size() <= (int64_t)cus ? 8 * jg::kWave : 4 * jg::kWave;
+    } else if (cus > 0) {
+      // The packs run in rounds of what the GPU holds at once, and a last round that is nearly empty costs a
+      // whole one.  A pack's time grows with its bodies, from what 64 of them cost on; beyond 128 its colours
+      // have more manifolds than a wave has lanes.  With the network, most of the work is per
+      // point.  The size with the least rounds times that is taken (the largest of equals).  Measured, two
+      // steps of falling towers of 24 to 120 boxes: 4,096 of them 2.01 ms in one round of packs of 120,
+      // 2.69 in two of 52; two steps of 3,000 towers of 36 to 72 with the network 3.03 in one round
+      // of 180, 3.34 in two of 98, 3.62 in three of 72.
+      std::vector<int64_t> sizes(jg::kRegBodies + 1, 0);
+      int64_t bodies = 0;
+      int largest = 1;
+      for (int t : order) {
+        const int n = (int)w->tower_bodies[t].size();
+        if (n > jg::kRegBodies) continue;
+        sizes[n] += 1;
+        bodies += n;
+        largest = std::max(largest, n);
+      }
+      // the towers in packs of at most `cap` bodies, largest first, each where it fits tightest: their number,
+      // and the CUs that hold them all at once
+      auto fill = [&](int cap, int64_t& packs, double& held) {
+        std::vector<int64_t> left(cap + 1, 0);   // packs by the bodies that they still take
+        packs = 0;
+        held = 0.0;
+        for (int n = jg::kRegBodies; n >= 1; --n) {
+          int64_t c = sizes[n];
+          for (int r = n; r <= cap && c > 0;) {
+            const int64_t k = std::min(c, left[r]);
+            left[r] -= k;
+            left[r - n] += k;
+            c -= k;
+            r = k > 0 ? n : r + 1;   // (what is left of those may take another)
+          }
+          if (c == 0) continue;
+          const int64_t each = std::max(1, cap / n), full = c / each, rest = c % each;
+          packs += full + (rest ? 1 : 0);
+          if (n <= cap) {
+            left[cap - (int)each * n] += full;
+            if (rest) left[cap - (int)rest * n] += 1;
+          } else {
+            held += (double)c / std::max(1, per_cu_of(n));
+          }
+        }
+        for (int r = 0; r <= cap; ++r) held += (double)left[r] / std::max(1, per_cu_of(cap - r));
+      };
+      double best = 0.0;
+      for (int cap = 8; cap <= jg::kRegBodies && bodies > 0 && per_cu_of(cap) > 0; ++cap) {
+        int64_t packs = 0;
+        double held = 0.0;
+        fill(cap, packs, held);
+        const double size = (wide ? 28.0 : 64.0 + 2.0 * std::max(0, cap - 128)) + (double)bodies / (double)packs;
+        // (one round if the packs fit with the largest one's LDS each: CUs that hold packs of several sizes
+        // leave some of it)
+        const bool once = packs <= (int64_t)cus * per_cu_of(std::max(cap, largest));
+        const double cost = (once ? 1.0 : std::max(2.0, std::ceil(held / (double)cus))) * size;
+        if (best == 0.0 || cost <= best) { best = cost; target = cap; }
+      }
     }
   }
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -303,7 +369,7 @@ int32_t build_layout(jg_world* w) {
   for (int t : order) {
     const int n = (int)w->tower_bodies[t].size();
     // an island beyond the LDS path (register broadphase windows, or LDS) is a global pack
-    if (n > jg::kRegBodies || lds_of(n, 1, tower_pushes[t]) > 160 * 1024 || w->prm.pack_bodies < 0) {
+    if (n > jg::kRegBodies || layout_bytes(n, 1, tower_pushes[t], true) > 160 * 1024 || w->prm.pack_bodies < 0) {
       Bin b;
       b.bodies = n; b.cap = n; b.towers.push_back(t); b.global = true;
       bins.push_back(b);
@@ -325,7 +391,7 @@ int32_t build_layout(jg_world* w) {
       int pushes = 0;
       for (int t : bins[b].towers) pushes += tower_pushes[t];
       key[b] = bins[b].global ? (1 << 30)   // global packs last, one class of their own
-                              : (int)((160 * 1024) / std::max<size_t>(1, lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes)));
+                              : per_cu_lds(lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes));
     }
     std::vector<size_t> idx(bins.size());
     for (size_t b = 0; b < idx.size(); ++b) idx[b] = b;
@@ -369,7 +435,7 @@ int32_t build_layout(jg_world* w) {
     w->pack_push0.push_back((int)w->push_order.size());
     // launch class: packs that fit the same number of workgroups per CU (global packs: one class)
     const size_t lds = lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes);
-    const int per_cu = bins[b].global ? 0 : (int)((160 * 1024) / lds);
+    const int per_cu = bins[b].global ? 0 : std::min(reg_packs, per_cu_lds(lds));
     if (!bins[b].global && per_cu == 0)
       return fail(JG_ECAPACITY, "a pack needs " + std::to_string(lds) + " bytes of LDS (max 163840); "
                                 "use smaller towers or fewer manifolds per body");
@@ -407,11 +473,31 @@ int32_t build_layout(jg_world* w) {
     w->mega_of_tower[t] = (int)w->megas.size();
     w->megas.push_back(m);
   }
+  // One-wave packs that the GPU holds all at once, with the largest one's LDS each, are one launch (800 towers
+  // of 24 to 120 boxes, two steps: 0.70 ms in the launches of three classes, 0.64 in one).
+  int packs = 0;
+  for (const auto& c : w->classes) packs += c.global || c.lat ? 0 : c.count;
+  w->many = cus > 0 && reg_packs > 8 && packs > 8 * cus;
+  if (cus > 0 && packs > 0) {
+    jg_world::PackClass all = w->classes[0];
+    size_t n = 0;
+    for (; n < w->classes.size() && !w->classes[n].global; ++n) {
+      const auto& c = w->classes[n];
+      all.nbp = std::max(all.nbp, c.nbp);
+      all.tpc = std::max(all.tpc, c.tpc);
+      all.ppc = std::max(all.ppc, c.ppc);
+    }
+    if (n > 1 && packs <= cus * std::min(reg_packs, per_cu_lds(lds_of(all.nbp, all.tpc, all.ppc)))) {
+      all.count = packs;
+      w->classes.erase(w->classes.begin() + 1, w->classes.begin() + (long)n);
+      w->classes[0] = all;
+    }
+  }
   // neighbouring classes whose LDS would fit more workgroups per CU than the kernel's registers
   // allow run at the same occupancy: one launch holds them all (with the largest pack's LDS, as
   // long as that still fits the register-bound count), so that they share one launch tail
   {
-    const int reg_cap = lat ? 8 * jg::kWave / lat : ((w->prm.warm_start == 2 || w->prm.record_features) ? 4 : 8);
+    const int reg_cap = lat ? 8 * jg::kWave / lat : reg_packs;
     for (size_t k = 1; k < w->classes.size();) {
       jg_world::PackClass& into = w->classes[k - 1];
       const jg_world::PackClass& from = w->classes[k];
@@ -419,7 +505,7 @@ int32_t build_layout(jg_world* w) {
                         from.per_cu >= reg_cap;
       const int nbp = std::max(into.nbp, from.nbp), tpc = std::max(into.tpc, from.tpc),
                 ppc = std::max(into.ppc, from.ppc);
-      if (same && (int)((160 * 1024) / lds_of(nbp, tpc, ppc)) >= reg_cap) {
+      if (same && per_cu_lds(lds_of(nbp, tpc, ppc)) >= reg_cap) {
         into.count += from.count;
         into.nbp = nbp;
         into.tpc = tpc;
@@ -462,15 +548,15 @@ int32_t build_layout(jg_world* w) {
         return fail(JG_ECAPACITY, "a pack kept in device memory needs " + std::to_string(c.lds) +
                                   " bytes of LDS for its towers and pushes (max 163840)");
       // (with the network, every wave of the island has its own staging rows)
-      c.gwords = ((int64_t)jg::kManPackWords * c.pc + jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) +
+      c.gwords = ((int64_t)jg::kManPackWords * c.pc + jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode, true, pairs) +
                   (mode == 2 ? (int64_t)(jg::kLearnedIslandWaves - 1) * jg::kStageWords : 0) +
-                  jg::window_words(c.nbp) + (2 + 4) * (int64_t)jg::kCandPerBody * c.nbp + 3 + 3) & ~(int64_t)3;
+                  jg::window_words(c.nbp) + (2 + 4) * (int64_t)jg::kCandPerBody * c.nbp + 3 + 31) & ~(int64_t)31;   // (whole lines)
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     } else {
-      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode) + (c.lat ? jg::lat_words(c.nbp, c.lat) : 0)) * 4;
+      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode, c.lat != 0, pairs) + (c.lat ? jg::lat_words(c.nbp, c.lat) : 0)) * 4;
       if (c.lds > 160 * 1024)
         return fail(JG_ECAPACITY, "a launch class needs " + std::to_string(c.lds) + " bytes of LDS (max 163840)");
-      c.gwords = ((int64_t)jg::kManPackWords * c.pc + (c.lat ? jg::lat_dev_words(c.pc, c.lat) : 0) + 3) & ~(int64_t)3;
+      c.gwords = ((int64_t)jg::kManPackWords * c.pc + (c.lat ? jg::lat_dev_words(c.pc, c.lat) : jg::pack_store_words(c.nbp, c.pc, mode)) + 31) & ~(int64_t)31;
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     }
     for (int k = 0; k < c.count; ++k) w->pack_slot0.push_back(w->pack_slot0.back() + c.pc);
@@ -1080,6 +1166,7 @@ int32_t jg_step_batch(jg_world* w, int32_t n_steps) {
     cls[k].in_gmem = c.global ? 1 : 0;
     cls[k].hot_bodies = c.hot_bodies ? 1 : 0;
     cls[k].lat = c.lat;
+    cls[k].many = w->many ? 1 : 0;
     cls[k].pack_goff = w->d_pack_goff.p;
   }
   if (w->prm.use_graph) {
