@@ -2572,9 +2572,10 @@ __device__ __forceinline__ int colour_group(int n, int i, int j, uint32_t* mlo, 
 }
 
 // The same colouring by every wave of a workgroup, the waves in turn.  A wave that waits has its manifolds and
-// what they share with each other ready, so the list advances at the chain's pace, about 50 cycles a
-// manifold.  One wave walking it in rounds took 29 % of a 4,096-stone wall's step; rounds by every wave,
-// each manifold waiting for its bodies' turns in LDS, 15 % (130 cycles a manifold).
+// what they share with each other ready, so the list advances at the chain's pace, 14 instructions a
+// manifold: with the rest of the phase 134 cycles a manifold of a 4,096-stone wall, and 166 of a 9,000-stone
+// wall with the masks in device memory.  One wave walking the list in rounds took 29 % of the
+// smaller wall's step and 24 M cycles of the larger one's.
 template <bool kLds>   // the bodies' masks are in LDS
 __device__ __forceinline__ void colour_turns(const Lds& L, int nb, int nman, int tid, int nthr) {
   const int lane = tid & (kWave - 1);
