@@ -2227,43 +2227,74 @@ __device__ __forceinline__ float support_margin(const Lds& L, int b0, int b1, fl
 __device__ __forceinline__ void episode_update(const Lds& L, const StepArgs& a, int gt0, int gb0, int nt, int lane,
                                                int64_t step, float* scratch) {
   const int NB = L.nbp, CAP = a.cap;
-  for (int t = lane; t < nt; t += kWave) {
+  for (int t0 = 0; t0 < nt; t0 += kWave) {
+    // The towers' sums, one tower after another: its bodies' terms by the lanes, added in body order (as one
+    // lane over a tower's bodies, waiting for each one's mass and first position, the criteria took
+    // 13 % of 1,500 towers' steps: four steps 2.76 ms, now 2.56); lane t - t0 keeps tower t's.
+    float ek = 0.f, dxmax = 0.f, rzz = 1.f, msum = 0.f, cx = 0.f, cy = 0.f;
+    bool cd = false;
+    for (int u = t0; u < min(nt, t0 + kWave); ++u) {
+      if (__builtin_amdgcn_readfirstlane(a.ep_state[(size_t)(gt0 + u) * kEpisodeWords + kEpFlags]) & kEpDone) continue;
+      const int b0 = __builtin_amdgcn_readfirstlane(L.tb0[u]), b1 = __builtin_amdgcn_readfirstlane(L.tb1[u]);
+      float uek = 0.f, um = 0.f, ux = 0.f, uy = 0.f, udx = 0.f, urz = 1.f;
+      bool ucd = false;
+      for (int i0 = b0; i0 < b1; i0 += kWave) {
+        const int i = i0 + lane;
+        const bool in = i < b1 && (L.flag[i] & (kActive | kDynamic)) == (kActive | kDynamic);
+        float m = 0.f, vv = 0.f, rr = 0.f, x = 0.f, y = 0.f;
+        if (in) {
+          m = a.mass[gb0 + i];
+          float R[9];
+          body_R(L, i, R);
+          const float l = 2.f * L.he[i], wd = 2.f * L.he[NB + i], hh = 2.f * L.he[2 * NB + i];
+          const float I0 = m / 12.f * (wd * wd + hh * hh), I1 = m / 12.f * (l * l + hh * hh),
+                      I2 = m / 12.f * (l * l + wd * wd);
+          float v[3], w[3];
+          load3(L.v, NB, i, v);
+          load3(L.w, NB, i, w);
+          const float wb0 = R[0] * w[0] + R[3] * w[1] + R[6] * w[2];
+          const float wb1 = R[1] * w[0] + R[4] * w[1] + R[7] * w[2];
+          const float wb2 = R[2] * w[0] + R[5] * w[1] + R[8] * w[2];
+          vv = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
+          rr = I0 * wb0 * wb0 + I1 * wb1 * wb1 + I2 * wb2 * wb2;
+          float d2 = 0.f;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const float d = L.x[k * NB + i] - a.ep_x0[k * CAP + gb0 + i];
+            d2 += d * d;
+          }
+          const float dn = sqrtf(d2);
+          udx = fmaxf(udx, dn);
+          ucd = ucd || dn > a.ep_fd * l;
+          urz = fminf(urz, R[8]);
+          x = L.x[i];
+          y = L.x[NB + i];
+        }
+        for (uint64_t todo = __ballot(in); todo; todo &= todo - 1) {
+          const int k = __builtin_ctzll(todo);
+          auto of = [&](float f) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), k)); };
+          const float mk = of(m);
+          uek = __builtin_fmaf(0.5f * mk, of(vv), uek);
+          uek = __builtin_fmaf(0.5f, of(rr), uek);
+          um += mk;
+          ux = __builtin_fmaf(mk, of(x), ux);
+          uy = __builtin_fmaf(mk, of(y), uy);
+        }
+      }
+#pragma unroll
+      for (int d = 1; d < kWave; d <<= 1) {
+        udx = fmaxf(udx, __shfl_xor(udx, d));
+        urz = fminf(urz, __shfl_xor(urz, d));
+      }
+      const bool any = __ballot(ucd) != 0ull;
+      if (lane == u - t0) { ek = uek; dxmax = udx; rzz = urz; msum = um; cx = ux; cy = uy; cd = any; }
+    }
+    const int t = t0 + lane;
+    if (t >= nt) continue;
     uint32_t* st = a.ep_state + (size_t)(gt0 + t) * kEpisodeWords;
     uint32_t flags = st[kEpFlags];
     if (flags & kEpDone) continue;
     const int b0 = L.tb0[t], b1 = L.tb1[t];
-    float ek = 0.f, dxmax = 0.f, rzz = 1.f, msum = 0.f, cx = 0.f, cy = 0.f;
-    bool cd = false;
-    for (int i = b0; i < b1; ++i) {
-      if ((L.flag[i] & (kActive | kDynamic)) != (kActive | kDynamic)) continue;
-      const float m = a.mass[gb0 + i];
-      float R[9];
-      body_R(L, i, R);
-      const float l = 2.f * L.he[i], wd = 2.f * L.he[NB + i], hh = 2.f * L.he[2 * NB + i];
-      const float I0 = m / 12.f * (wd * wd + hh * hh), I1 = m / 12.f * (l * l + hh * hh),
-                  I2 = m / 12.f * (l * l + wd * wd);
-      float v[3], w[3];
-      load3(L.v, NB, i, v);
-      load3(L.w, NB, i, w);
-      const float wb0 = R[0] * w[0] + R[3] * w[1] + R[6] * w[2];
-      const float wb1 = R[1] * w[0] + R[4] * w[1] + R[7] * w[2];
-      const float wb2 = R[2] * w[0] + R[5] * w[1] + R[8] * w[2];
-      ek += 0.5f * m * (v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-      ek += 0.5f * (I0 * wb0 * wb0 + I1 * wb1 * wb1 + I2 * wb2 * wb2);
-      float d2 = 0.f;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const float d = L.x[k * NB + i] - a.ep_x0[k * CAP + gb0 + i];
-        d2 += d * d;
-      }
-      const float dn = sqrtf(d2);
-      dxmax = fmaxf(dxmax, dn);
-      cd = cd || dn > a.ep_fd * l;
-      rzz = fminf(rzz, R[8]);
-      msum += m;
-      cx += m * L.x[i];
-      cy += m * L.x[NB + i];
-    }
     if (msum > 0.f) { cx /= msum; cy /= msum; }
     int nhull = 0;
     const float margin = support_margin(L, b0, b1, a.ep_eps, cx, cy, scratch + 16 * b0, nhull);
