@@ -187,6 +187,16 @@ inline int64_t lds_words(int nbp, int pc, int tpc, int ppc, int mode, bool lists
   if (pairs && !lists) w += (int64_t)kManPairWords * pc + 3;
   return w;
 }
+// The same with every pair's words, the whole store and the learned start's terms on chip: a tower that does
+// not fit LDS so is kept in device memory, where several waves share its step (100 towers of 228 bodies with
+// the network's start, two steps: 1.27 ms there, 2.41 ms on one wave each).
+inline int64_t full_words(int nbp, int pc, int tpc, int ppc, int mode) {
+  int64_t w = (int64_t)nbp * kBodyWords + (int64_t)tpc * kTowerWords + (int64_t)ppc * kPushWords + 4 * (int64_t)pc +
+              2 * (kMaxColours + 1) + 16 + kRing + 2 * kPhases;
+  if (mode >= 1) w += (int64_t)pc * kWarmWords;
+  if (mode == 2) w += kStageWords + 6 * (int64_t)nbp + 2 * (int64_t)pc + 3 * (int64_t)tpc;
+  return w;
+}
 // what a one-wave pack keeps in its device block instead (after kManPackWords per slot)
 inline int64_t pack_store_words(int nbp, int pc, int mode) {
   return (mode >= 1 ? (int64_t)pc * (kWarmWords - 1) : 0) + (mode == 2 ? 6 * (int64_t)nbp + 2 * (int64_t)pc : 0);

@@ -270,10 +270,11 @@ int32_t build_layout(jg_world* w) {
   const bool pairs = jg::pairs_on_chip(mode, w->prm.record_features != 0);
   auto pc_of = [&](int nb) { return std::max(16, (int)std::ceil(mpb * nb)); };
   int lat = 0;   // threads of a small batch's workgroups
-  auto layout_bytes = [&](int nb, int towers, int pushes, bool lists) -> size_t {
-    return (size_t)jg::lds_words(nb, pc_of(nb), std::max(1, towers), std::max(1, pushes), mode, lists, pairs) * 4;
+  // LDS of a pack stepped by one wave, or by `threads` threads
+  auto lds_of = [&](int nb, int towers, int pushes, int threads) -> size_t {
+    return (size_t)(jg::lds_words(nb, pc_of(nb), std::max(1, towers), std::max(1, pushes), mode, threads != 0, pairs) +
+                    (threads ? jg::lat_words(nb, threads) : 0)) * 4;
   };
-  auto lds_of = [&](int nb, int towers, int pushes) { return layout_bytes(nb, towers, pushes, lat != 0); };
   // workgroups with that much LDS to a CU (it is allocated in pieces of 1,280 bytes: ten of 15,360, nine of 15,368)
   auto per_cu_lds = [](size_t bytes) { return (int)((160 * 1024) / std::max<size_t>(1280, (bytes + 1279) / 1280 * 1280)); };
   // an on-chip pack holds at most kRegBodies bodies (the register broadphase); larger islands
@@ -287,7 +288,7 @@ int32_t build_layout(jg_world* w) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, w->prm.device) != hipSuccess) cus = 0;
   if (target <= 0) {
-    auto per_cu_of = [&](int nb) { return std::min(reg_packs, per_cu_lds(lds_of(nb, 4, w->pushes.empty() ? 1 : 8))); };
+    auto per_cu_of = [&](int nb) { return std::min(reg_packs, per_cu_lds(lds_of(nb, 4, w->pushes.empty() ? 1 : 8, 0))); };
     target = 8;   // bodies of a pack as the LDS allows with every wave that the registers do
     while (target < jg::kRegBodies && per_cu_of(target + 1) >= reg_packs) ++target;
     if (cus > 0 && (int64_t)order.size() <= (int64_t)cus * (wide ? 4 : 8)) {
@@ -362,14 +363,15 @@ int32_t build_layout(jg_world* w) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
     return w->tower_bodies[a].size() > w->tower_bodies[b].size();
   });
-  struct Bin { int bodies = 0, cap = 0; std::vector<int> towers; bool global = false; };
+  struct Bin { int bodies = 0, cap = 0, lat = 0; std::vector<int> towers; bool global = false; };
   std::vector<Bin> bins;
   std::vector<int> tower_pushes(T, 0);
   for (const auto& pr : w->pushes) ++tower_pushes[w->body_tower[pr.body]];
   for (int t : order) {
     const int n = (int)w->tower_bodies[t].size();
     // an island beyond the LDS path (register broadphase windows, or LDS) is a global pack
-    if (n > jg::kRegBodies || layout_bytes(n, 1, tower_pushes[t], true) > 160 * 1024 || w->prm.pack_bodies < 0) {
+    if (n > jg::kRegBodies || w->prm.pack_bodies < 0 ||
+        jg::full_words(n, pc_of(n), 1, std::max(1, tower_pushes[t]), mode) * 4 > 160 * 1024) {
       Bin b;
       b.bodies = n; b.cap = n; b.towers.push_back(t); b.global = true;
       bins.push_back(b);
@@ -380,7 +382,13 @@ int32_t build_layout(jg_world* w) {
       if (!b.global && b.bodies + n <= b.cap && (int)b.towers.size() < 255) {
         b.towers.push_back(t); b.bodies += n; placed = true; break;
       }
-    if (!placed) { Bin b; b.bodies = n; b.cap = std::max(target, n); b.towers.push_back(t); bins.push_back(b); }
+    if (!placed) {
+      Bin b;
+      b.bodies = n; b.cap = std::max(target, n); b.towers.push_back(t);
+      // (a small batch's tower whose waves' shared words do not fit beside it is stepped by one wave)
+      if (lat && lds_of(n, 1, tower_pushes[t], lat) <= 160 * 1024) b.lat = lat;
+      bins.push_back(b);
+    }
   }
   std::stable_sort(bins.begin(), bins.end(), [](const Bin& a, const Bin& b) { return a.bodies > b.bodies; });
   // group packs by how many fit a CU (their LDS), largest LDS first, so that each launch class
@@ -390,8 +398,10 @@ int32_t build_layout(jg_world* w) {
     for (size_t b = 0; b < bins.size(); ++b) {
       int pushes = 0;
       for (int t : bins[b].towers) pushes += tower_pushes[t];
-      key[b] = bins[b].global ? (1 << 30)   // global packs last, one class of their own
-                              : per_cu_lds(lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes));
+      // (global packs last, one class of their own; before them one-wave packs of a small batch)
+      key[b] = bins[b].global ? (1 << 30)
+                              : per_cu_lds(lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes, bins[b].lat)) +
+                                    (lat && !bins[b].lat ? 1 << 20 : 0);
     }
     std::vector<size_t> idx(bins.size());
     for (size_t b = 0; b < idx.size(); ++b) idx[b] = b;
@@ -434,17 +444,18 @@ int32_t build_layout(jg_world* w) {
     w->pack_tower0.push_back((int)w->tower_order.size());
     w->pack_push0.push_back((int)w->push_order.size());
     // launch class: packs that fit the same number of workgroups per CU (global packs: one class)
-    const size_t lds = lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes);
+    const size_t lds = lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes, bins[b].lat);
     const int per_cu = bins[b].global ? 0 : std::min(reg_packs, per_cu_lds(lds));
     if (!bins[b].global && per_cu == 0)
       return fail(JG_ECAPACITY, "a pack needs " + std::to_string(lds) + " bytes of LDS (max 163840); "
                                 "use smaller towers or fewer manifolds per body");
-    if (w->classes.empty() || w->classes.back().per_cu != per_cu || w->classes.back().global != bins[b].global) {
+    if (w->classes.empty() || w->classes.back().per_cu != per_cu || w->classes.back().global != bins[b].global ||
+        w->classes.back().lat != bins[b].lat) {
       jg_world::PackClass c;
       c.first = (int)b;
       c.per_cu = per_cu;
       c.global = bins[b].global;
-      c.lat = bins[b].global ? 0 : lat;
+      c.lat = bins[b].lat;
       w->classes.push_back(c);
     }
     jg_world::PackClass& c = w->classes.back();
@@ -478,7 +489,7 @@ int32_t build_layout(jg_world* w) {
   int packs = 0;
   for (const auto& c : w->classes) packs += c.global || c.lat ? 0 : c.count;
   w->many = cus > 0 && reg_packs > 8 && packs > 8 * cus;
-  if (cus > 0 && packs > 0) {
+  if (cus > 0 && packs > 0 && !lat) {
     jg_world::PackClass all = w->classes[0];
     size_t n = 0;
     for (; n < w->classes.size() && !w->classes[n].global; ++n) {
@@ -487,7 +498,7 @@ int32_t build_layout(jg_world* w) {
       all.tpc = std::max(all.tpc, c.tpc);
       all.ppc = std::max(all.ppc, c.ppc);
     }
-    if (n > 1 && packs <= cus * std::min(reg_packs, per_cu_lds(lds_of(all.nbp, all.tpc, all.ppc)))) {
+    if (n > 1 && packs <= cus * std::min(reg_packs, per_cu_lds(lds_of(all.nbp, all.tpc, all.ppc, 0)))) {
       all.count = packs;
       w->classes.erase(w->classes.begin() + 1, w->classes.begin() + (long)n);
       w->classes[0] = all;
@@ -505,7 +516,7 @@ int32_t build_layout(jg_world* w) {
                         from.per_cu >= reg_cap;
       const int nbp = std::max(into.nbp, from.nbp), tpc = std::max(into.tpc, from.tpc),
                 ppc = std::max(into.ppc, from.ppc);
-      if (same && per_cu_lds(lds_of(nbp, tpc, ppc)) >= reg_cap) {
+      if (same && per_cu_lds(lds_of(nbp, tpc, ppc, into.lat)) >= reg_cap) {
         into.count += from.count;
         into.nbp = nbp;
         into.tpc = tpc;
@@ -524,9 +535,12 @@ int32_t build_layout(jg_world* w) {
     return n;
   };
   while (lds_classes() > 4) {
-    size_t k = 1;
-    for (size_t i = 2; i < w->classes.size(); ++i)
-      if (!w->classes[i].global && w->classes[i].count < w->classes[k].count) k = i;
+    size_t k = 0;
+    for (size_t i = 1; i < w->classes.size(); ++i)
+      if (!w->classes[i].global && w->classes[i].lat == w->classes[i - 1].lat &&
+          (k == 0 || w->classes[i].count < w->classes[k].count))
+        k = i;
+    if (k == 0) break;
     jg_world::PackClass& into = w->classes[k - 1];
     const jg_world::PackClass& from = w->classes[k];
     into.count += from.count;
@@ -553,7 +567,7 @@ int32_t build_layout(jg_world* w) {
                   jg::window_words(c.nbp) + (2 + 4) * (int64_t)jg::kCandPerBody * c.nbp + 3 + 31) & ~(int64_t)31;   // (whole lines)
       for (int k = 0; k < c.count; ++k) { goff.push_back(gtotal); gtotal += c.gwords; }
     } else {
-      c.lds = (size_t)(jg::lds_words(c.nbp, c.pc, c.tpc, c.ppc, mode, c.lat != 0, pairs) + (c.lat ? jg::lat_words(c.nbp, c.lat) : 0)) * 4;
+      c.lds = lds_of(c.nbp, c.tpc, c.ppc, c.lat);
       if (c.lds > 160 * 1024)
         return fail(JG_ECAPACITY, "a launch class needs " + std::to_string(c.lds) + " bytes of LDS (max 163840)");
       c.gwords = ((int64_t)jg::kManPackWords * c.pc + (c.lat ? jg::lat_dev_words(c.pc, c.lat) : jg::pack_store_words(c.nbp, c.pc, mode)) + 31) & ~(int64_t)31;

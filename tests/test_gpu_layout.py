@@ -1,0 +1,51 @@
+"""Which route a batch takes and the LDS that it is launched with: what fits a workgroup is stepped, to the
+same bits on every route, whatever the manifold capacity and however many pushes a tower has."""
+import numpy as np
+import pytest
+
+from paper_2606_28394_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def J():
+    from paper_2606_28394_amd import jenga
+    jenga.load_library()
+    return jenga
+
+
+def _towers(levels, pushes=None, seed=90):
+    """Upright towers; pushes[t] rows of no force on tower t's bodies in turn (they only take room)."""
+    sb = W.SceneBuilder(W.default_params(), 4)
+    for t, n in enumerate(levels):
+        he, m, pos, quat, _, _ = W.jenga_tower(n, W.rng_for(seed, t))
+        b0 = sum(3 * k for k in levels[:t])
+        sb.add_tower(he, m, pos, quat, 0.4)
+        for r in range((pushes or [0] * len(levels))[t]):
+            sb.add_push(b0 + r % (3 * n), [0.0, 0.0, 0.0], 0, 4)
+    return sb.build()
+
+
+def _after(J, sc, steps=3, **kw):
+    w = J.World(sc, **kw)
+    w.step(steps)
+    st = w.stats()
+    assert st.error_word == 0
+    out = [np.asarray(x) for x in w.state()] + [np.asarray([st.candidates, st.manifolds, st.points, st.colours])]
+    w.close()
+    return out
+
+
+# (previous-step starts: the widest layout of a small batch)
+@pytest.mark.parametrize("levels,pushes,kw", [
+    ([70], None, {"manifolds_per_body": 8.0}),        # fits LDS without the small batch's shared words only
+    ([58, 8], None, {"manifolds_per_body": 10.0}),
+    ([85], [40], {}),                                 # the same at the default capacity
+    ([85], [1060], {"manifolds_per_body": 4.0}),      # on chip, but not with the shared words: one wave
+])
+def test_towers_at_the_lds_limit_are_stepped(J, levels, pushes, kw):
+    a = _after(J, _towers(levels, pushes), warm_start=1, **kw)
+    b = _after(J, _towers(levels), warm_start=1, small_batch=-1)
+    for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
