@@ -424,6 +424,9 @@ int32_t build_layout(jg_world* w) {
   w->pack_slot0.assign(1, 0);
   w->push_order.clear();
   w->classes.clear();
+  auto fits_launch = [&](const jg_world::PackClass& c, int nb, int towers, int pushes) {
+    return c.global || lds_of(std::max(c.nbp, nb), std::max(c.tpc, towers), std::max(c.ppc, pushes), c.lat) <= 160 * 1024;
+  };
   std::vector<std::vector<int>> push_of_body(N);
   for (size_t r = 0; r < w->pushes.size(); ++r) push_of_body[w->pushes[r].body].push_back((int)r);
   for (size_t b = 0; b < bins.size(); ++b) {
@@ -443,14 +446,16 @@ int32_t build_layout(jg_world* w) {
     w->pack_body0.push_back((int)w->body_of_int.size());
     w->pack_tower0.push_back((int)w->tower_order.size());
     w->pack_push0.push_back((int)w->push_order.size());
-    // launch class: packs that fit the same number of workgroups per CU (global packs: one class)
+    // launch class: packs that fit the same number of workgroups per CU (global packs: one class), as long as a
+    // workgroup of the most bodies, towers and pushes among them fits
     const size_t lds = lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes, bins[b].lat);
     const int per_cu = bins[b].global ? 0 : std::min(reg_packs, per_cu_lds(lds));
     if (!bins[b].global && per_cu == 0)
       return fail(JG_ECAPACITY, "a pack needs " + std::to_string(lds) + " bytes of LDS (max 163840); "
                                 "use smaller towers or fewer manifolds per body");
     if (w->classes.empty() || w->classes.back().per_cu != per_cu || w->classes.back().global != bins[b].global ||
-        w->classes.back().lat != bins[b].lat) {
+        w->classes.back().lat != bins[b].lat ||
+        !fits_launch(w->classes.back(), bins[b].bodies, (int)bins[b].towers.size(), pushes)) {
       jg_world::PackClass c;
       c.first = (int)b;
       c.per_cu = per_cu;
@@ -538,6 +543,7 @@ int32_t build_layout(jg_world* w) {
     size_t k = 0;
     for (size_t i = 1; i < w->classes.size(); ++i)
       if (!w->classes[i].global && w->classes[i].lat == w->classes[i - 1].lat &&
+          fits_launch(w->classes[i - 1], w->classes[i].nbp, w->classes[i].tpc, w->classes[i].ppc) &&
           (k == 0 || w->classes[i].count < w->classes[k].count))
         k = i;
     if (k == 0) break;

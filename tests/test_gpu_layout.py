@@ -49,3 +49,14 @@ def test_towers_at_the_lds_limit_are_stepped(J, levels, pushes, kw):
     b = _after(J, _towers(levels), warm_start=1, small_batch=-1)
     for x, y in zip(a, b):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("levels,pushes,kw", [
+    ([84, 8], [0, 100], {}),      # one's bodies and the other's pushes are more than a workgroup's LDS
+    ([83, 60, 8, 8, 8, 8, 8], [0, 40, 0, 300, 700, 1100, 2100], {}),
+])
+def test_towers_that_fit_alone_are_stepped_together(J, levels, pushes, kw):
+    a = _after(J, _towers(levels, pushes), warm_start=1, **kw)
+    b = _after(J, _towers(levels), warm_start=1, pack_bodies=-1)
+    for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
