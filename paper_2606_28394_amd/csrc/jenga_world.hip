@@ -363,7 +363,7 @@ int32_t build_layout(jg_world* w) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
     return w->tower_bodies[a].size() > w->tower_bodies[b].size();
   });
-  struct Bin { int bodies = 0, cap = 0, lat = 0; std::vector<int> towers; bool global = false; };
+  struct Bin { int bodies = 0, cap = 0, lat = 0, pushes = 0; std::vector<int> towers; bool global = false; };
   std::vector<Bin> bins;
   std::vector<int> tower_pushes(T, 0);
   for (const auto& pr : w->pushes) ++tower_pushes[w->body_tower[pr.body]];
@@ -379,12 +379,13 @@ int32_t build_layout(jg_world* w) {
     }
     bool placed = false;
     for (auto& b : bins)
-      if (!b.global && b.bodies + n <= b.cap && (int)b.towers.size() < 255) {
-        b.towers.push_back(t); b.bodies += n; placed = true; break;
+      if (!b.global && b.bodies + n <= b.cap && (int)b.towers.size() < 255 &&
+          lds_of(b.bodies + n, (int)b.towers.size() + 1, b.pushes + tower_pushes[t], b.lat) <= 160 * 1024) {
+        b.towers.push_back(t); b.bodies += n; b.pushes += tower_pushes[t]; placed = true; break;
       }
     if (!placed) {
       Bin b;
-      b.bodies = n; b.cap = std::max(target, n); b.towers.push_back(t);
+      b.bodies = n; b.cap = std::max(target, n); b.pushes = tower_pushes[t]; b.towers.push_back(t);
       // (a small batch's tower whose waves' shared words do not fit beside it is stepped by one wave)
       if (lat && lds_of(n, 1, tower_pushes[t], lat) <= 160 * 1024) b.lat = lat;
       bins.push_back(b);
@@ -396,11 +397,9 @@ int32_t build_layout(jg_world* w) {
   {
     std::vector<int> key(bins.size());
     for (size_t b = 0; b < bins.size(); ++b) {
-      int pushes = 0;
-      for (int t : bins[b].towers) pushes += tower_pushes[t];
       // (global packs last, one class of their own; before them one-wave packs of a small batch)
       key[b] = bins[b].global ? (1 << 30)
-                              : per_cu_lds(lds_of(bins[b].bodies, (int)bins[b].towers.size(), pushes, bins[b].lat)) +
+                              : per_cu_lds(lds_of(bins[b].bodies, (int)bins[b].towers.size(), bins[b].pushes, bins[b].lat)) +
                                     (lat && !bins[b].lat ? 1 << 20 : 0);
     }
     std::vector<size_t> idx(bins.size());

@@ -60,3 +60,10 @@ def test_towers_that_fit_alone_are_stepped_together(J, levels, pushes, kw):
     b = _after(J, _towers(levels), warm_start=1, pack_bodies=-1)
     for x, y in zip(a, b):
         np.testing.assert_array_equal(x, y)
+
+
+def test_shared_packs_hold_their_pushes(J):
+    """Ten towers would share a pack of 250 bodies, but not with 450 pushes each."""
+    a = _after(J, _towers([8] * 10, [450] * 10), pack_bodies=250)
+    for x, y in zip(a, _after(J, _towers([8] * 10))):
+        np.testing.assert_array_equal(x, y)
