@@ -107,6 +107,7 @@ struct StepArgs {
   int64_t step0;
   // capacities of this launch (LDS layout)
   int32_t lat;     // small batches: threads of the workgroup that steps one tower (0: not one)
+  int32_t waves;   // packs in device memory: waves of a workgroup
   int32_t many;    // one-wave packs: more than two to a SIMD of the GPU
   int32_t nbp;     // bodies per pack
   int32_t pc;      // manifolds per pack
@@ -132,6 +133,7 @@ constexpr int kManListWords = 4;   // a one-wave pack's canonical pairs (kManWor
 constexpr int kManPackWords = kManDevWords + kManBiasWords + kManSatWords + kManPairWords + kManListWords;   // per slot of a pack
 constexpr int kWarmWords = 18;     // sorted -> canonical map + previous step store (17)
 constexpr int kStageWords = 64 * 16 + 64 * 3;   // network input rows of one 64-point chunk (bf16)
+constexpr int kIslandWaves = 8;                 // waves of a pack in device memory
 constexpr int kLearnedIslandWaves = 4;          // waves of a pack in device memory with the network
                                                 // and the chunk's previous dimensionless impulses
 constexpr int kFeatRecord = 30;
@@ -155,16 +157,22 @@ __host__ __device__ inline int64_t window_words(int nbp) { return 6 * (int64_t)(
 constexpr int kCandPerBody = 16;
 
 // LDS words of a pack kept in device memory: its small arrays (phase counters, colour offsets,
-// the candidate ring, towers, pushes, broadphase windows) and, with `bodies`, the body arrays
-// that the serial walks (broadphase, colouring) read: positions, AABB half sizes and colour
-// masks, flags, colouring lane masks (9 words per body)
+// towers, pushes, broadphase windows, its waves' list starts and colour counts) and, with `bodies`,
+// the body arrays that the serial walks (broadphase, colouring) read: positions, AABB half sizes and
+// colour masks, flags (7 words per body), and the broadphase's counts and starts (2), whose place the
+// waves' colour counts take afterwards.  A pack with so many pushes that the counts of all its waves do
+// not fit runs fewer waves: with one it needs no more than its pushes leave.
 constexpr int kMostWaves = 8;     // waves of a workgroup that share a step
-constexpr int kWaveWords = kMostWaves * kMaxColours + 3 * (kMostWaves + 1);   // their colour counts and list starts
-constexpr int kHotBodyWords = 9;
-__host__ __device__ inline int64_t hot_words(int nbp, int tpc, int ppc, bool bodies) {
-  int64_t w = 2 * kPhases + 2 * (kMaxColours + 1) + 16 + kRing + (int64_t)tpc * kTowerWords +
-              (int64_t)ppc * kPushWords + window_words(nbp) + kWaveWords;
-  if (bodies) w += (int64_t)kHotBodyWords * nbp;
+constexpr int kSegWords = 3 * (kMostWaves + 1);   // their list starts
+constexpr int kHotBodyWords = 7;
+__host__ __device__ inline int shared_count_words(int nbp, int waves) {
+  return 2 * nbp > waves * kMaxColours ? 2 * nbp : waves * kMaxColours;
+}
+inline int64_t hot_words(int nbp, int tpc, int ppc, bool bodies, int waves) {
+  int64_t w = 2 * kPhases + 2 * (kMaxColours + 1) + 16 + kSegWords + (int64_t)tpc * kTowerWords +
+              (int64_t)ppc * kPushWords + window_words(nbp);
+  if (bodies) w += (int64_t)kHotBodyWords * nbp + shared_count_words(nbp, waves);
+  else w += (int64_t)waves * kMaxColours;
   return w;
 }
 

@@ -49,7 +49,6 @@ namespace jg {
 namespace {
 
 constexpr uint32_t kGround = 0xffffu;
-constexpr int kIslandWaves = 8;   // waves of a workgroup that steps an island in device memory
 constexpr int kLatencyWaves = 8;  // most waves of a workgroup that steps one tower of a small batch
 
 // A barrier among the lanes of one wave, all that a pack's steps need: LDS and device-memory
@@ -223,7 +222,7 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
     L.cyc = (unsigned long long*)htake(2 * kPhases);   // first: 8-byte aligned
     L.coloff = (int32_t*)htake(kMaxColours + 1); L.colcnt = (int32_t*)htake(kMaxColours + 1);
     L.scal = (int32_t*)htake(16);
-    L.ring = (uint32_t*)htake(kRing);
+    L.seg = (int32_t*)htake(kSegWords);
     L.tb0 = (int32_t*)htake(nt); L.tb1 = (int32_t*)htake(nt); L.mu = htake(nt);
     L.tcnt = (uint32_t*)htake(4 * nt); L.tres = htake(2 * nt);
     L.tc0 = (int32_t*)htake(nt); L.tc1 = (int32_t*)htake(nt); L.tpts = (int32_t*)htake(nt);
@@ -231,11 +230,13 @@ __device__ __forceinline__ Lds carve(float* base, float* dev, float* hot, bool u
     L.pb = (int32_t*)htake(np); L.ps = (int32_t*)htake(np); L.pn = (int32_t*)htake(np);
     L.pf = htake(3 * np); L.pwd = htake(np); L.px0 = htake(3 * np);
     L.wbox = htake((int)window_words(nb));
-    L.wcol = (int32_t*)htake(kMostWaves * kMaxColours);
-    L.seg = (int32_t*)htake(3 * (kMostWaves + 1));
     if (hot_bodies) {
       L.x = htake(3 * nb); L.hm = htake(3 * nb); L.flag = (uint32_t*)htake(nb);
-      L.lmlo = (uint32_t*)htake(nb); L.lmhi = (uint32_t*)htake(nb);
+      // (the broadphase's counts and starts are done with before the colours are counted)
+      L.wcol = (int32_t*)htake(shared_count_words(nb, a.waves));
+      L.lmlo = (uint32_t*)L.wcol; L.lmhi = L.lmlo + nb;
+    } else {
+      L.wcol = (int32_t*)htake(a.waves * kMaxColours);
     }
   }
   return L;
@@ -4717,10 +4718,10 @@ int step_launch_config(const StepArgs& a, const void** func, unsigned* block_thr
   if (learned) {
     *func = !a.in_gmem ? step_variant_learned_pack()
                        : (a.hot_bodies ? step_variant_learned_island_hot() : step_variant_learned_island());
-    if (a.in_gmem) threads = step_threads<true, true>();
+    if (a.in_gmem) threads = (unsigned)(a.waves * kWave);
   } else if (a.in_gmem) {
     *func = step_variant_island(a.hot_bodies != 0, ext);
-    threads = step_threads<false, true>();
+    threads = (unsigned)(a.waves * kWave);
   } else if (a.lat) {
     *func = step_variant_lat(ext);
     threads = (unsigned)a.lat;

@@ -94,6 +94,7 @@ struct jg_world {
     bool global = false;     // packs keep their state in device memory (islands too large for LDS)
     bool hot_bodies = false; // global packs: the serial walks' body arrays in LDS
     int lat = 0;             // threads of a workgroup that steps one tower (small batches; 0: not one)
+    int waves = 0;           // global packs: waves of a workgroup
     int64_t gwords = 0;      // words of one pack's device region
   };
   std::vector<PackClass> classes;   // launch classes, in pack order
@@ -561,8 +562,10 @@ int32_t build_layout(jg_world* w) {
     c.pc = pc_of(c.nbp);
     if (c.global) {
       // small arrays in LDS always; the serial walks' body arrays too when they fit
-      c.hot_bodies = jg::hot_words(c.nbp, c.tpc, c.ppc, true) * 4 <= 160 * 1024;
-      c.lds = (size_t)jg::hot_words(c.nbp, c.tpc, c.ppc, c.hot_bodies) * 4;
+      c.waves = wide ? jg::kLearnedIslandWaves : jg::kIslandWaves;
+      c.hot_bodies = jg::hot_words(c.nbp, c.tpc, c.ppc, true, c.waves) * 4 <= 160 * 1024;
+      while (c.waves > 1 && jg::hot_words(c.nbp, c.tpc, c.ppc, c.hot_bodies, c.waves) * 4 > 160 * 1024) --c.waves;
+      c.lds = (size_t)jg::hot_words(c.nbp, c.tpc, c.ppc, c.hot_bodies, c.waves) * 4;
       if (c.lds > 160 * 1024)
         return fail(JG_ECAPACITY, "a pack kept in device memory needs " + std::to_string(c.lds) +
                                   " bytes of LDS for its towers and pushes (max 163840)");
@@ -1185,6 +1188,7 @@ int32_t jg_step_batch(jg_world* w, int32_t n_steps) {
     cls[k].in_gmem = c.global ? 1 : 0;
     cls[k].hot_bodies = c.hot_bodies ? 1 : 0;
     cls[k].lat = c.lat;
+    cls[k].waves = c.waves;
     cls[k].many = w->many ? 1 : 0;
     cls[k].pack_goff = w->d_pack_goff.p;
   }

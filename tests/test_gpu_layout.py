@@ -1,11 +1,14 @@
 """Which route a batch takes and the LDS that it is launched with: what fits a workgroup is stepped, to the
 same bits on every route, whatever the manifold capacity and however many pushes a tower has."""
+import os
+
 import numpy as np
 import pytest
 
 from paper_2606_28394_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+NET = os.path.join(os.path.dirname(W.__file__), "data", "warmstart_mlp.npy")
 
 
 @pytest.fixture(scope="module")
@@ -66,4 +69,14 @@ def test_shared_packs_hold_their_pushes(J):
     """Ten towers would share a pack of 250 bodies, but not with 450 pushes each."""
     a = _after(J, _towers([8] * 10, [450] * 10), pack_bodies=250)
     for x, y in zip(a, _after(J, _towers([8] * 10))):
+        np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("pushes,start", [(4050, 0), (4062, 1), (4062, 2)])
+def test_islands_hold_as_many_pushes_as_lds(J, pushes, start):
+    """An island's push rows leave LDS for some of its waves' words only: it runs fewer of them."""
+    kw = dict(warm_start=start)
+    if start == 2:
+        kw.update(mlp=np.load(NET), mlp_iters=4)
+    for x, y in zip(_after(J, _towers([100], [pushes]), **kw), _after(J, _towers([100]), **kw)):
         np.testing.assert_array_equal(x, y)
