@@ -269,7 +269,8 @@ int32_t build_layout(jg_world* w) {
   float mpb = w->prm.manifolds_per_body > 0.f ? w->prm.manifolds_per_body : 3.5f;
   const int mode = w->prm.warm_start == 2 ? 2 : ((w->prm.warm_start == 1 || w->prm.record_features) ? 1 : 0);
   const bool pairs = jg::pairs_on_chip(mode, w->prm.record_features != 0);
-  auto pc_of = [&](int nb) { return std::max(16, (int)std::ceil(mpb * nb)); };
+  int pool = 16;   // manifold slots that every pack has
+  auto pc_of = [&](int nb) { return std::max(pool, (int)std::ceil(mpb * nb)); };
   int lat = 0;   // threads of a small batch's workgroups
   // LDS of a pack stepped by one wave, or by `threads` threads
   auto lds_of = [&](int nb, int towers, int pushes, int threads) -> size_t {
@@ -310,6 +311,13 @@ int32_t build_layout(jg_world* w) {
       // steps of falling towers of 24 to 120 boxes: 4,096 of them 2.01 ms in one round of packs of 120,
       // 2.69 in two of 52; two steps of 3,000 towers of 36 to 72 with the network 3.03 in one round
       // of 180, 3.34 in two of 98, 3.62 in three of 72.
+      // A small pack has the slots of one that fills 20 KB (40 KB with the network) with every pair's words on
+      // chip, so that a tower that collapses alone or beside few others has room for its pairs (389 with the
+      // zero start; at 3.5 per body a tower of 54 bodies alone would have 189).
+      const int64_t budget = (wide ? 40 : 20) * 1024;
+      int held = 8;
+      while (held < jg::kRegBodies && jg::full_words(held + 1, pc_of(held + 1), 4, 8, mode) * 4 <= budget) ++held;
+      pool = pc_of(held);
       std::vector<int64_t> sizes(jg::kRegBodies + 1, 0);
       int64_t bodies = 0;
       int largest = 1;

@@ -80,3 +80,28 @@ def test_islands_hold_as_many_pushes_as_lds(J, pushes, start):
         kw.update(mlp=np.load(NET), mlp_iters=4)
     for x, y in zip(_after(J, _towers([100], [pushes]), **kw), _after(J, _towers([100]), **kw)):
         np.testing.assert_array_equal(x, y)
+
+
+def _heaps(n, dense):
+    """Towers of 54 cubes: three by three by six of them pressed together (365 pairs) or apart (none)."""
+    k = np.stack(np.meshgrid(range(3), range(3), range(6), indexing="ij"), -1).reshape(-1, 3)
+    sb = W.SceneBuilder(W.default_params(), 1)
+    for t in range(n):
+        pos = k * (0.0199 if dense(t) else 0.1) + [0.0, 0.0, 0.5]
+        sb.add_tower(np.full((54, 3), 0.01), np.full(54, 0.01), pos, np.tile([1.0, 0, 0, 0], (54, 1)), 0.4)
+    return sb.build()
+
+
+def test_a_batch_in_shared_packs_has_room_for_a_heap(J):
+    """2,100 towers, just more than get a workgroup each: a heap beside a tower without contacts has 365 pairs."""
+    w = J.World(_heaps(2100, lambda t: t < 40 and t % 2 == 0))
+    w.step(1)
+    assert w.stats().error_word == 0
+    assert [w.stats(t).manifolds for t in range(0, 40, 2)] == [365] * 20
+    state = [x[:54] for x in w.state()]
+    w.close()
+    alone = J.World(_heaps(1, lambda t: True), manifolds_per_body=8.0)
+    alone.step(1)
+    for x, y in zip(state, alone.state()):
+        np.testing.assert_array_equal(x, y)
+    alone.close()
