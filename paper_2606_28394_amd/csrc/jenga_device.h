@@ -108,7 +108,7 @@ struct StepArgs {
   // capacities of this launch (LDS layout)
   int32_t lat;     // small batches: threads of the workgroup that steps one tower (0: not one)
   int32_t waves;   // packs in device memory: waves of a workgroup
-  int32_t many;    // one-wave packs: more than two to a SIMD of the GPU
+  int32_t many;    // one-wave packs: three to a SIMD
   int32_t nbp;     // bodies per pack
   int32_t pc;      // manifolds per pack
   int32_t tpc;     // towers per pack

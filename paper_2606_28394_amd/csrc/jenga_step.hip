@@ -2703,9 +2703,8 @@ constexpr int step_threads() {
 // either compiles to flat instructions, which are as slow as device memory even on LDS).
 // kExt: the solver variants (disc friction, restitution targets, reference-face clipping) and the
 // episode criteria are compiled in; the default plain kernel carries none of their registers.
-// kMany: a batch of more packs than two waves per SIMD hold.  Three waves hide more of each other's latency
-// than the spills of a third fewer registers cost (16,384 falling towers: 8.98 ms for two steps, 7.95 with
-// three; of 1,500 towers, which are all resident either way, 2.00 and 2.12 ms).
+// kMany: three waves to a SIMD instead of two (the registers of a third spilled), where that saves rounds of
+// packs: twelve to a CU take 1.28 times as long as eight (jg_commit chooses, for the criteria's kernel too).
 template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false, bool kMany = false>
 __global__ void __launch_bounds__((step_threads<kLearned, kGlobal, kLat>()))
 __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel(StepArgs a) {
@@ -4651,7 +4650,9 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
 // The step kernel's variants, by part of the build (this file is compiled once per part, side by side)
 #if JG_STEP_PART == 1
 const void* step_variant_pack(bool ext, bool many) {
-  if (ext) return (const void*)step_kernel<false, false, false, true>;
+  if (ext)
+    return many ? (const void*)step_kernel<false, false, false, true, false, true>
+                : (const void*)step_kernel<false, false, false, true>;
   return many ? (const void*)step_kernel<false, false, false, false, false, true>
               : (const void*)step_kernel<false, false, false, false>;
 }
@@ -4690,9 +4691,9 @@ int ensure_lds_limit() {
   if (dev < 0 || dev >= kMaxDevices) return (int)hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(attr_mutex);
   if (!attr_set[dev]) {
-    const void* variants[13] = {(const void*)mega_kernel,
+    const void* variants[14] = {(const void*)mega_kernel,
                                 step_variant_pack(false, false),   step_variant_pack(false, true),
-                                step_variant_pack(true, false),
+                                step_variant_pack(true, false),    step_variant_pack(true, true),
                                 step_variant_lat(false),           step_variant_lat(true),
                                 step_variant_island(false, false), step_variant_island(false, true),
                                 step_variant_island(true, false),  step_variant_island(true, true),

@@ -178,7 +178,7 @@ struct jg_world {
     }
   };
   std::vector<Mega> megas;
-  bool many = false;                // more one-wave packs than two to a SIMD
+  bool many = false;                // one-wave packs three to a SIMD
   std::vector<int> mega_of_tower;   // tower id -> index in megas (-1: in a pack)
 };
 
@@ -282,17 +282,30 @@ int32_t build_layout(jg_world* w) {
   // an on-chip pack holds at most kRegBodies bodies (the register broadphase); larger islands
   // are kept in device memory, one tower each
   int target = w->prm.pack_bodies > 0 ? std::min(w->prm.pack_bodies, jg::kRegBodies) : 0;
-  // packs that the kernel's registers let a CU hold: the plain one three to a SIMD, the solver variants two,
-  // the network one
+  // packs that the kernel's registers let a CU hold: the plain one's two builds eight (two to a SIMD) and
+  // twelve, the solver variants' eight, the network's four
   const bool wide = w->prm.warm_start == 2 || w->prm.record_features;
   const bool variants = w->prm.friction_cone || w->prm.restitution_bias || w->prm.manifold_mode;
-  const int reg_packs = wide ? 4 : (variants ? 8 : 12);
+  const int few_packs = wide ? 4 : 8, many_packs = wide || variants ? few_packs : 12;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, w->prm.device) != hipSuccess) cus = 0;
+  // The packs run in rounds of what the GPU holds at once.  The time of `h` such rounds of one-wave packs, in
+  // rounds: one if they fit at once; else the last round costs 0.6 of a whole one as soon as it holds a pack,
+  // and packs that fill the rounds to the last place (0.8 %) start another: 8,192 towers of 36 to 72 boxes, four
+  // steps, 5.46 ms in 1.95 rounds, 7.08 in 2.00, 6.55 in 2.46 of smaller packs.
+  auto rounds = [](double h, bool once) {
+    if (once) return 1.0;
+    h = std::max(1.0, 1.008 * h);
+    return std::floor(h) + 0.6 + 0.4 * (h - std::floor(h));
+  };
+  // A round of twelve packs to a CU takes this much longer than one of eight of the same size: 4,096 such towers
+  // 2.72 ms in one round of packs of 108, eight to a CU, 3.03 in one of packs of 92; 8,192 5.46 in
+  // two of 111, 5.64 in two of 92; 4,096 falling towers of 24 to 120 boxes, two steps, 2.31 in one of 144,
+  // 2.13 in one of 120.
+  constexpr double kManyTime = 1.28;
   if (target <= 0) {
-    auto per_cu_of = [&](int nb) { return std::min(reg_packs, per_cu_lds(lds_of(nb, 4, w->pushes.empty() ? 1 : 8, 0))); };
     target = 8;   // bodies of a pack as the LDS allows with every wave that the registers do
-    while (target < jg::kRegBodies && per_cu_of(target + 1) >= reg_packs) ++target;
+    while (target < jg::kRegBodies && per_cu_lds(lds_of(target + 1, 4, w->pushes.empty() ? 1 : 8, 0)) >= many_packs) ++target;
     if (cus > 0 && (int64_t)order.size() <= (int64_t)cus * (wide ? 4 : 8)) {
       // A batch with no more towers than the GPU holds workgroups at once gets one tower per pack:
       // sharing a pack would only run towers one after another that could run side by side
@@ -304,13 +317,10 @@ int32_t build_layout(jg_world* w) {
       if (w->prm.small_batch >= 0 && !wide && (int64_t)order.size() <= 2 * (int64_t)cus)
         lat = (int64_t)order.size() <= (int64_t)cus ? 8 * jg::kWave : 4 * jg::kWave;
     } else if (cus > 0) {
-      // The packs run in rounds of what the GPU holds at once, and a last round that is nearly empty costs a
-      // whole one.  A pack's time grows with its bodies, from what 64 of them cost on; beyond 128 its colours
+      // A pack's time grows with its bodies, from what 64 of them cost on; beyond 128 its colours
       // have more manifolds than a wave has lanes.  With the network, most of the work is per
-      // point.  The size with the least rounds times that is taken (the largest of equals).  Measured, two
-      // steps of falling towers of 24 to 120 boxes: 4,096 of them 2.01 ms in one round of packs of 120,
-      // 2.69 in two of 52; two steps of 3,000 towers of 36 to 72 with the network 3.03 in one round
-      // of 180, 3.34 in two of 98, 3.62 in three of 72.
+      // point: two steps of 3,000 towers of 36 to 72 boxes 3.03 ms in one round of packs of 180, 3.34 in two
+      // of 98, 3.62 in three of 72.  The size with the least rounds times that is taken (the largest of equals).
       // A small pack has the slots of one that fills 20 KB (40 KB with the network) with every pair's words on
       // chip, so that a tower that collapses alone or beside few others has room for its pairs (389 with the
       // zero start; at 3.5 per body a tower of 54 bodies alone would have 189).
@@ -328,44 +338,60 @@ int32_t build_layout(jg_world* w) {
         bodies += n;
         largest = std::max(largest, n);
       }
-      // the towers in packs of at most `cap` bodies, largest first, each where it fits tightest: their number,
-      // and the CUs that hold them all at once
-      auto fill = [&](int cap, int64_t& packs, double& held) {
-        std::vector<int64_t> left(cap + 1, 0);   // packs by the bodies that they still take
-        packs = 0;
-        held = 0.0;
+      std::vector<int> fit(jg::kRegBodies + 1, 1);   // packs of so many bodies that a CU's LDS holds
+      for (int n = 1; n <= jg::kRegBodies; ++n) fit[n] = per_cu_lds(lds_of(n, 4, w->pushes.empty() ? 1 : 8, 0));
+      // the towers in packs of at most `cap` bodies, largest first, each where it fits tightest: packs by the
+      // bodies that they still take, and their number
+      std::vector<int64_t> left;
+      auto fill = [&](int cap) {
+        left.assign(cap + 1, 0);
+        uint64_t some[jg::kRegBodies / 64 + 1] = {};   // bit r: left[r] > 0
+        auto first = [&](int r) {   // the first such r' >= r (beyond cap: none)
+          for (int k = r / 64; k <= cap / 64; ++k) {
+            const uint64_t m = some[k] & (k == r / 64 ? ~0ull << (r % 64) : ~0ull);
+            if (m) return 64 * k + __builtin_ctzll(m);
+          }
+          return cap + 1;
+        };
+        auto add = [&](int r, int64_t k) {
+          left[r] += k;
+          if (left[r]) some[r / 64] |= 1ull << (r % 64);
+          else some[r / 64] &= ~(1ull << (r % 64));
+        };
+        int64_t packs = 0;
         for (int n = jg::kRegBodies; n >= 1; --n) {
           int64_t c = sizes[n];
-          for (int r = n; r <= cap && c > 0;) {
-            const int64_t k = std::min(c, left[r]);
-            left[r] -= k;
-            left[r - n] += k;
-            c -= k;
-            r = k > 0 ? n : r + 1;   // (what is left of those may take another)
-          }
           if (c == 0) continue;
-          const int64_t each = std::max(1, cap / n), full = c / each, rest = c % each;
-          packs += full + (rest ? 1 : 0);
-          if (n <= cap) {
-            left[cap - (int)each * n] += full;
-            if (rest) left[cap - (int)rest * n] += 1;
-          } else {
-            held += (double)c / std::max(1, per_cu_of(n));
+          if (n > cap) { packs += c; continue; }
+          for (int r = first(n); r <= cap && c > 0; r = first(n)) {
+            const int64_t k = std::min(c, left[r]);
+            add(r, -k);
+            add(r - n, k);
+            c -= k;
           }
+          const int64_t each = cap / n, full = c / each, rest = c % each;
+          packs += full + (rest ? 1 : 0);
+          add(cap - (int)each * n, full);
+          if (rest) add(cap - (int)rest * n, 1);
         }
-        for (int r = 0; r <= cap; ++r) held += (double)left[r] / std::max(1, per_cu_of(cap - r));
+        return packs;
       };
       double best = 0.0;
-      for (int cap = 8; cap <= jg::kRegBodies && bodies > 0 && per_cu_of(cap) > 0; ++cap) {
-        int64_t packs = 0;
-        double held = 0.0;
-        fill(cap, packs, held);
+      for (int cap = 8; cap <= jg::kRegBodies && bodies > 0 && fit[cap] > 0; ++cap) {
+        const int64_t packs = fill(cap);
         const double size = (wide ? 28.0 : 64.0 + 2.0 * std::max(0, cap - 128)) + (double)bodies / (double)packs;
-        // (one round if the packs fit with the largest one's LDS each: CUs that hold packs of several sizes
-        // leave some of it)
-        const bool once = packs <= (int64_t)cus * per_cu_of(std::max(cap, largest));
-        const double cost = (once ? 1.0 : std::max(2.0, std::ceil(held / (double)cus))) * size;
-        if (best == 0.0 || cost <= best) { best = cost; target = cap; }
+        for (int most : {few_packs, many_packs}) {
+          auto per_cu = [&](int n) { return std::max(1, std::min(most, fit[n])); };
+          double held = 0.0;   // CUs that hold them all at once
+          for (int n = cap + 1; n <= jg::kRegBodies; ++n) held += (double)sizes[n] / per_cu(n);
+          for (int r = 0; r < cap; ++r) held += (double)left[r] / per_cu(cap - r);
+          // (one round if the packs fit with the largest one's LDS each: CUs that hold packs of several sizes
+          // leave some of it)
+          const bool once = packs <= (int64_t)cus * std::min(most, fit[std::max(cap, largest)]);
+          const double cost = rounds(held / (double)cus, once) * size * (most > few_packs ? kManyTime : 1.0);
+          if (best == 0.0 || cost < best || (cost == best && most == few_packs)) { best = cost; target = cap; }
+          if (most == many_packs) break;   // (one build)
+        }
       }
     }
   }
@@ -419,6 +445,27 @@ int32_t build_layout(jg_world* w) {
     for (size_t b : idx) sorted.push_back(std::move(bins[b]));
     bins.swap(sorted);
   }
+  // the plain kernel's build, by the same figures for the packs as they came out
+  int packs = 0;
+  {
+    double held[2] = {0.0, 0.0};
+    int nbp = 1, tpc = 1, ppc = 1;
+    for (const auto& b : bins) {
+      if (b.global || b.lat) continue;
+      const int fit = std::max(1, per_cu_lds(lds_of(b.bodies, (int)b.towers.size(), b.pushes, 0)));
+      held[0] += 1.0 / std::min(few_packs, fit);
+      held[1] += 1.0 / std::min(many_packs, fit);
+      nbp = std::max(nbp, b.bodies);
+      tpc = std::max(tpc, (int)b.towers.size());
+      ppc = std::max(ppc, b.pushes);
+      ++packs;
+    }
+    const int fit = per_cu_lds(lds_of(nbp, tpc, ppc, 0));
+    auto time = [&](double h, int most) { return rounds(h / cus, packs <= (int64_t)cus * std::min(most, fit)); };
+    w->many = many_packs > few_packs && cus > 0 && packs > 0 &&
+              kManyTime * time(held[1], many_packs) < time(held[0], few_packs);
+  }
+  const int reg_packs = w->many ? many_packs : few_packs;
   // internal order
   const int N = (int)w->he.size() / 3;
   w->int_of_body.assign(N, -1);
@@ -499,9 +546,6 @@ int32_t build_layout(jg_world* w) {
   }
   // One-wave packs that the GPU holds all at once, with the largest one's LDS each, are one launch (800 towers
   // of 24 to 120 boxes, two steps: 0.70 ms in the launches of three classes, 0.64 in one).
-  int packs = 0;
-  for (const auto& c : w->classes) packs += c.global || c.lat ? 0 : c.count;
-  w->many = cus > 0 && reg_packs > 8 && packs > 8 * cus;
   if (cus > 0 && packs > 0 && !lat) {
     jg_world::PackClass all = w->classes[0];
     size_t n = 0;

@@ -105,3 +105,26 @@ def test_a_batch_in_shared_packs_has_room_for_a_heap(J):
     for x, y in zip(state, alone.state()):
         np.testing.assert_array_equal(x, y)
     alone.close()
+
+
+@pytest.mark.parametrize("what,start", [("episodes", 0), ("episodes", 1), ("friction_cone", 0), ("restitution_bias", 1),
+                                        ("manifold_mode", 0), ("manifold_mode", 1)])
+def test_shared_packs_of_both_builds_give_the_same_bits(J, what, start):
+    """2,100 packs of one tower (with the criteria, three waves to a SIMD) and 420 of five (two)."""
+    sc = W.tilted_towers(5, 2100, levels_range=(8, 8), n_steps=8)
+    if what != "episodes":
+        sc = dict(sc, params=dict(sc["params"], **{what: 1}))
+    out = []
+    for bodies in (24, 120):
+        w = J.World(sc, warm_start=start, pack_bodies=bodies, manifolds_per_body=6.0)
+        if what == "episodes":
+            w.begin_episodes()
+        w.step(2)
+        w.step(2)
+        st = w.stats()
+        assert st.error_word == 0
+        out.append([*w.state(), np.asarray([st.candidates, st.manifolds, st.points, st.colours])] +
+                   ([np.frombuffer(bytes(w.episode(t)), np.uint8) for t in range(0, 2100, 50)] if what == "episodes" else []))
+        w.close()
+    for x, y in zip(*out):
+        np.testing.assert_array_equal(x, y)
