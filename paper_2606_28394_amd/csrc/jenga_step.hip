@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <float.h>
 #include <math.h>
 #include <stdint.h>
 #include <type_traits>
@@ -954,12 +955,13 @@ __device__ __forceinline__ float row_lambda(float lam, float u, float k, float b
 }
 
 // the tangent pair's unclipped new impulses projected onto the disc of radius b (both lanes of a
-// pair compute it from the same bits)
+// pair compute it from the same bits).  A pair whose square is denormal counts as the least normal one:
+// its reciprocal root would be infinite, and a point without normal impulse (b = 0) not finite.
 __device__ __forceinline__ void disc_project(float& l1, float& l2, float b) {
 #pragma clang fp contract(off)
   const float s2 = __builtin_fmaf(l1, l1, l2 * l2);
   if (s2 > b * b) {
-    const float f = b * __builtin_amdgcn_rsqf(s2);
+    const float f = b * __builtin_amdgcn_rsqf(fmaxf(s2, FLT_MIN));
     l1 *= f;
     l2 *= f;
   }
