@@ -1661,12 +1661,9 @@ __device__ __forceinline__ void record_solution(const Lds& L, int m, float* rec)
   }
 }
 
-// Natural-map residual of each tower (RMS over its rows and max |r|) into tres: partial sums per
-// canonical pair in psum / pmax (which may alias cab / cpos: each entry is read before it is
-// written), then each tower's contiguous canonical range.  With `only`, towers whose flag is
-// clear keep their residual.
 // Each canonical pair's residual terms (pairs first, first + stride, ...); psum and pmax may
-// alias the canonical lists (a pair's entry is read before it is overwritten, by one thread).
+// alias the canonical lists (a pair's entry is read before it is overwritten, by one thread).  With
+// `only`, the towers whose flag is set.
 __device__ __forceinline__ void residual_parts(const Lds& L, int nman, int first, int stride, float* psum, float* pmax,
                                                const uint32_t* only, const SolveOpts& o) {
   for (int p = first; p < nman; p += stride) {
@@ -1681,14 +1678,11 @@ __device__ __forceinline__ void residual_parts(const Lds& L, int nman, int first
   }
 }
 
-// The towers' residuals from the pairs' terms (fixed summation order); `parts` false when the
-// terms are already in psum and pmax.
-__device__ __forceinline__ void tower_residuals(const Lds& L, int nman, int nt, int lane, float* psum, float* pmax,
-                                const uint32_t* only, const SolveOpts& o, bool parts = true) {
-  if (parts) {
-    residual_parts(L, nman, lane, kWave, psum, pmax, only, o);
-    wave_sync();
-  }
+// Natural-map residual of each tower (RMS over its rows and max |r|) into tres, by one wave: the pairs'
+// terms in psum and pmax over the tower's contiguous canonical range, in a fixed order.  With `only`,
+// towers whose flag is clear keep theirs.
+__device__ __forceinline__ void tower_residuals(const Lds& L, int nt, int lane, const float* psum, const float* pmax,
+                                                const uint32_t* only) {
   if (nt == 1) {
     // one tower (an island): the whole wave reduces its range
     if (!only || only[0]) {
@@ -1723,9 +1717,6 @@ __device__ __forceinline__ void tower_residuals(const Lds& L, int nman, int nt, 
   }
 }
 
-// Contact manifolds of the canonical pairs p = first, first + stride, ... < nman, written into
-// their colour-sorted slots (points, normal, depth, and the previous step's impulses when kept).
-// Pairs are independent, so any number of threads can share the list.
 // The contact points of colliding pair (i, j) (j the ground when `ground`): lever arms r_A in the
 // contact frame into rec[0..12), the normal (from i to j) and depth; returns the point count and
 // the points' slots (4 bits each).  The ground: Sec. "Narrowphase" reading R18; two boxes: the
@@ -1849,6 +1840,9 @@ __device__ __forceinline__ int sat_slot(const Lds& L, int nw, int p) {
   return start[w] + (p - pre[w]);
 }
 
+// Contact manifolds of the canonical pairs p = first, first + stride, ... < nman, written into
+// their colour-sorted slots (points, normal, depth, and the previous step's impulses when kept).
+// Pairs are independent, so any number of threads can share the list.
 // kFar: the previous step's store lies in prev_data from slot `slot0` on (one-wave packs)
 template <bool kExt, bool kFar>
 __device__ __forceinline__ void build_manifolds(const Lds& L, const StepArgs& a, const float* sat, int nw, int first,
@@ -3121,7 +3115,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel
           residual_parts(L, nman, tid, nthr, L.rpart, L.rpart + PC, nullptr, opts);
           sync();
           if (wave == 0) {
-            tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, nullptr, opts, false);
+            tower_residuals(L, nt, lane, L.rpart, L.rpart + PC, nullptr);
             wave_sync();
             int any = 0;
             for (int t = lane; t < nt; t += kWave) {
@@ -3160,7 +3154,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel
             if (wave == 0) {
               for (int t = lane; t < nt; t += kWave)
                 if (L.tfb[t]) { L.tfc[2 * t] += 1u; L.tfc[2 * t + 1] += (uint32_t)L.tpts[t]; }
-              tower_residuals(L, nman, nt, lane, L.rpart, L.rpart + PC, L.tfb, opts, false);
+              tower_residuals(L, nt, lane, L.rpart, L.rpart + PC, L.tfb);
             }
           }
           sync();
@@ -3243,7 +3237,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel
         float* const pmax = reinterpret_cast<float*>(L.cpos);
         residual_parts(L, nman, tid, nthr, psum, pmax, nullptr, opts);
         sync();
-        if (wave == 0) tower_residuals(L, nman, nt, lane, psum, pmax, nullptr, opts, false);
+        if (wave == 0) tower_residuals(L, nt, lane, psum, pmax, nullptr);
         sync();
         timer.mark(L, tid, 7);
       }
