@@ -404,9 +404,12 @@ int32_t build_layout(jg_world* w) {
   for (const auto& pr : w->pushes) ++tower_pushes[w->body_tower[pr.body]];
   for (int t : order) {
     const int n = (int)w->tower_bodies[t].size();
-    // an island beyond the LDS path (register broadphase windows, or LDS) is a global pack
+    // an island beyond the LDS path (register broadphase windows, or LDS) is a global pack; a small batch's
+    // workgroups need less of it, and step a tower that fits them faster (256 stones with the previous step's
+    // start: 0.23 ms, 0.52 in device memory)
+    const bool small = lat && lds_of(n, 1, tower_pushes[t], lat) <= 160 * 1024;
     if (n > jg::kRegBodies || w->prm.pack_bodies < 0 ||
-        jg::full_words(n, pc_of(n), 1, std::max(1, tower_pushes[t]), mode) * 4 > 160 * 1024) {
+        (!small && jg::full_words(n, pc_of(n), 1, std::max(1, tower_pushes[t]), mode) * 4 > 160 * 1024)) {
       Bin b;
       b.bodies = n; b.cap = n; b.towers.push_back(t); b.global = true;
       bins.push_back(b);
@@ -422,7 +425,7 @@ int32_t build_layout(jg_world* w) {
       Bin b;
       b.bodies = n; b.cap = std::max(target, n); b.pushes = tower_pushes[t]; b.towers.push_back(t);
       // (a small batch's tower whose waves' shared words do not fit beside it is stepped by one wave)
-      if (lat && lds_of(n, 1, tower_pushes[t], lat) <= 160 * 1024) b.lat = lat;
+      if (small) b.lat = lat;
       bins.push_back(b);
     }
   }
