@@ -109,6 +109,7 @@ struct StepArgs {
   int32_t lat;     // small batches: threads of the workgroup that steps one tower (0: not one)
   int32_t waves;   // packs in device memory: waves of a workgroup
   int32_t many;    // one-wave packs: three to a SIMD
+  int32_t pairs;   // one-wave packs: the sorted pairs' words on chip (the plain kernel; the network's has them so)
   int32_t nbp;     // bodies per pack
   int32_t pc;      // manifolds per pack
   int32_t tpc;     // towers per pack
@@ -180,8 +181,8 @@ inline int64_t hot_words(int nbp, int tpc, int ppc, bool bodies, int waves) {
 // feature records); 2 learned warm start: the store plus network input staging, saved
 // velocities (6 per body), residual partials (2 per manifold), fallback state (3 per tower).
 // lists: the canonical pairs, both lane masks, the whole store and the learned start's terms are part of the
-// layout (small batches, islands); a one-wave pack has the sorted pairs' words on chip instead where the
-// network's registers leave LDS over (pairs_on_chip)
+// layout (small batches, islands); a one-wave pack has the sorted pairs' words on chip instead where LDS is
+// left over: with the network's registers (pairs_on_chip), or where the batch's packs are resident all the same
 inline bool pairs_on_chip(int mode, bool features) { return mode == 2 || features; }
 inline int64_t lds_words(int nbp, int pc, int tpc, int ppc, int mode, bool lists, bool pairs) {
   int64_t w = 0;
@@ -212,7 +213,7 @@ inline int64_t pack_store_words(int nbp, int pc, int mode) {
 
 // the step kernel's variants (each defined by the build part that compiles it): packs on chip, small
 // batches, islands in device memory (hot: the walks' body arrays in LDS), and with the network
-const void* step_variant_pack(bool ext, bool many);
+const void* step_variant_pack(bool ext, bool many, bool pairs);
 const void* step_variant_lat(bool ext);
 const void* step_variant_island(bool hot, bool ext);
 const void* step_variant_learned_pack();

@@ -2699,9 +2699,11 @@ constexpr int step_threads() {
 // either compiles to flat instructions, which are as slow as device memory even on LDS).
 // kExt: the solver variants (disc friction, restitution targets, reference-face clipping) and the
 // episode criteria are compiled in; the default plain kernel carries none of their registers.
+// kPairs: the sorted pairs' words in LDS, where every pack of the batch is resident all the same (1,500 towers of
+// 12 to 24 levels, two steps: 0.967 ms, 0.992 with the words in device memory).
 // kMany: three waves to a SIMD instead of two (the registers of a third spilled), where that saves rounds of
 // packs: twelve to a CU take 1.28 times as long as eight (jg_commit chooses, for the criteria's kernel too).
-template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false, bool kMany = false>
+template <bool kLearned, bool kGlobal, bool kHot, bool kExt, bool kLat = false, bool kMany = false, bool kPairs = kLearned>
 __global__ void __launch_bounds__((step_threads<kLearned, kGlobal, kLat>()))
 __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel(StepArgs a) {
   constexpr bool kMulti = kGlobal || kLat;   // several waves
@@ -2711,7 +2713,7 @@ __attribute__((amdgpu_waves_per_eu(kLearned ? 1 : (kMany ? 3 : 2)))) step_kernel
   constexpr bool kFar = !kMulti && (kLearned || !kExt);
   extern __shared__ __align__(16) float smem[];
   float* const dev = a.gmem + a.pack_goff[a.pack_first + blockIdx.x];
-  const Lds L = carve(kGlobal ? dev + kManPackWords * a.pc : smem, dev, smem, kGlobal, kGlobal && kHot, kMulti, kFar, kLearned && !kMulti, a);
+  const Lds L = carve(kGlobal ? dev + kManPackWords * a.pc : smem, dev, smem, kGlobal, kGlobal && kHot, kMulti, kFar, kPairs && !kMulti, a);
   const bool keep_prev = lds_mode(a) >= 1;   // previous-step store kept (warm start or records)
   const int tid = threadIdx.x;
   const int nthr = kMulti ? (int)blockDim.x : kWave;
@@ -4663,10 +4665,11 @@ __global__ void __launch_bounds__(kMegaThreads) mega_kernel(MegaArgs a) {
 
 // The step kernel's variants, by part of the build (this file is compiled once per part, side by side)
 #if JG_STEP_PART == 1
-const void* step_variant_pack(bool ext, bool many) {
+const void* step_variant_pack(bool ext, bool many, bool pairs) {
   if (ext)
     return many ? (const void*)step_kernel<false, false, false, true, false, true>
                 : (const void*)step_kernel<false, false, false, true>;
+  if (pairs) return (const void*)step_kernel<false, false, false, false, false, false, true>;
   return many ? (const void*)step_kernel<false, false, false, false, false, true>
               : (const void*)step_kernel<false, false, false, false>;
 }
@@ -4705,9 +4708,10 @@ int ensure_lds_limit() {
   if (dev < 0 || dev >= kMaxDevices) return (int)hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(attr_mutex);
   if (!attr_set[dev]) {
-    const void* variants[14] = {(const void*)mega_kernel,
-                                step_variant_pack(false, false),   step_variant_pack(false, true),
-                                step_variant_pack(true, false),    step_variant_pack(true, true),
+    const void* variants[15] = {(const void*)mega_kernel,
+                                step_variant_pack(false, false, false), step_variant_pack(false, false, true),
+                                step_variant_pack(false, true, false),
+                                step_variant_pack(true, false, false),  step_variant_pack(true, true, false),
                                 step_variant_lat(false),           step_variant_lat(true),
                                 step_variant_island(false, false), step_variant_island(false, true),
                                 step_variant_island(true, false),  step_variant_island(true, true),
@@ -4741,7 +4745,7 @@ int step_launch_config(const StepArgs& a, const void** func, unsigned* block_thr
     *func = step_variant_lat(ext);
     threads = (unsigned)a.lat;
   } else {
-    *func = step_variant_pack(ext, a.many != 0);
+    *func = step_variant_pack(ext, a.many != 0, a.pairs != 0);
   }
   *block_threads = threads;
   return 0;

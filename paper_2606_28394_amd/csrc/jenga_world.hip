@@ -179,6 +179,7 @@ struct jg_world {
   };
   std::vector<Mega> megas;
   bool many = false;                // one-wave packs three to a SIMD
+  bool pairs = false;               // and with the sorted pairs' words on chip
   std::vector<int> mega_of_tower;   // tower id -> index in megas (-1: in a pack)
 };
 
@@ -268,10 +269,12 @@ int32_t build_layout(jg_world* w) {
   // workgroup (below) has LDS to spare and gets 6, room for a sinking or collapsing tower's pairs
   float mpb = w->prm.manifolds_per_body > 0.f ? w->prm.manifolds_per_body : 3.5f;
   const int mode = w->prm.warm_start == 2 ? 2 : ((w->prm.warm_start == 1 || w->prm.record_features) ? 1 : 0);
-  const bool pairs = jg::pairs_on_chip(mode, w->prm.record_features != 0);
+  bool pairs = jg::pairs_on_chip(mode, w->prm.record_features != 0);
   int pool = 16;   // manifold slots that every pack has
   auto pc_of = [&](int nb) { return std::max(pool, (int)std::ceil(mpb * nb)); };
   int lat = 0;   // threads of a small batch's workgroups
+  std::vector<int> tower_pushes(T, 0);
+  for (const auto& pr : w->pushes) ++tower_pushes[w->body_tower[pr.body]];
   // LDS of a pack stepped by one wave, or by `threads` threads
   auto lds_of = [&](int nb, int towers, int pushes, int threads) -> size_t {
     return (size_t)(jg::lds_words(nb, pc_of(nb), std::max(1, towers), std::max(1, pushes), mode, threads != 0, pairs) +
@@ -316,6 +319,16 @@ int32_t build_layout(jg_world* w) {
       // per SIMD), or of eight where every tower has a CU to itself, which share its step
       if (w->prm.small_batch >= 0 && !wide && (int64_t)order.size() <= 2 * (int64_t)cus)
         lat = (int64_t)order.size() <= (int64_t)cus ? 8 * jg::kWave : 4 * jg::kWave;
+      if (!lat && !wide) {
+        int nbp = 1, ppc = 1;
+        for (int t : order) {
+          if (w->tower_bodies[t].size() > (size_t)jg::kRegBodies) continue;
+          nbp = std::max(nbp, (int)w->tower_bodies[t].size());
+          ppc = std::max(ppc, tower_pushes[t]);
+        }
+        pairs = true;
+        pairs = (int64_t)order.size() <= (int64_t)cus * std::min(few_packs, per_cu_lds(lds_of(nbp, 1, ppc, 0)));
+      }
     } else if (cus > 0) {
       // A pack's time grows with its bodies, from what 64 of them cost on; beyond 128 its colours
       // have more manifolds than a wave has lanes.  With the network, most of the work is per
@@ -400,8 +413,6 @@ int32_t build_layout(jg_world* w) {
   });
   struct Bin { int bodies = 0, cap = 0, lat = 0, pushes = 0; std::vector<int> towers; bool global = false; };
   std::vector<Bin> bins;
-  std::vector<int> tower_pushes(T, 0);
-  for (const auto& pr : w->pushes) ++tower_pushes[w->body_tower[pr.body]];
   for (int t : order) {
     const int n = (int)w->tower_bodies[t].size();
     // an island beyond the LDS path (register broadphase windows, or LDS) is a global pack; a small batch's
@@ -468,6 +479,7 @@ int32_t build_layout(jg_world* w) {
     w->many = many_packs > few_packs && cus > 0 && packs > 0 &&
               kManyTime * time(held[1], many_packs) < time(held[0], few_packs);
   }
+  w->pairs = pairs;
   const int reg_packs = w->many ? many_packs : few_packs;
   // internal order
   const int N = (int)w->he.size() / 3;
@@ -1245,6 +1257,7 @@ int32_t jg_step_batch(jg_world* w, int32_t n_steps) {
     cls[k].lat = c.lat;
     cls[k].waves = c.waves;
     cls[k].many = w->many ? 1 : 0;
+    cls[k].pairs = w->pairs ? 1 : 0;
     cls[k].pack_goff = w->d_pack_goff.p;
   }
   if (w->prm.use_graph) {

@@ -128,3 +128,11 @@ def test_shared_packs_of_both_builds_give_the_same_bits(J, what, start):
         w.close()
     for x, y in zip(*out):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("start", [0, 1])
+def test_pair_words_on_chip_give_the_same_bits(J, start):
+    """600 towers, one to a pack with its pairs' words in LDS, and in shared packs with them in device memory."""
+    sc = W.tilted_towers(5, 600, levels_range=(8, 20), n_steps=8)
+    for x, y in zip(_after(J, sc, warm_start=start), _after(J, sc, warm_start=start, pack_bodies=128)):
+        np.testing.assert_array_equal(x, y)
