@@ -84,9 +84,11 @@ typedef struct {
   void* stream;          /* hipStream_t for all GPU work; NULL = default stream */
   int32_t pack_bodies;   /* bodies per on-chip pack (at most 256); 0 = automatic (one tower per pack when
                             the batch has no more towers than the GPU holds workgroups at once, else the
-                            largest pack that keeps 8, or with features 4, workgroups per CU); -1 = every
+                            size whose packs take the least time in rounds of what it holds); -1 = every
                             tower keeps its state in device memory (the path of islands over 256 bodies) */
-  float manifolds_per_body;  /* manifold capacity per body in a pack; 0 = automatic (3.5) */
+  float manifolds_per_body;  /* manifold capacity per body in a pack; 0 = automatic (6 with one tower per
+                                pack, else 3.5, and no fewer in a pack than one that fills 20 KB, or 40
+                                with features, has) */
   int32_t mlp_iters;     /* PGS iterations after a learned warm start; default 8 */
   double fallback_tau;   /* tower residual [m/s] above which a learned solve is redone plainly
                             (pre-solve velocities, zero impulses, iters sweeps); default 1e30 */

@@ -2,9 +2,9 @@
 
 The step kernel gives each workgroup a pack of whole towers.  A larger pack fills more of
 a wave's 64 lanes in every colour of the coloured Gauss-Seidel sweep, but needs more LDS,
-so fewer workgroups share a compute unit.  The library picks the largest pack that keeps
-eight workgroups per CU (``pack_bodies = 0``); this tuner times a few pack sizes on the
-batch itself and keeps the fastest.
+so fewer workgroups share a compute unit.  The library picks the size whose packs take the
+least time in rounds of what the GPU holds, by a fixed estimate of a pack's time
+(``pack_bodies = 0``); this tuner times a few pack sizes on the batch itself and keeps the fastest.
 
 It runs the batch for ``lead_in`` steps first (the tilted towers are falling by then, so
 the contacts are those of the collapse, not of the intact towers), then builds one world

@@ -307,7 +307,7 @@ struct MegaArgs {
 // queues the cooperative launch of an island's steps (blocks from mega_blocks); a hipError_t
 int launch_mega(const MegaArgs& a, int blocks, void* stream);
 // the workgroups of the grid-wide kernel for an island of `bodies` bodies: every one resident at
-// once (at most the occupancy of the current device times its CUs, two per CU); a hipError_t
+// once (one per 128 bodies, at least four, and at most one per CU, whose LDS it takes); a hipError_t
 int mega_blocks(int bodies, int* blocks);
 
 }  // namespace jg

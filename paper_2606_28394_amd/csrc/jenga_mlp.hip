@@ -83,8 +83,8 @@ __global__ void mlp_pack_kernel(const float* __restrict__ P, uint4* __restrict__
 
 // Batch inference.  A workgroup keeps the packed network (45 KB) in LDS and its waves walk the rows
 // 32 at a time.  The two GELU layers bound it (about 17 VALU instructions per activation, two of them
-// at a quarter of the rate): with the weights in LDS a wave needs 94 registers instead of 500, so
-// four share a SIMD instead of one (200,003 rows: 40 us, from 55).  Chunks are dealt to workgroups
+// at a quarter of the rate): with the weights in LDS a wave needs 114 registers instead of 500, so
+// four share a SIMD instead of one (200,003 rows: 35.5 us, from 55).  Chunks are dealt to workgroups
 // first and to their waves last, so that a small batch has a SIMD to each wave.
 constexpr int kInferWaves = 8;
 constexpr int kInferRows = 32;

@@ -1390,7 +1390,8 @@ __device__ __forceinline__ void visit_owned(float4* vw, OwnedManifold& w, const 
 // and its LDS round trip are what counts: about 210 instead of 546.  Two manifolds to a pair of a
 // four-wave workgroup cover towers of up to 256 manifolds (28 levels) at the two waves per SIMD that
 // let a CU hold two towers (with one to a pair the 156 manifolds of 18 levels had fallen back to
-// pgs_sweeps: 429 us a step, now 204); eight waves cover 512.  The bits are those
+// pgs_sweeps: 429 us a step; with two in a four-wave workgroup 204, in one of eight waves, which covers
+// 512, 167 for the whole step).  The bits are those
 // of pgs_sweeps (the pair mode, which single lanes match bit for bit).  A tower with more
 // manifolds, or the disc friction variant, takes pgs_sweeps.  Every thread passes the same barriers.
 __device__ __forceinline__ void pgs_sweeps_lat(const Lds& L, int sweeps, int ncol, int tid, int nthr, int nb,
@@ -2159,7 +2160,8 @@ __device__ __forceinline__ void learned_chunks(const Lds& L, const StepArgs& a, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// episodes (Sec. "Stability Detection and Collapse"): at the end of each step, one lane per tower
+// episodes (Sec. "Stability Detection and Collapse"): at the end of each step; a tower's sums on the
+// lanes of a wave, its support polygon and the rules on one lane
 // ------------------------------------------------------------------------------------------------
 // The support polygon of Eq. (stability): the horizontal corners of every active block whose lowest
 // point is within eps of the ground, staged in scratch (16 floats per body of the tower), wrapped
@@ -2691,8 +2693,8 @@ constexpr int step_threads() {
   return kGlobal ? (kLearned ? kLearnedIslandWaves : kIslandWaves) * kWave : (kLat ? kLatencyWaves * kWave : kWave);
 }
 
-// The plain variants are held to two waves per SIMD (at most 256 registers): occupancy is what
-// hides the latency of the pack's serial phases, and a register count that drifts above 256
+// The plain variants are held to two waves per SIMD (at most 256 registers; kMany: three, 168): occupancy is
+// what hides the latency of the pack's serial phases, and a register count that drifts above that
 // would halve it.
 // kHot (packs in device memory): the body arrays of the serial walks are in LDS too.  It is a
 // template parameter so that every access has one known address space (a pointer that may be

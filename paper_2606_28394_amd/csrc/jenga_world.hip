@@ -238,12 +238,13 @@ int32_t download_state(jg_world* w) {
 }
 
 // Pack towers into workgroups (first fit, largest first).  A pack holds whole towers and at
-// most `target` bodies, where `target` is the largest pack whose LDS fits as many workgroups on
-// a CU as the step kernel's registers allow: eight (two waves per SIMD) for the plain variant,
-// four for the variant with contact features (learned warm start, feature records); or one
-// tower per pack when the batch has no more towers than the GPU holds such workgroups.  A tower
-// larger than the target gets a pack of its own.  Packs are then grouped into launch
-// classes of equal workgroups-per-CU, each launched with the LDS its largest pack needs.
+// most `target` bodies: one tower when the batch has no more towers than the GPU holds workgroups
+// at once (eight to a CU, four with contact features: learned warm start, feature records), each then with
+// several waves where there are at most two towers to a CU; else the size with the least time in rounds
+// of what the GPU holds (by LDS, and by registers eight packs to a CU or twelve, four with contact
+// features).  A tower larger than the target gets a pack of its own, one too large for LDS a pack in
+// device memory.  Packs are then grouped into launch classes of equal workgroups-per-CU, each launched
+// with the LDS its largest pack needs.
 int32_t build_layout(jg_world* w) {
   const int T = (int)w->tower_bodies.size();
   std::vector<int> order, mega_towers;
