@@ -293,20 +293,23 @@ int32_t build_layout(jg_world* w) {
   const int few_packs = wide ? 4 : 8, many_packs = wide || variants ? few_packs : 12;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, w->prm.device) != hipSuccess) cus = 0;
-  // The packs run in rounds of what the GPU holds at once.  The time of `h` such rounds of one-wave packs, in
-  // rounds: one if they fit at once; else the last round costs 0.6 of a whole one as soon as it holds a pack,
-  // and packs that fill the rounds to the last place (0.8 %) start another: 8,192 towers of 36 to 72 boxes, four
-  // steps, 5.46 ms in 1.95 rounds, 7.08 in 2.00, 6.55 in 2.46 of smaller packs.
-  auto rounds = [](double h, bool once) {
+  // The packs run in rounds of what the GPU holds at once, `h` of them for packs that `most` fit a CU by registers.
+  // Their time, in rounds: a last round that is nearly empty costs a whole one of two, and less of it after
+  // more rounds, in which the packs have drawn apart.  Two waves to a SIMD do not fill their last places
+  // (8,192 towers of 36 to 72 boxes, four steps: 5.46 ms in 1.95 rounds, 7.08 in 2.00 of smaller packs).
+  auto rounds = [&](double h, int most, bool once) {
     if (once) return 1.0;
-    h = std::max(1.0, 1.008 * h);
-    return std::floor(h) + 0.6 + 0.4 * (h - std::floor(h));
+    if (!wide && most == few_packs) h *= 1.008;
+    const double c = std::ceil(h);
+    return c < 2.0 ? 1.03 : h + (c - h) / (c - 1.0);   // (one round of several launches leaves some of the CUs' LDS)
   };
   // A round of twelve packs to a CU takes this much longer than one of eight of the same size: 4,096 such towers
   // 2.72 ms in one round of packs of 108, eight to a CU, 3.03 in one of packs of 92; 8,192 5.46 in
   // two of 111, 5.64 in two of 92; 4,096 falling towers of 24 to 120 boxes, two steps, 2.31 in one of 144,
-  // 2.13 in one of 120.
-  constexpr double kManyTime = 1.28;
+  // 2.13 in one of 120; 16,384 of them 7.40 in five of 124, 7.29 in four of 110 (20 steps of their collapse 71.6
+  // and 65.9).
+  constexpr double kManyTime = 1.27;
+  int chosen = 0;   // packs to a CU by registers, with the size below
   if (target <= 0) {
     target = 8;   // bodies of a pack as the LDS allows with every wave that the registers do
     while (target < jg::kRegBodies && per_cu_lds(lds_of(target + 1, 4, w->pushes.empty() ? 1 : 8, 0)) >= many_packs) ++target;
@@ -402,8 +405,8 @@ int32_t build_layout(jg_world* w) {
           // (one round if the packs fit with the largest one's LDS each: CUs that hold packs of several sizes
           // leave some of it)
           const bool once = packs <= (int64_t)cus * std::min(most, fit[std::max(cap, largest)]);
-          const double cost = rounds(held / (double)cus, once) * size * (most > few_packs ? kManyTime : 1.0);
-          if (best == 0.0 || cost < best || (cost == best && most == few_packs)) { best = cost; target = cap; }
+          const double cost = rounds(held / (double)cus, most, once) * size * (most > few_packs ? kManyTime : 1.0);
+          if (best == 0.0 || cost < best || (cost == best && most == few_packs)) { best = cost; target = cap; chosen = most; }
           if (most == many_packs) break;   // (one build)
         }
       }
@@ -460,7 +463,8 @@ int32_t build_layout(jg_world* w) {
     for (size_t b : idx) sorted.push_back(std::move(bins[b]));
     bins.swap(sorted);
   }
-  // the plain kernel's build, by the same figures for the packs as they came out
+  // the plain kernel's build: as chosen with the size, or by the same figures for the packs of a given size; two
+  // waves to a SIMD where LDS holds no more
   int packs = 0;
   {
     double held[2] = {0.0, 0.0};
@@ -476,9 +480,10 @@ int32_t build_layout(jg_world* w) {
       ++packs;
     }
     const int fit = per_cu_lds(lds_of(nbp, tpc, ppc, 0));
-    auto time = [&](double h, int most) { return rounds(h / cus, packs <= (int64_t)cus * std::min(most, fit)); };
-    w->many = many_packs > few_packs && cus > 0 && packs > 0 &&
-              kManyTime * time(held[1], many_packs) < time(held[0], few_packs);
+    auto time = [&](double h, int most) { return rounds(h / cus, most, packs <= (int64_t)cus * std::min(most, fit)); };
+    w->many = many_packs > few_packs && cus > 0 && held[1] < held[0] &&
+              (chosen ? chosen == many_packs
+                      : kManyTime * time(held[1], many_packs) < time(held[0], few_packs));
   }
   w->pairs = pairs;
   const int reg_packs = w->many ? many_packs : few_packs;
